@@ -133,19 +133,20 @@ RepDev make_rep(const nem_params& p, int nc, int cell_base, int part_base, int n
 
 // Offsets of every buffer for given sizes (shared by nem_arena_bytes and carve()).
 struct Offs {
-  size_t reps, work, cell_start, count, cursor, perm;
+  size_t reps, work, hdr, cell_start, count, cursor, perm;
   size_t t_key, t_off, t_lo, t_u, t_q, t_drho, t_acc, t_id, t_img, t_qyy;
   size_t off0, off1, offlo, u, q0, q1, drho, acc, id, cell, img, qyy0, qyy1;
   size_t V, bk, dh, apart, uv, pi, P, drhat, flags, umax, stage, red, nl, ncnt, fe, vl, vcnt, off_build;
   size_t total;
 };
 
-Offs layout(int R, int64_t ntot, int64_t ncells, int64_t work_cap, int64_t stage_n) {
+Offs layout(int R, int64_t ntot, int64_t ncells, int64_t work_cap, int64_t stage_n, int64_t hdr_cap) {
   Layout L;
   Offs o;
   const size_t N = (size_t)ntot, C = (size_t)ncells;
   o.reps = L.put(sizeof(RepDev) * R);
   o.work = L.put(sizeof(int) * 2 * (size_t)work_cap);
+  o.hdr = L.put(sizeof(int) * (size_t)hdr_cap);
   o.cell_start = L.put(sizeof(int) * (C + 1));
   o.count = L.put(sizeof(int) * C);
   o.cursor = L.put(sizeof(int) * C);
@@ -195,10 +196,11 @@ Offs layout(int R, int64_t ntot, int64_t ncells, int64_t work_cap, int64_t stage
   return o;
 }
 
-struct Sizes { int64_t ntot = 0, ncells = 0, work_cap = 0, stage_n = 0; };
+struct Sizes { int64_t ntot = 0, ncells = 0, work_cap = 0, stage_n = 0, hdr_cap = 0; };
 
 int sizes_for(const nem_params* p, const int64_t* n, int R, Sizes& s, std::string& why) {
   if (R < 1 || R > 4096) { why = "replica count out of range"; return NEM_E_INVAL; }
+  int64_t work8 = 0;
   for (int r = 0; r < R; ++r) {
     int rc = check_params(p[r], n[r], why);
     if (rc) return rc;
@@ -213,8 +215,10 @@ int sizes_for(const nem_params* p, const int64_t* n, int R, Sizes& s, std::strin
     s.ncells += (int64_t)nc * nc;
     const int64_t t4 = (int64_t)tiles_for(nc, 4);
     s.work_cap += t4 * t4;
+    work8 += (int64_t)tiles_for(nc, 8) * tiles_for(nc, 8);
     s.stage_n = std::max<int64_t>(s.stage_n, n[r]);
   }
+  s.hdr_cap = std::max(s.work_cap * tile_header_ints(4), work8 * tile_header_ints(8));
   if (s.ntot >= ((int64_t)1 << 31) - 1 || s.ncells >= ((int64_t)1 << 31) - 2) {
     why = "more than 2^31 particles or cells";
     return NEM_E_INVAL;
@@ -239,7 +243,7 @@ StepArgs step_args(nem_sim* s) {
   StepArgs a;
   const int c = s->parity, x = 1 - s->parity;
   a.reps = s->d_reps; a.work = s->d_work; a.nwork = s->nwork; a.T = s->T; a.lpp = s->LPP; a.grid = s->persist;
-  a.cell_start = s->cell_start; a.ncells = s->ncells; a.ntot = s->ntot;
+  a.hdr = s->d_hdr; a.cell_start = s->cell_start; a.ncells = s->ncells; a.ntot = s->ntot;
   a.off_cur = s->off[c]; a.off_nxt = s->off[x]; a.offlo = s->offlo; a.u = s->u;
   a.q_cur = s->q[c]; a.q_nxt = s->q[x]; a.acc = s->acc; a.drho = s->drho; a.cell = s->cell;
   a.qyy_cur = s->qyy[c]; a.qyy_nxt = s->qyy[x];
@@ -286,7 +290,13 @@ int build_work(nem_sim* s) {
   HIPCHK(hipMemcpyAsync(s->d_work, w.data(), w.size() * sizeof(int), hipMemcpyHostToDevice, s->stream));
   HIPCHK(hipMemcpyAsync(s->d_reps, s->reps.data(), sizeof(RepDev) * s->R, hipMemcpyHostToDevice, s->stream));
   HIPCHK(hipStreamSynchronize(s->stream));
+  build_headers(s, nullptr, s->stream);
   return NEM_OK;
+}
+
+// Tile headers of the current cells (gate: only when *gate != 0).
+void build_headers(nem_sim* s, const unsigned* gate, hipStream_t st) {
+  launch_tile_headers(s->T, s->hp[0].kernel, step_args(s), s->d_hdr, gate, st);
 }
 
 int read_flags(nem_sim* s, unsigned* f) {
@@ -363,6 +373,7 @@ int enqueue_prologue(nem_sim* s, hipStream_t st) {
     SortArgs a = sort_args(s, s->flags + 1);
     launch_rebin_key(a, st);
     launch_sort_tail(a, 0, s->ntot, 0, s->ncells, 0, st);
+    build_headers(s, s->flags + 1, st);
   }
   StepArgs a = step_args(s);
   launch_step_begin(s->flags, a.umax_nxt, s->R, st);
@@ -516,7 +527,7 @@ int nem_arena_bytes(const nem_params* p, const int64_t* n, int32_t R, uint64_t* 
   std::string why;
   int rc = sizes_for(p, n, R, z, why);
   if (rc) return rc;
-  *bytes = layout(R, z.ntot, z.ncells, z.work_cap, z.stage_n).total;
+  *bytes = layout(R, z.ntot, z.ncells, z.work_cap, z.stage_n, z.hdr_cap).total;
   return NEM_OK;
 }
 
@@ -537,7 +548,7 @@ int nem_create(const nem_params* p, const int64_t* n, int32_t R, void* dev_arena
   s->work_cap = (int)z.work_cap;
   s->stage_n = z.stage_n;
   s->stream = (hipStream_t)hip_stream;
-  const Offs o = layout(R, z.ntot, z.ncells, z.work_cap, z.stage_n);
+  const Offs o = layout(R, z.ntot, z.ncells, z.work_cap, z.stage_n, z.hdr_cap);
   if (dev_arena) {
     if (arena_bytes < o.total) { delete s; return NEM_E_NOMEM; }
     s->arena = (char*)dev_arena;
@@ -551,6 +562,7 @@ int nem_create(const nem_params* p, const int64_t* n, int32_t R, void* dev_arena
   }
   char* b = (char*)(((uintptr_t)s->arena + ALIGN - 1) / ALIGN * ALIGN);
   s->d_reps = (RepDev*)(b + o.reps); s->d_work = (int*)(b + o.work);
+  s->d_hdr = (int*)(b + o.hdr);
   s->cell_start = (int*)(b + o.cell_start); s->count = (int*)(b + o.count);
   s->cursor = (int*)(b + o.cursor); s->perm = (int*)(b + o.perm);
   s->t_key = (int*)(b + o.t_key); s->t_off = (float2*)(b + o.t_off); s->t_lo = (float2*)(b + o.t_lo);
@@ -611,6 +623,7 @@ int nem_set_state(nem_sim* s, int32_t r, const double* x, const double* y, const
   SortArgs a = sort_args(s, nullptr);
   launch_ingest(a, r, s->stage, n, s->umax + (size_t)s->parity * s->R * UMAX_SLOTS, s->stream);
   launch_sort_tail(a, R.part_base, n, R.cell_base, R.nc * R.nc, R.part_base, s->stream);
+  build_headers(s, nullptr, s->stream);
   launch_request_relist(s->flags, s->stream);
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(s->stream));
@@ -812,6 +825,7 @@ int nem_load_raw(nem_sim* s, const void* host, uint64_t bytes) {
     HIPCHK(hipMemcpyAsync(g.dev, w, g.bytes, hipMemcpyHostToDevice, s->stream));
     w += g.bytes;
   }
+  build_headers(s, nullptr, s->stream);
   HIPCHK(hipStreamSynchronize(s->stream));
   for (int r = 0; r < s->R; ++r) s->has_state[r] = 1;
   for (auto& sn : s->snap) sn.valid = false;

@@ -55,6 +55,7 @@ struct StepArgs {
   int nwork, T;           // work items, tile side in cells
   int lpp;                // lanes per particle in passes B-D (1, 2, 4)
   int grid;               // 0: one workgroup per tile; > 0: persistent grid size
+  const int* hdr;         // tile headers (layout in nem_pair.h), one per work item
   const int* cell_start;  // [ncells + 1], particles sorted by (replica, cell, id)
   int ncells, ntot;
   const float2* off_cur;  // cell-relative position (high part) at r^{n+1/2}
@@ -116,6 +117,8 @@ struct SortArgs {
 
 // Launchers (nem_passes.hip, nem_sort.hip).
 bool launch_pass(int pass, const PassCfg& c, const StepArgs& a, hipStream_t s);
+void launch_tile_headers(int T, int kern, const StepArgs& a, int* hdr, const unsigned* gate, hipStream_t s);
+int tile_header_ints(int T);
 bool launch_pass_a_verlet(const PassCfg& c, const StepArgs& a, hipStream_t s);
 void launch_request_relist(unsigned* flags, hipStream_t st);
 void launch_list_export(int T, int kern, const StepArgs& a, int rep, int which, int mode, int* cnt,

@@ -380,6 +380,7 @@ int restore_snapshot(nem_sim* s, int i) {
   launch_request_relist(s->flags, s->stream);
   s->parity = p;
   for (int r = 0; r < s->R; ++r) s->reps[r].dt = S.dt[r];
+  build_headers(s, nullptr, s->stream);
   int rc = upload_reps(s);
   if (rc) return rc;
   HIPCHK(hipStreamSynchronize(s->stream));

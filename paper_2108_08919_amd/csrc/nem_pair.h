@@ -28,6 +28,23 @@ struct TileLDS {
   float2 shift[16];                 // image shift of stencil direction (dx+1) | (dy+1) << 2
 };
 
+// Tile header, built by k_tile_headers whenever the cells or the tiles change
+// (new state, rebin, tile option, restored state) and read by every pair pass:
+// HDR_CELLS ints {interior particles nin, staged particles S, ni, nj, replica},
+// then one int2 {first global particle, first LDS slot | region x << 16 |
+// region y << 20} per staged cell (interior cells first, region coordinates
+// counted from the halo corner), and a closing entry whose slot is S. A pass
+// therefore starts loading fields one load after its launch; deriving the same
+// from the work list, the replica and cell_start in every pass was a chain of
+// three loads, a scan and a search per staged particle.
+// A tile over the LDS capacity has nin = S = 0 (and ERR_OVERFLOW is raised).
+constexpr int HDR_CELLS = 8;
+template <int T>
+struct HdrCfg {
+  static constexpr int NSC = (T + 2) * (T + 2);
+  static constexpr int INTS = HDR_CELLS + 2 * (NSC + 2);
+};
+
 // Staged-cell index of region cell (li, lj), li in [-1, ni], lj in [-1, nj].
 __device__ inline int staged_index(int li, int lj, int ni, int nj) {
   if (li >= 0 && li < ni && lj >= 0 && lj < nj) return lj * ni + li;
@@ -232,6 +249,67 @@ __device__ __forceinline__ bool tile_begin(const StepArgs& a, int w, TileLDS<T>&
     return false;
   }
   return true;
+}
+
+// ------------------------------------------------- pair passes: header staging
+struct TileRef {
+  const int* H;
+  int nin, S, ni, nj, rep;
+  __device__ __forceinline__ int2 cell(int c) const { return ((const int2*)(H + HDR_CELLS))[c]; }
+  // Global index of interior particle p (= LDS slot p): the cells of an
+  // interior row are contiguous in the sorted arrays.
+  template <int T>
+  __device__ __forceinline__ int global(int p) const {
+    int d = cell(0).x;
+#pragma unroll
+    for (int r = 1; r < T; ++r)
+      if (r < nj) {
+        const int2 e = cell(r * ni);
+        const int c0 = e.y & 0xFFFF;
+        if (p >= c0) d = e.x - c0;
+      }
+    return p + d;
+  }
+};
+
+template <int T>
+__device__ __forceinline__ TileRef tile_ref(const StepArgs& a, int w) {
+  TileRef t;
+  t.H = a.hdr + (size_t)w * HdrCfg<T>::INTS;
+  t.nin = t.H[0]; t.S = t.H[1]; t.ni = t.H[2]; t.nj = t.H[3]; t.rep = t.H[4];
+  return t;
+}
+
+// Stage every particle of the tile and its halo: LPC lanes take one cell each
+// round (LPC = 16 for the quintic's cells of 16 particles, 8 for Wendland's of
+// 7.3). load(g) returns a value, store(slot, entry, value) writes it to LDS; the
+// first particles of all cells of a batch of rounds are loaded before any is
+// stored, so their latencies overlap.
+template <int T, int KERN, typename Load, typename Store>
+__device__ __forceinline__ void stage_tile(const TileRef& t, Load&& load, Store&& store) {
+  constexpr int LPC = KERN == 1 ? 8 : 16, GR = WG / LPC, NSC = HdrCfg<T>::NSC;
+  constexpr int ROUNDS = (NSC + GR - 1) / GR, BATCH = ROUNDS < 4 ? ROUNDS : 4;
+  const int lane = threadIdx.x % LPC, grp = threadIdx.x / LPC;
+#pragma unroll
+  for (int r0 = 0; r0 < ROUNDS; r0 += BATCH) {
+    int2 e[BATCH];
+    int n[BATCH];
+    decltype(load(0)) v[BATCH];
+#pragma unroll
+    for (int b = 0; b < BATCH; ++b) {
+      const int c = min(grp + (r0 + b) * GR, NSC);   // entries past the tile's cells are empty
+      e[b] = t.cell(c);
+      n[b] = (t.cell(c + 1).y & 0xFFFF) - (e[b].y & 0xFFFF);
+    }
+#pragma unroll
+    for (int b = 0; b < BATCH; ++b)
+      if (lane < n[b]) v[b] = load(e[b].x + lane);
+#pragma unroll
+    for (int b = 0; b < BATCH; ++b) {
+      if (lane < n[b]) store((e[b].y & 0xFFFF) + lane, e[b].y, v[b]);
+      for (int k = lane + LPC; k < n[b]; k += LPC) store((e[b].y & 0xFFFF) + k, e[b].y, load(e[b].x + k));
+    }
+  }
 }
 
 // Global index of LDS slot t (staging loop).

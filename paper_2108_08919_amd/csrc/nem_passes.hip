@@ -54,6 +54,78 @@ __device__ __forceinline__ int wave_sum_int(int v, int lpp) {
   return v;
 }
 
+// Image shifts of the 16 stencil direction codes (dx + 1) | (dy + 1) << 2.
+__device__ __forceinline__ void stage_shift(float2* shift, const RepDev& R) {
+  const int t = threadIdx.x;
+  if (t < 16) shift[t] = make_float2((float)(1 - (t & 3)) * R.cs, (float)(1 - (t >> 2)) * R.cs);
+}
+
+// The cell tables of a tile from its header (the Verlet build walks cells).
+template <int T>
+__device__ __forceinline__ void tile_cells(const TileRef& t, TileLDS<T>& L, const RepDev& R) {
+  const int nreg = (t.ni + 2) * (t.nj + 2);
+  const int c = threadIdx.x;
+  if (c <= nreg) {
+    const int2 e = t.cell(c);
+    L.cstart[c] = e.y & 0xFFFF;
+    if (c < nreg) {
+      L.gstart[c] = e.x;
+      L.slot[((e.y >> 20) & 15) * (t.ni + 2) + ((e.y >> 16) & 15)] = c;
+    }
+  }
+  stage_shift(L.shift, R);
+}
+
+// Tile headers (see nem_pair.h), one workgroup per work item.
+template <int T, int KERN>
+__global__ __launch_bounds__(128) void k_tile_headers(const StepArgs a, int* hdr, const unsigned* gate) {
+  if (gate && *gate == 0u) return;
+  constexpr int NSC = HdrCfg<T>::NSC;
+  __shared__ int cnt[128];
+  const int c = threadIdx.x;
+  for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) {
+    const int rep = a.work[2 * w], tile = a.work[2 * w + 1];
+    const RepDev& R = a.reps[rep];
+    const int cx0 = (tile % R.tiles_x) * T, cy0 = (tile / R.tiles_x) * T;
+    const int ni = min(T, R.nc - cx0), nj = min(T, R.nc - cy0);
+    const int nreg = (ni + 2) * (nj + 2);
+    int s0 = 0, n = 0, rx = 0, ry = 0;
+    if (c < nreg) {
+      // staged cell c -> region cell (rx, ry): interior row-major, then the
+      // halo's bottom row, its two side columns by row, its top row
+      const int nint = ni * nj, k = c - nint;
+      if (k < 0) { rx = c % ni + 1; ry = c / ni + 1; }
+      else if (k < ni + 2) { rx = k; ry = 0; }
+      else if (k < ni + 2 + 2 * nj) { const int q = k - (ni + 2); ry = q / 2 + 1; rx = (q & 1) ? ni + 1 : 0; }
+      else { rx = k - (ni + 2) - 2 * nj; ry = nj + 1; }
+      const int gx = (cx0 + rx - 1 + R.nc) % R.nc, gy = (cy0 + ry - 1 + R.nc) % R.nc;
+      const int gc = R.cell_base + gy * R.nc + gx;
+      s0 = a.cell_start[gc];
+      n = max(a.cell_start[gc + 1] - s0, 0);
+      if (s0 < 0 || (int64_t)s0 + n > a.ntot) { flag(a.flags, ERR_RANGE); s0 = 0; n = 0; }
+    }
+    cnt[c] = n;
+    __syncthreads();
+    int start = 0, S = 0, nin = 0;   // cells are few: every thread sums the counts before its own
+    for (int k = 0; k < nreg; ++k) {
+      const int v = cnt[k];
+      if (k < c) start += v;
+      if (k < ni * nj) nin += v;
+      S += v;
+    }
+    const bool over = S > TileCfg<T, KERN>::MAXP;
+    if (over && c == 0) flag(a.flags, ERR_OVERFLOW);
+    int* H = hdr + (size_t)w * HdrCfg<T>::INTS;
+    if (c == 0) { H[0] = over ? 0 : nin; H[1] = over ? 0 : S; H[2] = ni; H[3] = nj; H[4] = rep; }
+    if (c < NSC + 2) {
+      int2 e = make_int2(0, over ? 0 : S);
+      if (c < nreg && !over) e = make_int2(s0, start | rx << 16 | ry << 20);
+      ((int2*)(H + HDR_CELLS))[c] = e;
+    }
+    __syncthreads();
+  }
+}
+
 // Pair geometry of a list entry (LDS slot | direction code << 12) through the
 // neighbour predicate: true when the pair is a neighbour at this step's
 // positions. Every pass, and the list export, decides with this one function.
@@ -248,15 +320,14 @@ __device__ __forceinline__ void tile_pass_a_build(const StepArgs& a, int w) {
   __shared__ TileLDS<T> L;
   __shared__ float2 s_off[TileCfg<T, KERN>::MAXP];
   __shared__ unsigned long long s_mask[9 * WG];
-  RepDev R;
-  int rep;
-  if (!tile_begin<T, KERN>(a, w, L, R, rep)) return;
-  const int ni = L.hdr[0], nint = L.hdr[2], nreg = L.hdr[3];
-  const int S = L.cstart[nreg];
-  for (int t = threadIdx.x; t < S; t += WG) s_off[t] = a.off_cur[staged_global<T>(a, L, t)];
-  __syncthreads();
-  const int nin = L.cstart[nint];
+  const TileRef t = tile_ref<T>(a, w);
+  const RepDev R = a.reps[t.rep];
+  const int ni = t.ni, nint = t.ni * t.nj, nreg = (t.ni + 2) * (t.nj + 2);
+  const int S = t.S, nin = t.nin;
   const int tid = threadIdx.x;
+  tile_cells<T>(t, L, R);
+  stage_tile<T, KERN>(t, [&](int g) { return a.off_cur[g]; }, [&](int j, int, float2 o) { s_off[j] = o; });
+  __syncthreads();
   for (int base = 0; base < nin; base += WG) {
     const int p = base + tid;
     if (p >= nin) break;
@@ -292,7 +363,6 @@ __device__ __forceinline__ void tile_pass_a_build(const StepArgs& a, int w) {
     }
     const int vk = min(cnt, KMAX);
     const int g = L.gstart[st] + (p - L.cstart[st]);
-    if (g < 0 || g >= a.ntot) { flag(a.flags, ERR_RANGE); continue; }
     if (cnt > KMAX || big) flag(a.flags, ERR_OVERFLOW);
     Acc<COMP> sw;
     sw.init();
@@ -327,28 +397,24 @@ __device__ __forceinline__ void tile_pass_a_build(const StepArgs& a, int w) {
 // Walk: the volume over the Verlet entries that pass the exact predicate.
 template <int T, int COMP, int KERN>
 __device__ __forceinline__ void tile_pass_a_walk(const StepArgs& a, int w) {
-  __shared__ TileLDS<T> L;
+  __shared__ float2 s_shift[16];
   __shared__ float2 s_off[TileCfg<T, KERN>::MAXP];
-  RepDev R;
-  int rep;
-  if (!tile_begin<T, KERN>(a, w, L, R, rep)) return;
-  const int nint = L.hdr[2], nreg = L.hdr[3];
-  const int S = L.cstart[nreg];
-  for (int t = threadIdx.x; t < S; t += WG) s_off[t] = a.off_cur[staged_global<T>(a, L, t)];
+  const TileRef t = tile_ref<T>(a, w);
+  const RepDev R = a.reps[t.rep];
+  const int S = t.S, nin = t.nin;
+  stage_shift(s_shift, R);
+  stage_tile<T, KERN>(t, [&](int g) { return a.off_cur[g]; }, [&](int j, int, float2 o) { s_off[j] = o; });
   __syncthreads();
-  const int nin = L.cstart[nint];
   for (int base = 0; base < nin; base += WG) {
     const int p = base + threadIdx.x;
     if (p >= nin) break;
-    const int st = find_cell(L.cstart, nint, p);
-    const int g = L.gstart[st] + (p - L.cstart[st]);
-    if (g < 0 || g >= a.ntot) { flag(a.flags, ERR_RANGE); continue; }
+    const int g = t.template global<T>(p);
     const float2 oi = s_off[p];
     Acc<COMP> sw;
     sw.init();
     each_listed<2>(a.vl, a.ntot, g, min(a.vcnt[g], KMAX), 1, 0, [&](uint32_t e) {
       int j; float rx, ry, r2;
-      const bool in = verlet_pair(e, L.shift, S - 1, s_off, oi, R.R2, j, rx, ry, r2);
+      const bool in = verlet_pair(e, s_shift, S - 1, s_off, oi, R.R2, j, rx, ry, r2);
       const float W = kernel_raw<KERN>(R, r2).W;
       sw.add(in ? W : 0.0f);                 // exact zero outside the support
     }, [&]() { sw.end_cell(); });
@@ -363,7 +429,7 @@ __device__ __forceinline__ void tile_pass_a_walk(const StepArgs& a, int w) {
 template <int T, int COMP, int FORM, int EL, int KERN, int Q3>
 __device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w) {
   static_assert(Q3 == 0 || (FORM == 0 && EL == 0), "quasi-2D: corrected form, no lambda terms");
-  __shared__ TileLDS<T> L;
+  __shared__ float2 s_shift[16];
   constexpr int MP = TileCfg<T, KERN>::MAXP;
   __shared__ float2 s_off[MP];
   __shared__ float2 s_u[MP];
@@ -371,22 +437,22 @@ __device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w) {
   __shared__ float s_V[MP];                  // V dWc: V_j F = s_V[j] Fr
   __shared__ float s_rho[FORM == 1 ? MP : 1];
   __shared__ float s_qc[Q3 == 1 ? MP : 1];   // Qyy of the quasi-2D variant
-  RepDev R;
-  int rep;
-  if (!tile_begin<T, KERN>(a, w, L, R, rep)) return;
-  const int nint = L.hdr[2], nreg = L.hdr[3];
-  const int S = L.cstart[nreg];
-  for (int t = threadIdx.x; t < S; t += WG) {
-    const int g = staged_global<T>(a, L, t);
-    s_off[t] = a.off_cur[g];
-    s_u[t] = a.u[g];
-    s_q[t] = a.q_cur[g];
-    if constexpr (Q3 == 1) s_qc[t] = a.qyy_cur[g];
-    s_V[t] = a.V[g] * R.dWc;
-    if constexpr (FORM == 1) s_rho[t] = R.rho0 + a.drho[g];
-  }
+  const TileRef t = tile_ref<T>(a, w);
+  const RepDev R = a.reps[t.rep];
+  const int S = t.S, nin = t.nin;
+  stage_shift(s_shift, R);
+  struct In { float2 off, u, q; float V, x; };
+  stage_tile<T, KERN>(t, [&](int g) {
+    return In{a.off_cur[g], a.u[g], a.q_cur[g], a.V[g], Q3 == 1 ? a.qyy_cur[g] : (FORM == 1 ? a.drho[g] : 0.0f)};
+  }, [&](int j, int, const In& v) {
+    s_off[j] = v.off;
+    s_u[j] = v.u;
+    s_q[j] = v.q;
+    if constexpr (Q3 == 1) s_qc[j] = v.x;
+    s_V[j] = v.V * R.dWc;
+    if constexpr (FORM == 1) s_rho[j] = R.rho0 + v.x;
+  });
   __syncthreads();
-  const int nin = L.cstart[nint];
   for (int base = 0; base < nin;) {
     const int lpp = lanes_for(nin - base, a.lpp);
     const int p = base + threadIdx.x / lpp;
@@ -394,9 +460,7 @@ __device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w) {
     base += WG / lpp;
     int g = -1;
     if (p < nin) {
-      const int st = find_cell(L.cstart, nint, p);
-      g = L.gstart[st] + (p - L.cstart[st]);
-      if (g < 0 || g >= a.ntot) { flag(a.flags, ERR_RANGE); g = -1; }
+      g = t.template global<T>(p);
     }
     const bool act = g >= 0;
     // raw pair sums (see the epilogue for their meaning)
@@ -425,7 +489,7 @@ __device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w) {
         int j; float rx, ry, r2;
         // entries outside the support are skipped (a branch measured faster
         // here than zeroing their terms with selects)
-        if (!verlet_pair(e, L.shift, S - 1, s_off, oi, R.R2, j, rx, ry, r2)) return;
+        if (!verlet_pair(e, s_shift, S - 1, s_off, oi, R.R2, j, rx, ry, r2)) return;
         const KW k = kernel_raw<KERN>(R, r2);
         const float2 uj = s_u[j], qj = s_q[j];
         const float c = s_V[j] * k.F;          // V_j W'(r)/r
@@ -588,28 +652,23 @@ __device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w) {
 // ------------------------------------------------------------------ pass C
 template <int T, int COMP, int KERN>
 __device__ __forceinline__ void tile_pass_c(const StepArgs& a, int w) {
-  __shared__ TileLDS<T> L;
+  __shared__ float2 s_shift[16];
   constexpr int MP = TileCfg<T, KERN>::MAXP;
   __shared__ float2 s_off[MP];
   __shared__ float s_dh[MP];
   __shared__ float2 s_u[MP];
-  RepDev R;
-  int rep;
-  if (!tile_begin<T, KERN>(a, w, L, R, rep)) return;
-  const int nint = L.hdr[2], nreg = L.hdr[3];
-  const int S = L.cstart[nreg];
-  for (int t = threadIdx.x; t < S; t += WG) {
-    const int g = staged_global<T>(a, L, t);
-    s_off[t] = a.off_cur[g];
-    s_dh[t] = a.dh[g];
-    s_u[t] = a.u[g];
-  }
+  const TileRef t = tile_ref<T>(a, w);
+  const RepDev R = a.reps[t.rep];
+  const int S = t.S, nin = t.nin;
+  stage_shift(s_shift, R);
+  struct In { float2 off, u; float dh; };
+  stage_tile<T, KERN>(t, [&](int g) { return In{a.off_cur[g], a.u[g], a.dh[g]}; },
+                      [&](int j, int, const In& v) { s_off[j] = v.off; s_dh[j] = v.dh; s_u[j] = v.u; });
   __syncthreads();
   unsigned umb = 0;
-  for (int k = 0; k < UMAX_SLOTS; ++k) umb = max(umb, a.umax_cur[rep * UMAX_SLOTS + k]);
+  for (int k = 0; k < UMAX_SLOTS; ++k) umb = max(umb, a.umax_cur[t.rep * UMAX_SLOTS + k]);
   const float c0 = R.c0_factor * __uint_as_float(umb);
   const float pc = R.rho0 * c0 * c0 / R.gamma_eos;
-  const int nin = L.cstart[nint];
   for (int base = 0; base < nin;) {
     const int lpp = lanes_for(nin - base, a.lpp);
     const int p = base + threadIdx.x / lpp;
@@ -617,9 +676,7 @@ __device__ __forceinline__ void tile_pass_c(const StepArgs& a, int w) {
     base += WG / lpp;
     int g = -1;
     if (p < nin) {
-      const int st = find_cell(L.cstart, nint, p);
-      g = L.gstart[st] + (p - L.cstart[st]);
-      if (g < 0 || g >= a.ntot) { flag(a.flags, ERR_RANGE); g = -1; }
+      g = t.template global<T>(p);
     }
     const bool act = g >= 0;
     Acc<COMP> sd, Wux, Wuy;   // in units of a2
@@ -632,7 +689,7 @@ __device__ __forceinline__ void tile_pass_c(const StepArgs& a, int w) {
         // entries outside the support add exact zeros (a select: a branch here
         // splits the four-entry iteration and measured 9% slower); the select
         // also drops the non-finite W of coincident particles
-        const bool in = verlet_pair(e, L.shift, S - 1, s_off, oi, R.R2, j, rx, ry, r2);
+        const bool in = verlet_pair(e, s_shift, S - 1, s_off, oi, R.R2, j, rx, ry, r2);
         const float Wr = kernel_raw<KERN>(R, r2).W;
         const float W = in ? Wr : 0.0f;
         const float2 uj = s_u[j];
@@ -666,7 +723,7 @@ __device__ __forceinline__ void tile_pass_c(const StepArgs& a, int w) {
 // INTEG: corrector, 0 kick-drift-kick, 1 midpoint (the integrator parameter picks the variant at launch).
 template <int T, int COMP, int FORM, int EL, int KERN, int INTEG>
 __device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w) {
-  __shared__ TileLDS<T> L;
+  __shared__ float2 s_shift[16];
   constexpr int MP = TileCfg<T, KERN>::MAXP;
   // FORM 0 stages V dWc (V_j F = s_V[j] Fr); without the lambda stress it also
   // stages s_P = P V dWc, so that (P_i + P_j) V_j F = (P_i s_V[j] + s_P[j]) Fr.
@@ -676,21 +733,21 @@ __device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w) {
   __shared__ float s_P[MP];
   __shared__ float2 s_pi[EL == 1 ? MP : 1];
   __shared__ float s_wmax[WG / 64];
-  RepDev R;
-  int rep;
-  if (!tile_begin<T, KERN>(a, w, L, R, rep)) return;
-  const int nint = L.hdr[2], nreg = L.hdr[3];
-  const int S = L.cstart[nreg];
-  for (int t = threadIdx.x; t < S; t += WG) {
-    const int g = staged_global<T>(a, L, t);
-    s_off[t] = a.off_cur[g];
-    const float Vd = a.V[g] * R.dWc;
-    s_V[t] = Vd;
-    s_P[t] = PV ? a.P[g] * Vd : a.P[g];
-    if constexpr (EL == 1) s_pi[t] = a.pi[g];
-  }
+  const TileRef t = tile_ref<T>(a, w);
+  const RepDev R = a.reps[t.rep];
+  const int S = t.S, nin = t.nin;
+  stage_shift(s_shift, R);
+  struct In { float2 off, pi; float V, P; };
+  stage_tile<T, KERN>(t, [&](int g) {
+    return In{a.off_cur[g], EL == 1 ? a.pi[g] : make_float2(0.f, 0.f), a.V[g], a.P[g]};
+  }, [&](int j, int, const In& v) {
+    s_off[j] = v.off;
+    const float Vd = v.V * R.dWc;
+    s_V[j] = Vd;
+    s_P[j] = PV ? v.P * Vd : v.P;
+    if constexpr (EL == 1) s_pi[j] = v.pi;
+  });
   __syncthreads();
-  const int nin = L.cstart[nint];
   float umax_l = 0.0f;
   bool rebin = false, bad = false, relist = false;
   for (int base = 0; base < nin;) {
@@ -700,9 +757,7 @@ __device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w) {
     base += WG / lpp;
     int g = -1;
     if (p < nin) {
-      const int st = find_cell(L.cstart, nint, p);
-      g = L.gstart[st] + (p - L.cstart[st]);
-      if (g < 0 || g >= a.ntot) { flag(a.flags, ERR_RANGE); g = -1; }
+      g = t.template global<T>(p);
     }
     const bool act = g >= 0;
     Acc<COMP> Px, Py, Exx, Exy, Eyx, Eyy;
@@ -719,7 +774,7 @@ __device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w) {
       const int cnt = min(a.vcnt[g], KMAX);
       each_listed<2>(a.vl, a.ntot, g, cnt, lpp, sub, [&](uint32_t e) {
         int j; float rx, ry, r2;
-        if (!verlet_pair(e, L.shift, S - 1, s_off, oi, R.R2, j, rx, ry, r2)) return;   // as in pass B
+        if (!verlet_pair(e, s_shift, S - 1, s_off, oi, R.R2, j, rx, ry, r2)) return;   // as in pass B
         ++nacc;
         const KW k = kernel_raw<KERN>(R, r2);
         const float c = (FORM == 0) ? s_V[j] * k.F : R.dWc * k.F;
@@ -829,7 +884,7 @@ __device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w) {
   if (threadIdx.x == 0) {
     float m = 0.0f;
     for (int w = 0; w < WG / 64; ++w) m = fmaxf(m, s_wmax[w]);
-    if (m > 0.0f) atomicMax(&a.umax_nxt[rep * UMAX_SLOTS + (w & (UMAX_SLOTS - 1))], __float_as_uint(m));
+    if (m > 0.0f) atomicMax(&a.umax_nxt[t.rep * UMAX_SLOTS + (w & (UMAX_SLOTS - 1))], __float_as_uint(m));
   }
   if (rebin) atomicOr(&a.flags[1], 1u);
   if (relist) atomicOr(&a.flags[2], 1u);
@@ -957,34 +1012,29 @@ void launch_free_energy(int T, int kern, const StepArgs& a, double* fe, hipStrea
 template <int T, int KERN>
 __global__ __launch_bounds__(WG) void k_list_export(const StepArgs a, int rep_only, int which, int mode, int* cnt,
                                                     const int64_t* row_ptr, int32_t* col, int64_t cap) {
-  __shared__ TileLDS<T> L;
+  __shared__ float2 s_shift[16];
   constexpr int MP = TileCfg<T, KERN>::MAXP;
   __shared__ float2 s_off[MP];
   __shared__ int s_id[MP];
-  RepDev R;
-  int rep;
-  if (!tile_begin<T, KERN>(a, blockIdx.x, L, R, rep)) return;
-  if (rep != rep_only) return;
-  const int nint = L.hdr[2], nreg = L.hdr[3];
-  const int S = L.cstart[nreg];
-  for (int t = threadIdx.x; t < S; t += WG) {
-    const int g = staged_global<T>(a, L, t);
-    s_off[t] = a.off_cur[g];
-    s_id[t] = a.id[g];
-  }
+  const TileRef t = tile_ref<T>(a, blockIdx.x);
+  if (t.rep != rep_only) return;
+  const RepDev R = a.reps[t.rep];
+  const int S = t.S, nin = t.nin;
+  stage_shift(s_shift, R);
+  struct In { float2 off; int id; };
+  stage_tile<T, KERN>(t, [&](int g) { return In{a.off_cur[g], a.id[g]}; },
+                      [&](int j, int, const In& v) { s_off[j] = v.off; s_id[j] = v.id; });
   __syncthreads();
-  const int nin = L.cstart[nint];
   for (int p = threadIdx.x; p < nin; p += WG) {
-    const int st = find_cell(L.cstart, nint, p);
-    const int g = L.gstart[st] + (p - L.cstart[st]);
+    const int g = t.template global<T>(p);
     const int idi = s_id[p];
-    if (g < 0 || g >= a.ntot || idi < 0 || idi >= R.n) { flag(a.flags, ERR_RANGE); continue; }
+    if (idi < 0 || idi >= R.n) { flag(a.flags, ERR_RANGE); continue; }
     const float2 oi = s_off[p];
     int c = 0;
     const int64_t base = (mode == 1) ? row_ptr[idi] : 0;
     each_listed(a.vl, a.ntot, g, min(a.vcnt[g], KMAX), 1, 0, [&](uint32_t e) {
       int j; float rx, ry, r2;
-      const bool in = verlet_pair(e, L.shift, S - 1, s_off, oi, R.R2, j, rx, ry, r2);
+      const bool in = verlet_pair(e, s_shift, S - 1, s_off, oi, R.R2, j, rx, ry, r2);
       if (which == 0 && !in) return;
       if (mode == 1) {
         if (base + c < cap) col[base + c] = s_id[j];
@@ -1122,6 +1172,19 @@ bool launch_pass(int pass, const PassCfg& c, const StepArgs& a, hipStream_t s) {
     if (c.T == 8) return launch_comp<8, 1>(pass, c, a, s);
   }
   return false;
+}
+
+int tile_header_ints(int T) { return T == 8 ? HdrCfg<8>::INTS : HdrCfg<4>::INTS; }
+
+void launch_tile_headers(int T, int kern, const StepArgs& a, int* hdr, const unsigned* gate, hipStream_t s) {
+  const dim3 grid(std::max(1, std::min(a.nwork, 1024))), block(128);
+  if (kern == 1) {
+    if (T == 8) hipLaunchKernelGGL((k_tile_headers<8, 1>), grid, block, 0, s, a, hdr, gate);
+    else hipLaunchKernelGGL((k_tile_headers<4, 1>), grid, block, 0, s, a, hdr, gate);
+  } else {
+    if (T == 8) hipLaunchKernelGGL((k_tile_headers<8, 0>), grid, block, 0, s, a, hdr, gate);
+    else hipLaunchKernelGGL((k_tile_headers<4, 0>), grid, block, 0, s, a, hdr, gate);
+  }
 }
 
 void launch_list_export(int T, int kern, const StepArgs& a, int rep, int which, int mode, int* cnt,

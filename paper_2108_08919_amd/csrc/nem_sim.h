@@ -22,6 +22,7 @@ struct nem_sim {
   RepDev* d_reps = nullptr;
   int* d_work = nullptr;
   int nwork = 0, work_cap = 0;
+  int* d_hdr = nullptr;   // tile headers, one per work item
   int *cell_start = nullptr, *count = nullptr, *cursor = nullptr, *perm = nullptr;
   int* t_key = nullptr; float2 *t_off = nullptr, *t_lo = nullptr, *t_u = nullptr, *t_q = nullptr;
   float* t_drho = nullptr; float2* t_acc = nullptr; int* t_id = nullptr; int2* t_img = nullptr;
@@ -100,6 +101,7 @@ void free_snapshot(nem_sim* s);
 int take_snapshot(nem_sim* s, int i = 0);
 int restore_snapshot(nem_sim* s, int i = 0);
 int build_work(nem_sim* s);
+void build_headers(nem_sim* s, const unsigned* gate, hipStream_t st);
 void drop_graphs(nem_sim* s);
 
 }  // namespace nem_host
