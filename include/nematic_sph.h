@@ -313,7 +313,7 @@ int nem_autotune(nem_sim* s, int32_t steps, int32_t* tile, int32_t* lpp, double*
 
 /* Accumulated kernel times (ms, from HIP events recorded on the library's
  * stream around each launch group) and launch counts since the last reset,
- * per pass: 0 rebin (five kernels that return at once unless a rebin was
+ * per pass: 0 rebin (two kernels that return at once unless a rebin was
  * requested), 1 pass A (volume), 2 pass B (gradients and rates), 3 pass C
  * (filter and EoS), 4 pass D (stress and update). Requires NEM_OPT_TIMING;
  * synchronises the stream. */

@@ -3,8 +3,8 @@
 // The runtime validates parameters, lays out one device arena (caller-owned or
 // allocated here), builds the per-replica tables and the tile work list, and
 // enqueues the per-step kernel sequence on the caller's stream:
-//   rebin (5 kernels, each returns at once unless a rebin was requested),
-//   step-begin, pass A, pass B, pass C, pass D.
+//   rebin (2 kernels, each returns at once unless a rebin was requested),
+//   pass A, pass B, pass C, pass D.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -133,7 +133,7 @@ RepDev make_rep(const nem_params& p, int nc, int cell_base, int part_base, int n
 
 // Offsets of every buffer for given sizes (shared by nem_arena_bytes and carve()).
 struct Offs {
-  size_t reps, work, hdr, cell_start, count, cursor, perm;
+  size_t reps, work, hdr, cell_old, cell_start, count, cursor, perm;
   size_t t_key, t_off, t_lo, t_u, t_q, t_drho, t_acc, t_id, t_img, t_qyy;
   size_t off0, off1, offlo, u, q0, q1, drho, acc, id, cell, img, qyy0, qyy1;
   size_t V, bk, dh, apart, uv, pi, P, drhat, flags, umax, stage, red, nl, ncnt, fe, vl, vcnt, off_build;
@@ -148,6 +148,7 @@ Offs layout(int R, int64_t ntot, int64_t ncells, int64_t work_cap, int64_t stage
   o.work = L.put(sizeof(int) * 2 * (size_t)work_cap);
   o.hdr = L.put(sizeof(int) * (size_t)hdr_cap);
   o.cell_start = L.put(sizeof(int) * (C + 1));
+  o.cell_old = L.put(sizeof(int) * (C + 1));
   o.count = L.put(sizeof(int) * C);
   o.cursor = L.put(sizeof(int) * C);
   o.perm = L.put(sizeof(int) * N);
@@ -182,7 +183,7 @@ Offs layout(int R, int64_t ntot, int64_t ncells, int64_t work_cap, int64_t stage
   o.pi = L.put(sizeof(float2) * N);
   o.P = L.put(sizeof(float) * N);
   o.drhat = L.put(sizeof(float) * N);
-  o.flags = L.put(sizeof(unsigned) * 4);
+  o.flags = L.put(sizeof(unsigned) * FLAG_WORDS);
   o.umax = L.put(sizeof(unsigned) * 2 * R * UMAX_SLOTS);
   o.nl = L.put(sizeof(uint32_t) * (KMAX / 2) * N);
   o.ncnt = L.put(sizeof(int) * N);
@@ -218,7 +219,10 @@ int sizes_for(const nem_params* p, const int64_t* n, int R, Sizes& s, std::strin
     work8 += (int64_t)tiles_for(nc, 8) * tiles_for(nc, 8);
     s.stage_n = std::max<int64_t>(s.stage_n, n[r]);
   }
-  s.hdr_cap = std::max(s.work_cap * tile_header_ints(4), work8 * tile_header_ints(8));
+  int maxp, ints4, ints8;
+  tile_header_shape(4, 0, &maxp, &ints4);
+  tile_header_shape(8, 0, &maxp, &ints8);
+  s.hdr_cap = std::max(s.work_cap * ints4, work8 * ints8);
   if (s.ntot >= ((int64_t)1 << 31) - 1 || s.ncells >= ((int64_t)1 << 31) - 2) {
     why = "more than 2^31 particles or cells";
     return NEM_E_INVAL;
@@ -226,16 +230,16 @@ int sizes_for(const nem_params* p, const int64_t* n, int R, Sizes& s, std::strin
   return NEM_OK;
 }
 
-SortArgs sort_args(nem_sim* s, const unsigned* gate) {
+SortArgs sort_args(nem_sim* s) {
   SortArgs a;
   a.reps = s->d_reps; a.R = s->R; a.ncells = s->ncells; a.ntot = s->ntot;
-  a.cell_start = s->cell_start; a.count = s->count; a.cursor = s->cursor; a.perm = s->perm;
+  a.cell_start = s->cell_start; a.cell_old = s->cell_old; a.count = s->count; a.cursor = s->cursor; a.perm = s->perm;
   a.t_key = s->t_key; a.t_off = s->t_off; a.t_lo = s->t_lo; a.t_u = s->t_u; a.t_q = s->t_q;
   a.t_drho = s->t_drho; a.t_acc = s->t_acc; a.t_id = s->t_id; a.t_img = s->t_img; a.t_qyy = s->t_qyy;
   a.off = s->off[s->parity]; a.offlo = s->offlo; a.u = s->u; a.q = s->q[s->parity];
   a.drho = s->drho; a.acc = s->acc; a.id = s->id; a.cell = s->cell; a.img = s->img;
   a.qyy = s->qyy[s->parity];
-  a.flags = s->flags; a.gate = gate; a.off_build = s->off_build;
+  a.flags = s->flags; a.req = s->flags + FLAG_REQ + 2 * s->parity; a.off_build = s->off_build;
   return a;
 }
 
@@ -248,7 +252,8 @@ StepArgs step_args(nem_sim* s) {
   a.q_cur = s->q[c]; a.q_nxt = s->q[x]; a.acc = s->acc; a.drho = s->drho; a.cell = s->cell;
   a.qyy_cur = s->qyy[c]; a.qyy_nxt = s->qyy[x];
   a.V = s->V; a.bk = s->bk; a.dh = s->dh; a.apart = s->apart; a.uv = s->uv; a.pi = s->pi;
-  a.P = s->P; a.drhat = s->drhat; a.flags = s->flags;
+  a.P = s->P; a.drhat = s->drhat; a.flags = s->flags; a.nrep = s->R;
+  a.req_cur = s->flags + FLAG_REQ + 2 * c; a.req_nxt = s->flags + FLAG_REQ + 2 * x;
   a.umax_cur = s->umax + (size_t)c * s->R * UMAX_SLOTS; a.umax_nxt = s->umax + (size_t)x * s->R * UMAX_SLOTS;
   a.nl = s->nl; a.ncnt = s->ncnt;
   a.feat = s->feat; a.id = s->id;
@@ -290,14 +295,23 @@ int build_work(nem_sim* s) {
   HIPCHK(hipMemcpyAsync(s->d_work, w.data(), w.size() * sizeof(int), hipMemcpyHostToDevice, s->stream));
   HIPCHK(hipMemcpyAsync(s->d_reps, s->reps.data(), sizeof(RepDev) * s->R, hipMemcpyHostToDevice, s->stream));
   HIPCHK(hipStreamSynchronize(s->stream));
-  build_headers(s, nullptr, s->stream);
+  build_headers(s);
   return NEM_OK;
 }
 
-// Tile headers of the current cells (gate: only when *gate != 0).
-void build_headers(nem_sim* s, const unsigned* gate, hipStream_t st) {
-  launch_tile_headers(s->T, s->hp[0].kernel, step_args(s), s->d_hdr, gate, st);
+HdrArgs hdr_args(nem_sim* s) {
+  HdrArgs h;
+  h.reps = s->d_reps; h.work = s->d_work; h.nwork = s->nwork; h.T = s->T;
+  tile_header_shape(s->T, s->hp[0].kernel, &h.maxp, &h.ints);
+  h.cell_start = s->cell_start; h.ntot = s->ntot; h.flags = s->flags; h.hdr = s->d_hdr;
+  return h;
 }
+
+// Tile headers of the current cells and tiles.
+void build_headers(nem_sim* s) { launch_tile_headers(hdr_args(s), s->stream); }
+
+// The next step rebuilds the Verlet list.
+void request_relist(nem_sim* s) { launch_set_requests(s->flags, s->parity, 1, 1, s->stream); }
 
 int read_flags(nem_sim* s, unsigned* f) {
   HIPCHK(hipMemcpyAsync(f, s->flags, sizeof(unsigned) * 2, hipMemcpyDeviceToHost, s->stream));
@@ -364,21 +378,15 @@ PassCfg pass_cfg(const nem_sim* s) {
 }
 
 // The start of a step on stream st: the rebin kernels (they return at once
-// unless a rebin was requested), step-begin (decides whether pass A rebuilds
-// the Verlet list) and pass A (Verlet build or walk: the list every pass walks,
-// and the volumes).
+// unless a rebin was requested) and pass A (Verlet build or walk: the list
+// every pass walks, and the volumes).
 int enqueue_prologue(nem_sim* s, hipStream_t st) {
   {
     Timed t(s, 0);
-    SortArgs a = sort_args(s, s->flags + 1);
-    launch_rebin_key(a, st);
-    launch_sort_tail(a, 0, s->ntot, 0, s->ncells, 0, st);
-    build_headers(s, s->flags + 1, st);
+    launch_rebin(sort_args(s), hdr_args(s), st);
   }
-  StepArgs a = step_args(s);
-  launch_step_begin(s->flags, a.umax_nxt, s->R, st);
   Timed t(s, 1);
-  if (!launch_pass_a_verlet(pass_cfg(s), a, st)) { s->err = "unsupported kernel configuration"; return NEM_E_INVAL; }
+  if (!launch_pass_a_verlet(pass_cfg(s), step_args(s), st)) { s->err = "unsupported kernel configuration"; return NEM_E_INVAL; }
   return NEM_OK;
 }
 
@@ -461,7 +469,7 @@ int deposit_grid(nem_sim* s, int r, int M) {
   if (!s->has_state[r]) return NEM_E_STATE;
   int rc = ensure_grid(s, M);
   if (rc) return rc;
-  SortArgs a = sort_args(s, nullptr);
+  SortArgs a = sort_args(s);
   launch_int_offsets(a, s->t_off, s->stream);
   StepArgs sa = step_args(s);
   sa.off_cur = s->t_off;
@@ -563,7 +571,7 @@ int nem_create(const nem_params* p, const int64_t* n, int32_t R, void* dev_arena
   char* b = (char*)(((uintptr_t)s->arena + ALIGN - 1) / ALIGN * ALIGN);
   s->d_reps = (RepDev*)(b + o.reps); s->d_work = (int*)(b + o.work);
   s->d_hdr = (int*)(b + o.hdr);
-  s->cell_start = (int*)(b + o.cell_start); s->count = (int*)(b + o.count);
+  s->cell_start = (int*)(b + o.cell_start); s->cell_old = (int*)(b + o.cell_old); s->count = (int*)(b + o.count);
   s->cursor = (int*)(b + o.cursor); s->perm = (int*)(b + o.perm);
   s->t_key = (int*)(b + o.t_key); s->t_off = (float2*)(b + o.t_off); s->t_lo = (float2*)(b + o.t_lo);
   s->t_u = (float2*)(b + o.t_u); s->t_q = (float2*)(b + o.t_q); s->t_drho = (float*)(b + o.t_drho);
@@ -620,11 +628,11 @@ int nem_set_state(nem_sim* s, int32_t r, const double* x, const double* y, const
   }
   unsigned* um = s->umax + ((size_t)s->parity * s->R + r) * UMAX_SLOTS;
   HIPCHK(hipMemsetAsync(um, 0, sizeof(unsigned) * UMAX_SLOTS, s->stream));
-  SortArgs a = sort_args(s, nullptr);
+  SortArgs a = sort_args(s);
   launch_ingest(a, r, s->stage, n, s->umax + (size_t)s->parity * s->R * UMAX_SLOTS, s->stream);
   launch_sort_tail(a, R.part_base, n, R.cell_base, R.nc * R.nc, R.part_base, s->stream);
-  build_headers(s, nullptr, s->stream);
-  launch_request_relist(s->flags, s->stream);
+  build_headers(s);
+  request_relist(s);
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(s->stream));
   s->has_state[r] = 1;
@@ -640,7 +648,7 @@ int nem_set_qyy(nem_sim* s, int32_t r, const double* qyy) {
   if (!s->hp[r].q3d) { s->err = "Qyy is a state variable of the quasi-2D variant (q3d = 1) only"; return NEM_E_INVAL; }
   const int n = (int)s->n[r];
   HIPCHK(hipMemcpyAsync(s->stage, qyy, sizeof(double) * n, hipMemcpyHostToDevice, s->stream));
-  SortArgs a = sort_args(s, nullptr);
+  SortArgs a = sort_args(s);
   launch_qyy_io(a, r, n, s->stage, 1, s->stream);
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(s->stream));
@@ -655,7 +663,7 @@ int nem_get_qyy(nem_sim* s, int32_t r, double* qyy) {
   if (!s->has_state[r]) { s->err = "state of this replica was never set"; return NEM_E_STATE; }
   if (!s->hp[r].q3d) { s->err = "Qyy is a state variable of the quasi-2D variant (q3d = 1) only"; return NEM_E_INVAL; }
   const int n = (int)s->n[r];
-  SortArgs a = sort_args(s, nullptr);
+  SortArgs a = sort_args(s);
   launch_qyy_io(a, r, n, s->stage, 0, s->stream);
   HIPCHK(hipGetLastError());
   HIPCHK(hipMemcpyAsync(qyy, s->stage, sizeof(double) * n, hipMemcpyDeviceToHost, s->stream));
@@ -671,7 +679,7 @@ int nem_get_state(nem_sim* s, int32_t r, double* x, double* y, double* ux, doubl
   if (!s || r < 0 || r >= s->R) return NEM_E_INVAL;
   if (!s->has_state[r]) { s->err = "state of this replica was never set"; return NEM_E_STATE; }
   const int n = (int)s->n[r];
-  SortArgs a = sort_args(s, nullptr);
+  SortArgs a = sort_args(s);
   launch_export(a, r, s->stage, n, s->stream);
   HIPCHK(hipGetLastError());
   double* dst[9] = {x, y, ux, uy, qxx, qxy, rho, ax, ay};
@@ -706,8 +714,9 @@ int nem_sync(nem_sim* s) {
 // every replica's particle count and parameters, field by field), then the
 // device state between steps in a fixed order: the current offsets, their low
 // parts, u^{n+1/2}, the current Q (and Qyy), a^{n-1/2}, rho - rho0, ids, cells,
-// image counters, cell starts, both parities' max-speed slots, the four flag
-// words, and the Verlet list with its counts and build offsets. Everything a
+// image counters, cell starts, both parities' max-speed slots, four flag words
+// (error bits, this parity's rebin and rebuild requests, zero; the segment
+// without a device address), and the Verlet list with its counts and build offsets. Everything a
 // step reads before writing it is there, so a load continues bit for bit.
 namespace {
 constexpr char RAW_MAGIC[8] = {'N', 'E', 'M', 'R', 'A', 'W', '0', '1'};
@@ -722,7 +731,7 @@ std::vector<RawSeg> raw_segments(nem_sim* s) {
           {s->q[p], sizeof(float2) * N}, {s->qyy[p], sizeof(float) * N}, {s->acc, sizeof(float2) * N},
           {s->drho, sizeof(float) * N}, {s->id, sizeof(int) * N}, {s->cell, sizeof(int) * N},
           {s->img, sizeof(int2) * N}, {s->cell_start, sizeof(int) * (C + 1)},
-          {s->umax, sizeof(unsigned) * 2 * (size_t)s->R * UMAX_SLOTS}, {s->flags, sizeof(unsigned) * 4},
+          {s->umax, sizeof(unsigned) * 2 * (size_t)s->R * UMAX_SLOTS}, {nullptr, sizeof(unsigned) * 4},
           {s->vl, sizeof(uint32_t) * (KMAX / 2) * N}, {s->vcnt, sizeof(int) * N},
           {s->off_build, sizeof(float2) * N}};
 }
@@ -769,8 +778,13 @@ int nem_save_raw(nem_sim* s, void* host, uint64_t bytes) {
     w += 8 + 8 * RAW_PD + 8 * RAW_PI;
   }
   HIPCHK(hipStreamSynchronize(s->stream));
+  unsigned fw[FLAG_WORDS];
+  HIPCHK(hipMemcpyAsync(fw, s->flags, sizeof(fw), hipMemcpyDeviceToHost, s->stream));
+  HIPCHK(hipStreamSynchronize(s->stream));
+  const unsigned fs[4] = {fw[0], fw[FLAG_REQ + 2 * s->parity], fw[FLAG_REQ + 2 * s->parity + 1], 0u};
   for (const RawSeg& g : raw_segments(s)) {
-    HIPCHK(hipMemcpyAsync(w, g.dev, g.bytes, hipMemcpyDeviceToHost, s->stream));
+    if (g.dev) HIPCHK(hipMemcpyAsync(w, g.dev, g.bytes, hipMemcpyDeviceToHost, s->stream));
+    else std::memcpy(w, fs, sizeof(fs));
     w += g.bytes;
   }
   HIPCHK(hipStreamSynchronize(s->stream));
@@ -821,11 +835,21 @@ int nem_load_raw(nem_sim* s, const void* host, uint64_t bytes) {
     if (rc) return rc;
   }
   s->parity = (int)hw[4];
+  unsigned fw[FLAG_WORDS] = {0};
   for (const RawSeg& g : raw_segments(s)) {
-    HIPCHK(hipMemcpyAsync(g.dev, w, g.bytes, hipMemcpyHostToDevice, s->stream));
+    if (g.dev) {
+      HIPCHK(hipMemcpyAsync(g.dev, w, g.bytes, hipMemcpyHostToDevice, s->stream));
+    } else {
+      unsigned fs[4];
+      std::memcpy(fs, w, sizeof(fs));
+      fw[0] = fs[0];
+      fw[FLAG_REQ + 2 * s->parity] = fs[1];
+      fw[FLAG_REQ + 2 * s->parity + 1] = fs[2];
+      HIPCHK(hipMemcpyAsync(s->flags, fw, sizeof(fw), hipMemcpyHostToDevice, s->stream));
+    }
     w += g.bytes;
   }
-  build_headers(s, nullptr, s->stream);
+  build_headers(s);
   HIPCHK(hipStreamSynchronize(s->stream));
   for (int r = 0; r < s->R; ++r) s->has_state[r] = 1;
   for (auto& sn : s->snap) sn.valid = false;
@@ -846,6 +870,7 @@ int nem_neighbor_list(nem_sim* s, int32_t r, int32_t which, int64_t* row_ptr, in
   int rc = enqueue_prologue(s, s->stream);
   s->timing = timing;
   if (rc) return rc;
+  launch_set_requests(s->flags, s->parity, 0, 0, s->stream);   // served: the next step walks this list
   // counts, row pointers and offsets in the staging area (9 * max n doubles)
   char* st = (char*)s->stage;
   int* d_cnt = (int*)st;
@@ -888,7 +913,7 @@ int nem_neighbor_list(nem_sim* s, int32_t r, int32_t which, int64_t* row_ptr, in
     for (int i = 0; i < n; ++i) std::sort(col + row_ptr[i], col + row_ptr[i + 1]);
   }
   if (cell_xy || off_xy) {
-    SortArgs sa = sort_args(s, nullptr);
+    SortArgs sa = sort_args(s);
     launch_export_offsets(sa, r, n, d_cxy, d_oxy, s->stream);
     HIPCHK(hipGetLastError());
     if (cell_xy) HIPCHK(hipMemcpyAsync(cell_xy, d_cxy, sizeof(int32_t) * 2 * n, hipMemcpyDeviceToHost, s->stream));
@@ -909,7 +934,7 @@ int nem_neighbors(nem_sim* s, int32_t r, int64_t* row_ptr, int32_t* col, int64_t
 int nem_diagnostics(nem_sim* s, int32_t r, nem_diag* out) {
   if (!s || r < 0 || r >= s->R || !out) return NEM_E_INVAL;
   if (!s->has_state[r]) return NEM_E_STATE;
-  SortArgs a = sort_args(s, nullptr);
+  SortArgs a = sort_args(s);
   // pair sums at the integer time level: integer-level offsets into the
   // staging array, then pass A (volumes, neighbour list) and the free-energy
   // kernel on them; the per-step temporaries are rebuilt by the next step
@@ -1039,7 +1064,7 @@ int nem_track(nem_sim* s, int32_t r, const int32_t* ids, int32_t n_ids, double* 
   int* d_ids = (int*)(s->stage + n);
   double* out = s->stage + 2 * (size_t)n;
   HIPCHK(hipMemcpyAsync(d_ids, ids, sizeof(int32_t) * n_ids, hipMemcpyHostToDevice, s->stream));
-  SortArgs a = sort_args(s, nullptr);
+  SortArgs a = sort_args(s);
   launch_track(a, r, n, inv, d_ids, n_ids, out, s->stream);
   HIPCHK(hipGetLastError());
   HIPCHK(hipMemcpyAsync(x, out, sizeof(double) * n_ids, hipMemcpyDeviceToHost, s->stream));
@@ -1068,7 +1093,7 @@ int nem_mixing(nem_sim* s, int32_t r, const uint8_t* colour, int32_t ncol, int32
   uint8_t* d_col = (uint8_t*)s->stage;  // n bytes of the 9 n double staging area
   HIPCHK(hipMemcpyAsync(d_col, colour, (size_t)n, hipMemcpyHostToDevice, s->stream));
   HIPCHK(hipMemsetAsync(s->g_mix, 0, sizeof(unsigned long long) * nb, s->stream));
-  SortArgs a = sort_args(s, nullptr);
+  SortArgs a = sort_args(s);
   launch_colour_counts(a, r, n, d_col, ncol, B, s->g_mix, s->stream);
   HIPCHK(hipGetLastError());
   std::vector<unsigned long long> h(nb);
@@ -1135,7 +1160,7 @@ int nem_defects_noalloc(nem_sim* s, int32_t r, int32_t M, int64_t* n_plus, int64
   unsigned long long* cnt = (unsigned long long*)((char*)s->scratch + NOALLOC_GRID_BYTES);
   // the same kernels as nem_defects: integer-level offsets (arena), deposit
   // (writes every node of the M x M grid), counters cleared, winding
-  SortArgs a = sort_args(s, nullptr);
+  SortArgs a = sort_args(s);
   launch_int_offsets(a, s->t_off, s->stream);
   StepArgs sa = step_args(s);
   sa.off_cur = s->t_off;
@@ -1161,7 +1186,7 @@ int nem_set_option(nem_sim* s, int32_t key, int64_t value) {
       if (value != 4 && value != 8) return NEM_E_INVAL;
       drop_graphs(s);
       s->T = (int)value;
-      launch_request_relist(s->flags, s->stream);  // LDS slots of the Verlet list change with the tile
+      request_relist(s);  // LDS slots of the Verlet list change with the tile
       return build_work(s);
     }
     case NEM_OPT_LPP:

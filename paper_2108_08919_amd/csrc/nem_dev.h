@@ -20,6 +20,13 @@ enum : unsigned {
   ERR_RANGE = 8u,
 };
 
+// Device flag words: [0] sticky error bits; [2 + 2 p], [3 + 2 p] rebin and
+// Verlet rebuild requests of a step of parity p; [6] ticket of the rebin's
+// last workgroup (zero between rebins). Requests alternate with the parity, so
+// that no kernel has to clear them between one step's pass D and the next
+// step's rebin check.
+constexpr int FLAG_WORDS = 8, FLAG_REQ = 2, FLAG_TICKET = 6;
+
 // One periodic box. All per-pair constants are FP32; csd and Ld keep the
 // double-precision geometry used when positions enter or leave the library.
 struct RepDev {
@@ -77,7 +84,11 @@ struct StepArgs {
   float2* pi;             // lambda part of the elastic stress (Pi_xx, Pi_xy)
   float* P;               // p / rho_hat^2
   float* drhat;           // rho_hat - rho0
-  unsigned* flags;        // [0] error bits, [1] rebin request, [2] Verlet rebuild request, [3] rebuild this step
+  int nrep;               // replicas
+  unsigned* flags;        // [0] error bits (the layout is at FLAG_WORDS)
+  unsigned* req_cur;      // requests for this step: [0] rebin, [1] Verlet rebuild; read by the rebin kernels and
+                          // pass A, cleared by pass C
+  unsigned* req_nxt;      // requests for the next step, raised by pass D
   const unsigned* umax_cur;  // [R][UMAX_SLOTS]: max |u^{n+1/2}| (float bits)
   unsigned* umax_nxt;        // [R][UMAX_SLOTS]: max |u^{n+3/2}| being accumulated
   uint32_t* nl;              // neighbour list of the direct search (diagnostics): word w of particle g
@@ -100,6 +111,7 @@ struct SortArgs {
   int R;
   int ncells, ntot;
   int* cell_start;       // [ncells + 1]
+  int* cell_old;         // [ncells + 1], the cells before a rebin
   int* count;            // [ncells], zero between sorts
   int* cursor;           // [ncells], zero between sorts
   int* perm;             // [ntot]
@@ -111,23 +123,33 @@ struct SortArgs {
   int2* img;             // periodic image of each particle: unwrapped r = r + img * L
   float* qyy;            // Qyy (quasi-2D variant), current parity
   unsigned* flags;
-  const unsigned* gate;  // run only when *gate != 0 (NULL: always)
+  unsigned* req;         // requests of the next step to run: [0] rebin, [1] Verlet rebuild
   const float2* off_build;  // offsets at the last Verlet build (displacement checks)
+};
+
+// What the tile headers (nem_pair.h) are built from.
+struct HdrArgs {
+  const RepDev* reps;
+  const int* work;
+  int nwork, T, maxp, ints;   // work items, tile side, LDS capacity, ints per header
+  const int* cell_start;
+  int ntot;
+  unsigned* flags;
+  int* hdr;
 };
 
 // Launchers (nem_passes.hip, nem_sort.hip).
 bool launch_pass(int pass, const PassCfg& c, const StepArgs& a, hipStream_t s);
-void launch_tile_headers(int T, int kern, const StepArgs& a, int* hdr, const unsigned* gate, hipStream_t s);
-int tile_header_ints(int T);
+void tile_header_shape(int T, int kern, int* maxp, int* ints);
+void launch_tile_headers(const HdrArgs& h, hipStream_t s);
 bool launch_pass_a_verlet(const PassCfg& c, const StepArgs& a, hipStream_t s);
-void launch_request_relist(unsigned* flags, hipStream_t st);
+void launch_set_requests(unsigned* flags, int parity, int keep_rebin, int relist, hipStream_t st);
 void launch_list_export(int T, int kern, const StepArgs& a, int rep, int which, int mode, int* cnt,
                         const int64_t* row_ptr, int32_t* col, int64_t cap, hipStream_t s);
 void launch_export_offsets(const SortArgs& s, int r, int n, int* cxy, float* oxy, hipStream_t st);
 void launch_ingest(const SortArgs& s, int r, const double* in, int n, unsigned* umax, hipStream_t st);
-void launch_rebin_key(const SortArgs& s, hipStream_t st);
+void launch_rebin(const SortArgs& s, const HdrArgs& h, hipStream_t st);
 void launch_sort_tail(const SortArgs& s, int k0, int n, int c0, int nc, int base, hipStream_t st);
-void launch_step_begin(unsigned* flags, unsigned* umax_nxt, int R, hipStream_t st);
 void launch_export(const SortArgs& s, int r, double* out, int n, hipStream_t st);
 void launch_track(const SortArgs& s, int r, int n, int* inv, const int* ids, int nt, double* out, hipStream_t st);
 void launch_qyy_io(const SortArgs& s, int r, int n, double* buf, int to_device, hipStream_t st);

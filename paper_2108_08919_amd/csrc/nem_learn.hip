@@ -59,7 +59,7 @@ __device__ __forceinline__ void block_speed_max(const SortArgs& s, unsigned* uma
   if (threadIdx.x == 0) {
     const float m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
     if (m > 0.0f) atomicMax(&umax_cur[r * UMAX_SLOTS + (blockIdx.x & (UMAX_SLOTS - 1))], __float_as_uint(m));
-    if (any_relist) atomicOr(&s.flags[2], 1u);
+    if (any_relist) atomicOr(&s.req[1], 1u);
   }
 }
 
@@ -336,7 +336,7 @@ int take_snapshot(nem_sim* s, int i) {
   add(s->img, S.img, sizeof(int2) * N);
   add(s->cell_start, S.cell_start, sizeof(int) * (C + 1));
   add(s->umax + (size_t)p * s->R * UMAX_SLOTS, S.umax, sizeof(unsigned) * s->R * UMAX_SLOTS);
-  add(s->flags + 1, S.umax + s->R * UMAX_SLOTS, sizeof(unsigned));  // rebin request
+  add(s->flags + FLAG_REQ + 2 * p, S.umax + s->R * UMAX_SLOTS, sizeof(unsigned));  // rebin request
   if (full) { s->err = "snapshot copy list too long"; return NEM_E_INVAL; }
   hipLaunchKernelGGL(k_copy_list, dim3(1024), dim3(256), 0, s->stream, cl);
   HIPCHK(hipGetLastError());
@@ -371,16 +371,16 @@ int restore_snapshot(nem_sim* s, int i) {
   add(S.img, s->img, sizeof(int2) * N);
   add(S.cell_start, s->cell_start, sizeof(int) * (C + 1));
   add(S.umax, s->umax + (size_t)p * s->R * UMAX_SLOTS, sizeof(unsigned) * s->R * UMAX_SLOTS);
-  // keep the sticky error bits (flags[0]), restore the rebin request (flags[1]);
+  // keep the sticky error bits (flags[0]), restore the rebin request;
   // the Verlet list is not part of the snapshot: rebuild it
-  add(S.umax + s->R * UMAX_SLOTS, s->flags + 1, sizeof(unsigned));
+  add(S.umax + s->R * UMAX_SLOTS, s->flags + FLAG_REQ + 2 * p, sizeof(unsigned));
   if (full) { s->err = "snapshot copy list too long"; return NEM_E_INVAL; }
   hipLaunchKernelGGL(k_copy_list, dim3(1024), dim3(256), 0, s->stream, cl);
   HIPCHK(hipGetLastError());
-  launch_request_relist(s->flags, s->stream);
   s->parity = p;
+  request_relist(s);
   for (int r = 0; r < s->R; ++r) s->reps[r].dt = S.dt[r];
-  build_headers(s, nullptr, s->stream);
+  build_headers(s);
   int rc = upload_reps(s);
   if (rc) return rc;
   HIPCHK(hipStreamSynchronize(s->stream));
@@ -391,7 +391,7 @@ int restore_snapshot(nem_sim* s, int i) {
 static int scale_dt(nem_sim* s, float factor) {
   unsigned* um = s->umax + (size_t)s->parity * s->R * UMAX_SLOTS;
   HIPCHK(hipMemsetAsync(um, 0, sizeof(unsigned) * s->R * UMAX_SLOTS, s->stream));
-  SortArgs a = sort_args(s, nullptr);
+  SortArgs a = sort_args(s);
   hipLaunchKernelGGL(k_repredict, rep_grid(s), dim3(256), 0, s->stream, a, factor, um);
   HIPCHK(hipGetLastError());
   for (auto& R : s->reps) R.dt *= factor;
@@ -699,7 +699,7 @@ static int samples_into(nem_sim* s, int32_t mult, float* X, float* T) {
     s->feat = nullptr;
   }
   if (!rc) {
-    SortArgs a = sort_args(s, nullptr);
+    SortArgs a = sort_args(s);
     hipLaunchKernelGGL(k_rows_by_id, dim3(grid_for(s->ntot)), dim3(256), 0, s->stream, a, (const float*)xs, X, 12);
     hipLaunchKernelGGL(k_export_qu, dim3(grid_for(s->ntot)), dim3(256), 0, s->stream, a, coarse);
   }
@@ -707,7 +707,7 @@ static int samples_into(nem_sim* s, int32_t mult, float* X, float* T) {
   if (!rc) rc = restore_snapshot(s);
   if (!rc) rc = run_steps(s, mult);
   if (!rc) {
-    SortArgs a = sort_args(s, nullptr);
+    SortArgs a = sort_args(s);
     hipLaunchKernelGGL(k_export_qu, dim3(grid_for(s->ntot)), dim3(256), 0, s->stream, a, T);
     hipLaunchKernelGGL(k_sub, dim3(grid_for(5 * (int64_t)s->ntot)), dim3(256), 0, s->stream, T, coarse,
                        5 * (int64_t)s->ntot);
@@ -761,7 +761,7 @@ int nem_step_learned(nem_sim* s, nem_mlp* m, int64_t n_macro, int32_t mult, doub
     unsigned* um = s->umax + (size_t)s->parity * s->R * UMAX_SLOTS;
     hipLaunchKernelGGL(k_learn_clear, dim3(1), dim3(256), 0, s->stream, mx + b, um, s->R * UMAX_SLOTS);
     launch_mlp_forward(m->P, m->hnorm, X, (int64_t)N, Y, mx + b, s->stream);
-    SortArgs a = sort_args(s, nullptr);
+    SortArgs a = sort_args(s);
     hipLaunchKernelGGL(k_correct, rep_grid(s), dim3(256), 0, s->stream, a, (const float*)Y, um,
                        (const unsigned*)(mx + b), tau_bits, dmx + b);
     if (!chk(hipGetLastError(), "k_correct")) return rc;

@@ -76,56 +76,6 @@ __device__ __forceinline__ void tile_cells(const TileRef& t, TileLDS<T>& L, cons
   stage_shift(L.shift, R);
 }
 
-// Tile headers (see nem_pair.h), one workgroup per work item.
-template <int T, int KERN>
-__global__ __launch_bounds__(128) void k_tile_headers(const StepArgs a, int* hdr, const unsigned* gate) {
-  if (gate && *gate == 0u) return;
-  constexpr int NSC = HdrCfg<T>::NSC;
-  __shared__ int cnt[128];
-  const int c = threadIdx.x;
-  for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) {
-    const int rep = a.work[2 * w], tile = a.work[2 * w + 1];
-    const RepDev& R = a.reps[rep];
-    const int cx0 = (tile % R.tiles_x) * T, cy0 = (tile / R.tiles_x) * T;
-    const int ni = min(T, R.nc - cx0), nj = min(T, R.nc - cy0);
-    const int nreg = (ni + 2) * (nj + 2);
-    int s0 = 0, n = 0, rx = 0, ry = 0;
-    if (c < nreg) {
-      // staged cell c -> region cell (rx, ry): interior row-major, then the
-      // halo's bottom row, its two side columns by row, its top row
-      const int nint = ni * nj, k = c - nint;
-      if (k < 0) { rx = c % ni + 1; ry = c / ni + 1; }
-      else if (k < ni + 2) { rx = k; ry = 0; }
-      else if (k < ni + 2 + 2 * nj) { const int q = k - (ni + 2); ry = q / 2 + 1; rx = (q & 1) ? ni + 1 : 0; }
-      else { rx = k - (ni + 2) - 2 * nj; ry = nj + 1; }
-      const int gx = (cx0 + rx - 1 + R.nc) % R.nc, gy = (cy0 + ry - 1 + R.nc) % R.nc;
-      const int gc = R.cell_base + gy * R.nc + gx;
-      s0 = a.cell_start[gc];
-      n = max(a.cell_start[gc + 1] - s0, 0);
-      if (s0 < 0 || (int64_t)s0 + n > a.ntot) { flag(a.flags, ERR_RANGE); s0 = 0; n = 0; }
-    }
-    cnt[c] = n;
-    __syncthreads();
-    int start = 0, S = 0, nin = 0;   // cells are few: every thread sums the counts before its own
-    for (int k = 0; k < nreg; ++k) {
-      const int v = cnt[k];
-      if (k < c) start += v;
-      if (k < ni * nj) nin += v;
-      S += v;
-    }
-    const bool over = S > TileCfg<T, KERN>::MAXP;
-    if (over && c == 0) flag(a.flags, ERR_OVERFLOW);
-    int* H = hdr + (size_t)w * HdrCfg<T>::INTS;
-    if (c == 0) { H[0] = over ? 0 : nin; H[1] = over ? 0 : S; H[2] = ni; H[3] = nj; H[4] = rep; }
-    if (c < NSC + 2) {
-      int2 e = make_int2(0, over ? 0 : S);
-      if (c < nreg && !over) e = make_int2(s0, start | rx << 16 | ry << 20);
-      ((int2*)(H + HDR_CELLS))[c] = e;
-    }
-    __syncthreads();
-  }
-}
-
 // Pair geometry of a list entry (LDS slot | direction code << 12) through the
 // neighbour predicate: true when the pair is a neighbour at this step's
 // positions. Every pass, and the list export, decides with this one function.
@@ -886,8 +836,8 @@ __device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w) {
     for (int w = 0; w < WG / 64; ++w) m = fmaxf(m, s_wmax[w]);
     if (m > 0.0f) atomicMax(&a.umax_nxt[t.rep * UMAX_SLOTS + (w & (UMAX_SLOTS - 1))], __float_as_uint(m));
   }
-  if (rebin) atomicOr(&a.flags[1], 1u);
-  if (relist) atomicOr(&a.flags[2], 1u);
+  if (rebin) atomicOr(&a.req_nxt[0], 1u);
+  if (relist) atomicOr(&a.req_nxt[1], 1u);
   if (bad) flag(a.flags, ERR_NUMERIC);
 }
 
@@ -1053,16 +1003,16 @@ template <int T, int COMP, int KERN>
 __global__ __launch_bounds__(WG) void k_pass_a(const StepArgs a) {
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_a<T, COMP, KERN>(a, w); __syncthreads(); }
 }
-// Gated on the rebuild flag of this step (flags[3], set by the step-begin
-// kernel): exactly one of the two runs its tiles, the other exits at once.
+// Gated on this step's requests (a rebin also renews the list): exactly one of
+// the two runs its tiles, the other exits at once.
 template <int T, int COMP, int KERN>
 __global__ __launch_bounds__(WG) void k_pass_a_build(const StepArgs a) {
-  if (a.flags[3] == 0u) return;
+  if ((a.req_cur[0] | a.req_cur[1]) == 0u) return;
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_a_build<T, COMP, KERN>(a, w); __syncthreads(); }
 }
 template <int T, int COMP, int KERN>
 __global__ __launch_bounds__(WG) void k_pass_a_walk(const StepArgs a) {
-  if (a.flags[3] != 0u) return;
+  if ((a.req_cur[0] | a.req_cur[1]) != 0u) return;
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_a_walk<T, COMP, KERN>(a, w); __syncthreads(); }
 }
 
@@ -1080,11 +1030,15 @@ template <int T, int COMP, int FORM, int EL, int KERN, int Q3>
 __global__ __launch_bounds__(WG)
 __attribute__((amdgpu_waves_per_eu(Q3 == 0 ? Waves<T, COMP, FORM, EL, KERN>::B : 1)))
 void k_pass_b(const StepArgs a) {
+  // the max-speed slots that this step's pass D fills (last read by the
+  // previous step's pass C)
+  for (int i = blockIdx.x * WG + threadIdx.x; i < a.nrep * UMAX_SLOTS; i += gridDim.x * WG) a.umax_nxt[i] = 0u;
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_b<T, COMP, FORM, EL, KERN, Q3>(a, w); __syncthreads(); }
 }
 template <int T, int COMP, int KERN>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(Waves<T, COMP, 0, 0, KERN>::C)))
 void k_pass_c(const StepArgs a) {
+  if (blockIdx.x == 0 && threadIdx.x < 2) a.req_cur[threadIdx.x] = 0u;   // served
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_c<T, COMP, KERN>(a, w); __syncthreads(); }
 }
 template <int T, int COMP, int FORM, int EL, int KERN, int INTEG>
@@ -1174,17 +1128,10 @@ bool launch_pass(int pass, const PassCfg& c, const StepArgs& a, hipStream_t s) {
   return false;
 }
 
-int tile_header_ints(int T) { return T == 8 ? HdrCfg<8>::INTS : HdrCfg<4>::INTS; }
-
-void launch_tile_headers(int T, int kern, const StepArgs& a, int* hdr, const unsigned* gate, hipStream_t s) {
-  const dim3 grid(std::max(1, std::min(a.nwork, 1024))), block(128);
-  if (kern == 1) {
-    if (T == 8) hipLaunchKernelGGL((k_tile_headers<8, 1>), grid, block, 0, s, a, hdr, gate);
-    else hipLaunchKernelGGL((k_tile_headers<4, 1>), grid, block, 0, s, a, hdr, gate);
-  } else {
-    if (T == 8) hipLaunchKernelGGL((k_tile_headers<8, 0>), grid, block, 0, s, a, hdr, gate);
-    else hipLaunchKernelGGL((k_tile_headers<4, 0>), grid, block, 0, s, a, hdr, gate);
-  }
+void tile_header_shape(int T, int kern, int* maxp, int* ints) {
+  *ints = T == 8 ? HdrCfg<8>::INTS : HdrCfg<4>::INTS;
+  if (kern == 1) *maxp = T == 8 ? TileCfg<8, 1>::MAXP : TileCfg<4, 1>::MAXP;
+  else *maxp = T == 8 ? TileCfg<8, 0>::MAXP : TileCfg<4, 0>::MAXP;
 }
 
 void launch_list_export(int T, int kern, const StepArgs& a, int rep, int which, int mode, int* cnt,

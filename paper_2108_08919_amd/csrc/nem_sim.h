@@ -23,7 +23,7 @@ struct nem_sim {
   int* d_work = nullptr;
   int nwork = 0, work_cap = 0;
   int* d_hdr = nullptr;   // tile headers, one per work item
-  int *cell_start = nullptr, *count = nullptr, *cursor = nullptr, *perm = nullptr;
+  int *cell_start = nullptr, *cell_old = nullptr, *count = nullptr, *cursor = nullptr, *perm = nullptr;
   int* t_key = nullptr; float2 *t_off = nullptr, *t_lo = nullptr, *t_u = nullptr, *t_q = nullptr;
   float* t_drho = nullptr; float2* t_acc = nullptr; int* t_id = nullptr; int2* t_img = nullptr;
   float* t_qyy = nullptr;
@@ -91,7 +91,7 @@ inline int hip_fail(nem_sim* s, hipError_t e, const char* what) {
     if (e_ != hipSuccess) return nem_host::hip_fail(s, e_, #expr); \
   } while (0)
 
-nem::SortArgs sort_args(nem_sim* s, const unsigned* gate);
+nem::SortArgs sort_args(nem_sim* s);
 nem::StepArgs step_args(nem_sim* s);
 int read_flags(nem_sim* s, unsigned* f);
 int status_from_flags(nem_sim* s, unsigned f);
@@ -101,7 +101,8 @@ void free_snapshot(nem_sim* s);
 int take_snapshot(nem_sim* s, int i = 0);
 int restore_snapshot(nem_sim* s, int i = 0);
 int build_work(nem_sim* s);
-void build_headers(nem_sim* s, const unsigned* gate, hipStream_t st);
+void build_headers(nem_sim* s);
+void request_relist(nem_sim* s);
 void drop_graphs(nem_sim* s);
 
 }  // namespace nem_host
