@@ -281,7 +281,7 @@ int nem_mixing(nem_sim* s, int32_t r, const uint8_t* colour, int32_t ncol, int32
 /* Tuning and instrumentation options (key, value):
  *   NEM_OPT_TILE       cells per tile side (4 or 8)
  *   NEM_OPT_LPP        lanes per particle in the pair loops (1, 2 or 4)
- *   NEM_OPT_COMP       pair-sum compensation: 0 none, 1 Kahan over chunks of 16 pairs
+ *   NEM_OPT_COMP       pair-sum compensation: 0 none, 1 Kahan over chunks of up to 16 pairs
  *                      (default), 2 Kahan on every pair term
  *   NEM_OPT_TIMING     1: record HIP events around every pass launch
  *   NEM_OPT_GRAPH      k > 0: capture k consecutive steps per buffer parity into

@@ -128,6 +128,16 @@ RepDev make_rep(const nem_params& p, int nc, int cell_base, int part_base, int n
   const double delta = 0.075 * p.h;
   R.R2v = (float)((rs + delta) * (rs + delta));
   R.disp2 = (float)((0.45 * delta) * (0.45 * delta));
+  // 2^32 units span at least 3.5 cell sides: a stencil pair's largest separation
+  // (two cells and the skin) cannot wrap into the Verlet radius
+  const double fix = std::exp2(std::floor(std::log2(4294967296.0 / (3.5 * csd))));
+  R.fix = (float)fix; R.unfix = (float)(1.0 / fix);
+  R.cs_fix = (int)(uint32_t)(int64_t)std::llround(csd * fix);
+  R.hinv_fix = (float)(1.0 / (p.h * fix));
+  auto sq = [&](double r) { return (float)((r * fix) * (r * fix)); };
+  R.R2v_fix = sq(rs + delta);
+  R.R2o_fix = sq((p.kernel == 1 ? 0.0 : 2.0 * p.h) + delta);
+  R.R2m_fix = sq((p.kernel == 1 ? 0.0 : p.h) + delta);
   return R;
 }
 
@@ -589,7 +599,7 @@ int nem_create(const nem_params* p, const int64_t* n, int32_t R, void* dev_arena
   s->stage = (double*)(b + o.stage); s->red = (double*)(b + o.red);
   s->nl = (uint32_t*)(b + o.nl); s->ncnt = (int*)(b + o.ncnt);
   s->fe = (double*)(b + o.fe);
-  s->vl = (uint32_t*)(b + o.vl); s->vcnt = (int*)(b + o.vcnt); s->off_build = (float2*)(b + o.off_build);
+  s->vl = (uint32_t*)(b + o.vl); s->vcnt = (uint32_t*)(b + o.vcnt); s->off_build = (float2*)(b + o.off_build);
 
   int cell_base = 0, part_base = 0;
   for (int r = 0; r < R; ++r) {
@@ -720,6 +730,7 @@ int nem_sync(nem_sim* s) {
 // step reads before writing it is there, so a load continues bit for bit.
 namespace {
 constexpr char RAW_MAGIC[8] = {'N', 'E', 'M', 'R', 'A', 'W', '0', '1'};
+constexpr int64_t RAW_VERSION = 2;
 constexpr int RAW_PD = 17, RAW_PI = 7;  // doubles and integers of nem_params
 
 struct RawSeg { void* dev; size_t bytes; };
@@ -768,7 +779,7 @@ int nem_save_raw(nem_sim* s, void* host, uint64_t bytes) {
   if (bytes < raw_total(s)) { s->err = "checkpoint buffer smaller than nem_raw_bytes"; return NEM_E_NOMEM; }
   char* b = (char*)host;
   std::memcpy(b, RAW_MAGIC, 8);
-  const int64_t hw[8] = {1, s->R, s->ntot, s->ncells, s->parity, s->T, s->LPP, s->COMP};
+  const int64_t hw[8] = {RAW_VERSION, s->R, s->ntot, s->ncells, s->parity, s->T, s->LPP, s->COMP};
   std::memcpy(b + 8, hw, sizeof(hw));
   char* w = b + 8 + sizeof(hw);
   for (int r = 0; r < s->R; ++r) {
@@ -801,7 +812,8 @@ int nem_load_raw(nem_sim* s, const void* host, uint64_t bytes) {
   if (bytes < raw_header_bytes(s->R) || std::memcmp(b, RAW_MAGIC, 8) != 0) return bad("not a checkpoint of this library");
   int64_t hw[8];
   std::memcpy(hw, b + 8, sizeof(hw));
-  if (hw[0] != 1) return bad("unknown checkpoint version");
+  // version 1 held the Verlet list in another format: it is rebuilt by the next step
+  if (hw[0] != 1 && hw[0] != RAW_VERSION) return bad("unknown checkpoint version");
   if (hw[1] != s->R || hw[2] != s->ntot || hw[3] != s->ncells) return bad("replica count or sizes differ");
   if (!(hw[4] == 0 || hw[4] == 1) || !(hw[5] == 4 || hw[5] == 8) || !(hw[6] == 1 || hw[6] == 2 || hw[6] == 4) ||
       hw[7] < 0 || hw[7] > 2)
@@ -844,7 +856,7 @@ int nem_load_raw(nem_sim* s, const void* host, uint64_t bytes) {
       std::memcpy(fs, w, sizeof(fs));
       fw[0] = fs[0];
       fw[FLAG_REQ + 2 * s->parity] = fs[1];
-      fw[FLAG_REQ + 2 * s->parity + 1] = fs[2];
+      fw[FLAG_REQ + 2 * s->parity + 1] = hw[0] == 1 ? 1u : fs[2];
       HIPCHK(hipMemcpyAsync(s->flags, fw, sizeof(fw), hipMemcpyHostToDevice, s->stream));
     }
     w += g.bytes;

@@ -52,6 +52,11 @@ struct RepDev {
   int q3d;         // 0: 2x2 Q (d = 2); 1: quasi-2D 3x3 Q with I/3 (Qyy stored, Qzz = -Qxx - Qyy)
   float R2v;       // Verlet list radius: fl32((kappa h + delta)^2), delta = 0.075 h
   float disp2;     // rebuild the Verlet list when a particle moved more than 0.45 delta: (0.45 delta)^2
+  // fixed-point positions of the pair passes (nem_pair.h): units per length and
+  // back, cell side in units, 1/h per unit; squared radii in units: the Verlet
+  // list and its distance classes, 2h + delta and h + delta (quintic)
+  float fix, unfix, hinv_fix, R2v_fix, R2o_fix, R2m_fix;
+  int cs_fix;
   double csd, Ld;
 };
 
@@ -95,9 +100,10 @@ struct StepArgs {
                              // at nl[w*ntot + g], two 16-bit entries (LDS slot | (dx+1)<<12 | (dy+1)<<14)
   int* ncnt;                 // its length per particle
   float* feat;               // NULL, or 12 features per particle at [g] (storage order)
-  uint32_t* vl;              // Verlet list (pairs within the Verlet radius at the last build), layout as nl;
-                             // every pass walks it through the neighbour predicate
-  int* vcnt;                 // Verlet list length
+  uint32_t* vl;              // Verlet list (pairs within the Verlet radius at the last build): word w of
+                             // particle g at vl[w*ntot + g], entries as ListFmt (nem_pair.h) packs them,
+                             // outer pairs first, then middle, then inner
+  uint32_t* vcnt;            // its counts (vc_total ... in nem_pair.h)
   float2* off_build;         // offset of each particle when the Verlet list was built
   const int* id;             // particle ids (sorted order)
 };

@@ -30,20 +30,29 @@ struct TileLDS {
 
 // Tile header, built by k_tile_headers whenever the cells or the tiles change
 // (new state, rebin, tile option, restored state) and read by every pair pass:
-// HDR_CELLS ints {interior particles nin, staged particles S, ni, nj, replica},
-// then one int2 {first global particle, first LDS slot | region x << 16 |
-// region y << 20} per staged cell (interior cells first, region coordinates
-// counted from the halo corner), and a closing entry whose slot is S. A pass
-// therefore starts loading fields one load after its launch; deriving the same
-// from the work list, the replica and cell_start in every pass was a chain of
-// three loads, a scan and a search per staged particle.
-// A tile over the LDS capacity has nin = S = 0 (and ERR_OVERFLOW is raised).
-constexpr int HDR_CELLS = 8;
+//   {interior particles nin, staged particles S, ni | nj << 8 | over
+//   << 16, replica, most list words of a particle (HDR_WORDS, set by the Verlet build)}, padded to 8 ints;
+//   per interior row {global index - LDS slot, first LDS slot} (the cells of an
+//   interior row are contiguous in the sorted arrays);
+//   per staged cell {first global particle, first LDS slot | region x << 16 |
+//   region y << 20} (interior cells first, region coordinates counted from the
+//   halo corner), and closing entries whose slot is S.
+// A pass therefore starts loading fields one load after its launch; deriving the
+// same from the work list, the replica and cell_start in every pass was a chain
+// of three loads, a scan and a search per staged particle (2048^2 box 61 us a
+// step more, 64^2 box 7.5 us a step more). The uniform part is read through the
+// constant address space, in one scalar load: as vector loads, each row's test
+// waited for a load of its own.
+// A tile over the LDS capacity has nin = S = 0 (pass A raises ERR_OVERFLOW).
+constexpr int HDR_ROWS = 8, HDR_WORDS = 4;
 template <int T>
 struct HdrCfg {
   static constexpr int NSC = (T + 2) * (T + 2);
-  static constexpr int INTS = HDR_CELLS + 2 * (NSC + 2);
+  static constexpr int CELLS = HDR_ROWS + 2 * T;
+  static constexpr int INTS = CELLS + 2 * (NSC + 2);
 };
+typedef const int __attribute__((address_space(4))) ConstInt;
+typedef const RepDev __attribute__((address_space(4))) ConstRep;
 
 // Staged-cell index of region cell (li, lj), li in [-1, ni], lj in [-1, nj].
 __device__ inline int staged_index(int li, int lj, int ni, int nj) {
@@ -172,6 +181,71 @@ __device__ __forceinline__ KW kernel_raw(const RepDev& R, float r2) {
   return k;
 }
 
+// Distance classes of the list (decided at the Verlet build with the margin
+// that particles may move before the next one): outer pairs stay at q > 2 (and
+// apart), middle pairs at q > 1, inner pairs are the rest. A class only drops
+// terms of the spline that are exactly zero for its pairs, so a pair may always
+// be taken in a later class. On the h = 1.3 dx lattice 24 of 44 pairs are outer
+// and 16 middle. Wendland C2 is one polynomial: its outer class only means
+// that a pair cannot coincide. Every form is zero from the support on, so a
+// listed pair beyond it adds nothing and needs no test.
+enum { OUTER = 0, MIDDLE = 1, INNER = 2 };
+struct Spline { float t3, t34, u, u4, t1, t14; };
+template <int CL>
+__device__ __forceinline__ Spline spline_terms(float r, float hinv) {
+  Spline s;
+  if constexpr (CL == OUTER) {
+    s.t3 = fminf(fmaxf(fmaf(-hinv, r, 3.0f), 0.0f), 1.0f);   // 3 - q <= 1 for an outer pair
+  } else {
+    // the terms take one rounded q: its error then cancels between them as the
+    // terms do (from r each, the errors add up: 14% more error in the gradients)
+    const float q = r * hinv;
+    s.t3 = fmaxf(3.0f - q, 0.0f);
+    s.u = fminf(fmaxf(fmaf(-0.5f, q, 1.0f), 0.0f), 1.0f);    // (2 - q)_+ / 2
+    const float b = s.u * s.u;
+    s.u4 = b * b;
+    if constexpr (CL == INNER) {
+      s.t1 = fminf(fmaxf(1.0f - q, 0.0f), 1.0f);             // (1 - q)_+
+      const float c = s.t1 * s.t1;
+      s.t14 = c * c;
+    }
+  }
+  const float a = s.t3 * s.t3;
+  s.t34 = a * a;
+  return s;
+}
+
+// W / a2 of a pair at distance r (hinv in the units of r).
+template <int KERN, int CL>
+__device__ __forceinline__ float class_w(float r, float hinv) {
+  if constexpr (KERN == 0) {
+    const Spline s = spline_terms<CL>(r, hinv);
+    float w = s.t34 * s.t3;
+    if constexpr (CL != OUTER) w = fmaf(-192.0f * s.u4, s.u, w);
+    if constexpr (CL == INNER) w = fmaf(15.0f * s.t14, s.t1, w);
+    return w;
+  } else {
+    const float t = fminf(fmaxf(fmaf(-0.5f * hinv, r, 1.0f), 0.0f), 1.0f);
+    const float t2 = t * t;
+    return (t2 * t2) * fmaf(2.0f * hinv, r, 1.0f);
+  }
+}
+
+// (W'(r) / r) / dWc from r and 1/r.
+template <int KERN, int CL>
+__device__ __forceinline__ float class_f(float r, float rinv, float hinv) {
+  if constexpr (KERN == 0) {
+    const Spline s = spline_terms<CL>(r, hinv);
+    float f = s.t34;
+    if constexpr (CL != OUTER) f = fmaf(-96.0f, s.u4, f);
+    if constexpr (CL == INNER) f = fmaf(15.0f, s.t14, f);
+    return f * rinv;
+  } else {
+    const float t = fminf(fmaxf(fmaf(-0.5f * hinv, r, 1.0f), 0.0f), 1.0f);
+    return (t * t) * t;
+  }
+}
+
 // W(0) / a2: the self term of the kernel sums in units of a2.
 template <int KERN>
 constexpr float kernel_w0_raw() { return KERN == 0 ? 66.0f : 1.0f; }
@@ -192,7 +266,7 @@ __device__ __forceinline__ float kernel_w(const RepDev& R, float r2) {
 }
 
 // A pair-sum accumulator. COMP 0: plain FP32 sum. COMP 1: Kahan summation over
-// short chunks of pairs (a chunk is 16 listed pairs): terms are added plainly
+// short chunks of pairs (1 to 8 list words of 2 or 3 pairs): terms are added plainly
 // into the chunk partial p, and at the end of the chunk p is added to the
 // running sum s with its rounding error recovered exactly (Fast2Sum) and
 // carried into the next chunk's partial. That is Kahan's update applied to the
@@ -251,33 +325,89 @@ __device__ __forceinline__ bool tile_begin(const StepArgs& a, int w, TileLDS<T>&
   return true;
 }
 
-// ------------------------------------------------- pair passes: header staging
-struct TileRef {
-  const int* H;
-  int nin, S, ni, nj, rep;
-  __device__ __forceinline__ int2 cell(int c) const { return ((const int2*)(H + HDR_CELLS))[c]; }
-  // Global index of interior particle p (= LDS slot p): the cells of an
-  // interior row are contiguous in the sorted arrays.
-  template <int T>
-  __device__ __forceinline__ int global(int p) const {
-    int d = cell(0).x;
-#pragma unroll
-    for (int r = 1; r < T; ++r)
-      if (r < nj) {
-        const int2 e = cell(r * ni);
-        const int c0 = e.y & 0xFFFF;
-        if (p >= c0) d = e.x - c0;
-      }
-    return p + d;
+// ------------------------------------------------------ Verlet list entries
+// A list word holds EPW slots of SBITS bits (three of 10 where the tile's LDS
+// capacity fits, else two of 12 in halves of 16), rotated left by 3: an entry
+// masked out of the word is the byte offset of its 8-byte LDS record, one or two
+// instructions. Three slots a word instead of two 16-bit entries with a
+// direction code are 60 bytes of list per particle and pass on the h = 1.3 dx
+// lattice instead of 88.
+template <int T, int KERN>
+struct ListFmt {
+  static constexpr int EPW = TileCfg<T, KERN>::MAXP <= 1024 ? 3 : 2;
+  static constexpr int SH = EPW == 3 ? 10 : 16;
+  static constexpr uint32_t MASK = (EPW == 3 ? 0x3FFu : 0xFFFu) << 3;
+    static constexpr int CHUNK = EPW == 3 ? 5 : 8;   // words per compensation chunk of pass B (15 or 16 pairs)
+  static_assert(TileCfg<T, KERN>::MAXP <= 4096, "slot must fit its field");
+  __device__ __forceinline__ static uint32_t pack(uint32_t slot, int i) { return slot << (SH * i); }
+  __device__ __forceinline__ static uint32_t seal(uint32_t w) { return (w << 3) | (w >> 29); }
+  // byte offset of entry i of word w in an array of 8-byte records
+  __device__ __forceinline__ static uint32_t at(uint32_t w, int i) {
+    return (i == 0 ? w : __builtin_amdgcn_alignbit(w, w, SH * i)) & MASK;
   }
 };
 
+// vcnt of a particle: its entries in bits 0-7, and for its group of 64
+// consecutive particles of the tile (a wave of the one-lane walk): entries all
+// of them can take as outer (bits 8-15), as outer or middle (16-23), and the
+// largest count (24-31). The first two are multiples of EPW.
+__device__ __forceinline__ int vc_total(uint32_t v) { return min((int)(v & 255u), KMAX); }
+__device__ __forceinline__ int vc_outer(uint32_t v) { return min((int)(v >> 8 & 255u), KMAX); }
+__device__ __forceinline__ int vc_middle(uint32_t v) { return min((int)(v >> 16 & 255u), KMAX); }
+__device__ __forceinline__ int vc_most(uint32_t v) { return min((int)(v >> 24), KMAX); }
+
+template <typename V>
+__device__ __forceinline__ V lds_at(const V* base, uint32_t byte_offset) {
+  static_assert(sizeof(V) == 8, "records of 8 bytes");
+  return *(const V*)((const char*)base + byte_offset);
+}
+
+// ------------------------------------------------- pair passes: header staging
 template <int T>
-__device__ __forceinline__ TileRef tile_ref(const StepArgs& a, int w) {
-  TileRef t;
-  t.H = a.hdr + (size_t)w * HdrCfg<T>::INTS;
-  t.nin = t.H[0]; t.S = t.H[1]; t.ni = t.H[2]; t.nj = t.H[3]; t.rep = t.H[4];
-  return t;
+struct TileRef {
+  ConstInt* H;
+  int nin, S, ni, nj, rep, words;
+  bool over;
+  __device__ __forceinline__ TileRef(const StepArgs& a, int w) {
+    H = (ConstInt*)(a.hdr + (size_t)w * HdrCfg<T>::INTS);
+    nin = H[0]; S = H[1]; ni = H[2] & 255; nj = (H[2] >> 8) & 255; over = H[2] >> 16; rep = H[3]; words = H[HDR_WORDS];
+  }
+  __device__ __forceinline__ int2 cell(int c) const {
+    return make_int2(H[HdrCfg<T>::CELLS + 2 * c], H[HdrCfg<T>::CELLS + 2 * c + 1]);
+  }
+  // Global index of interior particle p (= LDS slot p).
+  __device__ __forceinline__ int global(int p) const {
+    int d = H[HDR_ROWS];
+#pragma unroll
+    for (int r = 1; r < T; ++r) {
+      const int dr = H[HDR_ROWS + 2 * r], pr = H[HDR_ROWS + 2 * r + 1];
+      d = p >= pr ? dr : d;
+    }
+    return p + d;
+  }
+};
+__device__ __forceinline__ ConstRep& rep_of_tile(const StepArgs& a, int rep) { return ((ConstRep*)a.reps)[rep]; }
+
+// Positions of the passes that need no exact neighbour decision (A, B, C): 32-bit
+// integers in units of 1/fix relative to the tile's corner, fix a power of two
+// for which the 2^32 units are at least 3.5 cell sides. Differences of
+// neighbours are exact modulo 2^32, so a pair needs no image shift and is
+// rounded once, in the conversion to float; a unit is 2^-28 dx for cells of
+// 4 dx, 16 to 64 times finer than the FP32 offsets it is taken from. Distances
+// are in units; the powers of two come out of the sums at the end.
+template <typename Rep>
+__device__ __forceinline__ int2 fixed_position(Rep& R, float2 off, int entry) {
+  const int rx = (entry >> 16) & 15, ry = (entry >> 20) & 15;
+  return make_int2((int)((uint32_t)__float2int_rn(off.x * R.fix) + (uint32_t)rx * (uint32_t)R.cs_fix),
+                   (int)((uint32_t)__float2int_rn(off.y * R.fix) + (uint32_t)ry * (uint32_t)R.cs_fix));
+}
+struct FixPair { float rx, ry, r2; };
+__device__ __forceinline__ FixPair fixed_pair(int2 pi, int2 pj) {
+  FixPair d;
+  d.rx = (float)(int)((uint32_t)pi.x - (uint32_t)pj.x);
+  d.ry = (float)(int)((uint32_t)pi.y - (uint32_t)pj.y);
+  d.r2 = fmaf(d.rx, d.rx, d.ry * d.ry);
+  return d;
 }
 
 // Stage every particle of the tile and its halo: LPC lanes take one cell each
@@ -286,7 +416,7 @@ __device__ __forceinline__ TileRef tile_ref(const StepArgs& a, int w) {
 // first particles of all cells of a batch of rounds are loaded before any is
 // stored, so their latencies overlap.
 template <int T, int KERN, typename Load, typename Store>
-__device__ __forceinline__ void stage_tile(const TileRef& t, Load&& load, Store&& store) {
+__device__ __forceinline__ void stage_tile(const TileRef<T>& t, Load&& load, Store&& store) {
   constexpr int LPC = KERN == 1 ? 8 : 16, GR = WG / LPC, NSC = HdrCfg<T>::NSC;
   constexpr int ROUNDS = (NSC + GR - 1) / GR, BATCH = ROUNDS < 4 ? ROUNDS : 4;
   const int lane = threadIdx.x % LPC, grp = threadIdx.x / LPC;

@@ -8,13 +8,26 @@
 // anywhere in the box.
 //
 // Every pass walks the particle's Verlet list: the pairs of the 3 x 3 cell
-// stencil closer than 3h + delta when the list was built, as 16-bit entries
-// (LDS slot of the neighbour in the tile's staging order + stencil direction).
-// Each pass stages the same tile in the same order and puts every entry
-// through the same FP32 predicate (0 < r^2 < (3h)^2), so all four passes sum
-// over exactly the same neighbour set. Several lanes may share a particle
-// (each takes every lpp-th entry; sums are combined with wave shuffles); a
-// tile's short tail of particles is spread over more lanes.
+// stencil closer than 3h + delta when the list was built, as LDS slots in the
+// tile's staging order (each pass stages the same tile in the same order). Pass
+// D, whose APD sums carry no kernel weight, and the list export put every entry
+// through the exact FP32 predicate (0 < r^2 < (3h)^2); in passes A to C every
+// term carries W or W', which are zero from the support on, so a listed pair
+// beyond it adds nothing. Several lanes may share a particle (each takes every
+// lpp-th list word; sums are combined with wave shuffles); a tile's short tail
+// of particles is spread over more lanes.
+//
+// What bounds these passes is the number of vector instructions per pair (one
+// per 2.5 to 3 cycles and SIMD, whatever its kind; square roots 8), then the
+// list's bytes. So the list is ordered by distance class (nem_pair.h): 24 of the
+// 44 pairs of the lattice need one of the spline's three terms, 16 two; the
+// class bounds are the same for the 64 particles of a wave, so the loops are
+// scalar; and positions are fixed-point where no predicate is decided, which
+// takes the direction code, its decoding and its table read out of every pair.
+// Vector instructions per particle of passes A, B, C, D on the 2048^2 box: 1748,
+// 3522, 2103, 2382 -> 923, 2945, 1379, 1888; time 170, 321, 208, 237 -> 105, 265,
+// 156, 193 us; on the 64^2 box, where a pass is one workgroup's latency, 17.1,
+// 18.7, 16.8, 18.4 -> 8.9, 14.2, 10.8, 14.5 us.
 //
 //   pass A  Verlet list (rebuilt from the ~144 candidates of the stencil when
 //           particles have moved too far); volume V_i = 1 / sum_j W_ij
@@ -37,6 +50,25 @@
 
 namespace nem {
 
+// The exact neighbour predicate on staged records {offset, region cell}: the
+// cell difference times cs is the image shift of pair_accept's rule (-d cs,
+// exact for d = -1, 0, 1), added in one rounding. Pass D and the list export
+// decide with this one function; DUP: r2 > 0 is tested too.
+template <bool DUP>
+__device__ __forceinline__ bool neighbour(float2 oi, float2 ci, float2 oj, float2 cj, float cs, float R2, float& rx,
+                                          float& ry, float& r2) {
+#pragma clang fp contract(off)
+  const float tx = oi.x - oj.x, ty = oi.y - oj.y;
+  rx = fmaf(ci.x - cj.x, cs, tx);
+  ry = fmaf(ci.y - cj.y, cs, ty);
+  const float xx = rx * rx, yy = ry * ry;
+  r2 = xx + yy;
+  return (!DUP || r2 > 0.0f) && r2 < R2;
+}
+__device__ __forceinline__ float2 region_cell(int entry) {
+  return make_float2((float)((entry >> 16) & 15), (float)((entry >> 20) & 15));
+}
+
 // Lanes per particle for an iteration with `rem` particles left: the base
 // value, doubled while the particles still fill the workgroup (at most 16).
 __device__ __forceinline__ int lanes_for(int rem, int base_lpp) {
@@ -54,31 +86,25 @@ __device__ __forceinline__ int wave_sum_int(int v, int lpp) {
   return v;
 }
 
-// Image shifts of the 16 stencil direction codes (dx + 1) | (dy + 1) << 2.
-__device__ __forceinline__ void stage_shift(float2* shift, const RepDev& R) {
-  const int t = threadIdx.x;
-  if (t < 16) shift[t] = make_float2((float)(1 - (t & 3)) * R.cs, (float)(1 - (t >> 2)) * R.cs);
-}
-
 // The cell tables of a tile from its header (the Verlet build walks cells).
 template <int T>
-__device__ __forceinline__ void tile_cells(const TileRef& t, TileLDS<T>& L, const RepDev& R) {
+struct CellLDS {
+  int start[HdrCfg<T>::NSC + 1];   // first LDS slot of each staged cell
+  int slot[HdrCfg<T>::NSC];        // region cell y * (ni + 2) + x -> staged cell
+};
+template <int T>
+__device__ __forceinline__ void tile_cells(const TileRef<T>& t, CellLDS<T>& L) {
   const int nreg = (t.ni + 2) * (t.nj + 2);
   const int c = threadIdx.x;
   if (c <= nreg) {
     const int2 e = t.cell(c);
-    L.cstart[c] = e.y & 0xFFFF;
-    if (c < nreg) {
-      L.gstart[c] = e.x;
-      L.slot[((e.y >> 20) & 15) * (t.ni + 2) + ((e.y >> 16) & 15)] = c;
-    }
+    L.start[c] = e.y & 0xFFFF;
+    if (c < nreg) L.slot[((e.y >> 20) & 15) * (t.ni + 2) + ((e.y >> 16) & 15)] = c;
   }
-  stage_shift(L.shift, R);
 }
 
-// Pair geometry of a list entry (LDS slot | direction code << 12) through the
-// neighbour predicate: true when the pair is a neighbour at this step's
-// positions. Every pass, and the list export, decides with this one function.
+// Pair geometry of an entry of the direct search's list (LDS slot | direction
+// code << 12) through the neighbour predicate.
 __device__ __forceinline__ bool verlet_pair(uint32_t e, const float2* shift, int jmax, const float2* s_off,
                                             float2 oi, float R2, int& j, float& rx, float& ry, float& r2) {
   j = min((int)(e & 0xFFFu), jmax);
@@ -87,69 +113,114 @@ __device__ __forceinline__ bool verlet_pair(uint32_t e, const float2* shift, int
   return pair_accept(oi.x, oi.y, oj.x, oj.y, sh.x, sh.y, R2, rx, ry, r2);
 }
 
-// The 32-bit words of one particle's list (two 16-bit entries each, rows
-// `stride` words apart), each loaded DEPTH words before it is used. The
-// register copies w[i] = w[i + 1] make the compiler wait for a load DEPTH - 1
-// iterations after issuing it, so pair work overlaps each load's latency (a
-// load waited for at once left the passes stalled on HBM). Rows past the
-// particle's nw words are not loaded.
-template <int DEPTH>
-struct ListStream {
-  const uint32_t* p;
-  size_t stride;
-  int nw, m;
-  uint32_t w[DEPTH];
-  __device__ __forceinline__ ListStream(const uint32_t* p_, size_t stride_, int nwords)
-      : p(p_), stride(stride_), nw(nwords), m(DEPTH) {
-#pragma unroll
-    for (int i = 0; i < DEPTH; ++i) w[i] = nw > i ? p[(size_t)i * stride] : 0u;
+// Walk the direct search's list of particle g (two 16-bit entries a word);
+// flush() closes a compensation chunk every 16 entries (the last, open chunk is
+// summed by the accumulators' value()). One word is loaded ahead.
+template <typename Body, typename Flush>
+__device__ __forceinline__ void each_listed(const uint32_t* __restrict__ nl, int ntot, int g, int cnt, Body&& body,
+                                            Flush&& flush) {
+  const uint32_t* p = nl + g;
+  uint32_t next = cnt > 0 ? p[0] : 0u;
+  for (int k = 0; k < cnt; k += 2) {
+    const uint32_t w = next;
+    if (k + 2 < cnt) next = p[(size_t)(k / 2 + 1) * ntot];
+    body(w & 0xFFFFu);
+    if (k + 1 < cnt) body(w >> 16);
+    if ((k & 15) == 14) flush();
   }
-  __device__ __forceinline__ uint32_t next() {
-    const uint32_t r = w[0];
+}
+
+// One iteration of a pass over the tile's particles: this lane's particle, and
+// its first 16 list words and counts, which are requested as soon as the tile
+// header is known, together with the fields that are staged, and waited for
+// once. (Three words in flight in a rotation made every iteration of three
+// pairs wait for the word requested one iteration before: with one to four
+// workgroups a CU that was most of a pass.)
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+template <int T>
+struct Lane {
+  int p, g, sub, lpp;   // particle (LDS slot) and its global index (-1: none), lane of the particle's lpp
+  int nw;               // list words this lane may have
+  uint32_t vc;
+  u32x16 w;
+  // word i of this lane: word sub + i lpp of the list (row m of it at vl + m ntot)
+  __device__ __forceinline__ uint32_t word(const StepArgs& a, int i) const {
+    if (lpp == 1) return (a.vl + (size_t)i * (size_t)a.ntot)[(uint32_t)g];
+    return (a.vl + (size_t)(sub + i * lpp) * (size_t)a.ntot)[(uint32_t)g];
+  }
+  __device__ __forceinline__ void load(const StepArgs& a, int i0) {
 #pragma unroll
-    for (int i = 0; i + 1 < DEPTH; ++i) w[i] = w[i + 1];
-    w[DEPTH - 1] = m < nw ? p[(size_t)m * stride] : 0u;
-    ++m;
-    return r;
+    for (int i = 0; i < 16; ++i)
+      if (i0 + i < nw) w[i] = word(a, i0 + i);
+  }
+  // list = false: the lists are not built yet (pass A of a step that renews them)
+  __device__ __forceinline__ void begin(const StepArgs& a, const TileRef<T>& t, int base, int base_lpp, bool list = true) {
+    lpp = lanes_for(t.nin - base, base_lpp);
+    p = base + threadIdx.x / lpp;
+    sub = threadIdx.x & (lpp - 1);
+    g = p < t.nin ? t.global(p) : -1;
+    nw = 0;
+    vc = 0u;
+    if (list) lists(a, t);
+  }
+  __device__ __forceinline__ void lists(const StepArgs& a, const TileRef<T>& t) {
+    nw = (min(t.words, KMAX / 2) + lpp - 1) / lpp;
+    if (g >= 0) {
+      vc = a.vcnt[g];
+      load(a, 0);
+    }
   }
 };
 
-// Walk the list of particle g: lane `sub` of `lpp` takes entries sub,
-// sub+lpp, ...; flush() closes a compensation chunk every 16 entries (the
-// last, open chunk is summed by the accumulators' value()).
-// WPI: list words per iteration of the one-lane walk (2 puts four pairs of
-// work behind each load; the chunking of the compensated sums is the same).
-template <int WPI = 1, typename Body, typename Flush>
-__device__ __forceinline__ void each_listed(const uint32_t* __restrict__ nl, int ntot, int g, int cnt, int lpp,
-                                            int sub, Body&& body, Flush&& flush) {
-  const uint32_t* p = nl + g;
-  if (lpp == 1) {
-    ListStream<WPI == 2 ? 3 : 2> ls(p, (size_t)ntot, (cnt + 1) >> 1);
-    int k = 0;
-    if constexpr (WPI == 2) {
-      for (; k + 3 < cnt; k += 4) {
-        const uint32_t wa = ls.next();
-        const uint32_t wb = ls.next();
-        body(wa & 0xFFFFu);
-        body(wa >> 16);
-        body(wb & 0xFFFFu);
-        body(wb >> 16);
-        if ((k & 15) == 12) flush();
-      }
+template <int CL> struct Class { static constexpr int value = CL; };
+
+// Walk the lane's part of its particle's Verlet list; body(Class<CL>, byte
+// offset of the neighbour's LDS record). One lane per particle: the class
+// bounds are the same for the wave, so the loops are scalar. More lanes: every
+// entry in the general form. flush() closes a compensation chunk every FLUSH
+// words: every word in pass A, whose inner terms are the largest of a sum and
+// come last (with 15 pairs to a chunk the volume, and with it the acceleration,
+// was less exact than an uncompensated sum), 4 in passes C and D, 5 in pass B,
+// where a chunk closes 17 sums.
+template <int T, int KERN, int FLUSH, typename Body, typename Flush>
+__device__ __forceinline__ void walk_list(const StepArgs& a, Lane<T>& l, Body&& body, Flush&& flush) {
+  using F = ListFmt<T, KERN>;
+  constexpr int EPW = F::EPW;
+  const int cnt = vc_total(l.vc);
+  const uint32_t vu = (uint32_t)__builtin_amdgcn_readfirstlane((int)l.vc);
+  const int one = l.lpp == 1;
+  const int wo = one ? vc_outer(vu) / EPW : 0, wm = one ? vc_middle(vu) / EPW : 0;
+  const int wx = ((vc_most(vu) + EPW - 1) / EPW + l.lpp - 1) / l.lpp;   // <= l.nw, from the list alone
+  int f = 0;
+  auto chunk = [&]() {
+    if (++f == FLUSH) {
+      asm volatile("");   // a scalar branch around the sums, not selects on each of them
+      flush();
+      f = 0;
     }
-    for (; k + 1 < cnt; k += 2) {
-      const uint32_t w = ls.next();
-      body(w & 0xFFFFu);
-      body(w >> 16);
-      if ((k & 15) == 14) flush();
+  };
+  for (int m0 = 0; m0 < wx; m0 += 16) {
+    if (m0) l.load(a, m0);
+    int m = m0;
+    for (const int e = min(wo, m0 + 16); m < e; ++m) {
+      const uint32_t x = l.w[m - m0];
+#pragma unroll
+      for (int i = 0; i < EPW; ++i) body(Class<OUTER>(), F::at(x, i));
+      chunk();
     }
-    if (k < cnt) body(ls.next() & 0xFFFFu);
-  } else {
-    int it = 0;
-    for (int k = sub; k < cnt; k += lpp, ++it) {
-      const uint32_t w = p[(size_t)(k >> 1) * ntot];
-      body((k & 1) ? (w >> 16) : (w & 0xFFFFu));
-      if ((it & 15) == 15) flush();
+    for (const int e = min(wm, m0 + 16); m < e; ++m) {
+      const uint32_t x = l.w[m - m0];
+#pragma unroll
+      for (int i = 0; i < EPW; ++i) body(Class<MIDDLE>(), F::at(x, i));
+      chunk();
+    }
+    for (const int e = min(wx, m0 + 16); m < e; ++m) {
+      const uint32_t x = l.w[m - m0];
+      const int k = (l.sub + m * l.lpp) * EPW;
+#pragma unroll
+      for (int i = 0; i < EPW; ++i)
+        if (k + i < cnt) body(Class<INNER>(), F::at(x, i));
+      chunk();
     }
   }
 }
@@ -258,117 +329,139 @@ __device__ __forceinline__ void tile_pass_a(const StepArgs& a, int w) {
 // checks and requests a rebuild, as does every rebin, new state, tile change
 // or snapshot restore): a pair left out was at least 3h + delta apart, so it is
 // still more than 3h + 0.1 delta apart; pairs outside the stencil are excluded
-// by the rebin criterion. Every pass walks it and applies the exact predicate,
-// so the candidate search of the ~144 stencil particles runs only on rebuild
-// steps. Pass A sums the kernel over the accepted pairs (the volume).
+// by the rebin criterion. The same margin keeps outer pairs (beyond 2h + delta
+// at the build) at q > 2 and middle pairs (beyond h + delta) at q > 1.
 
-// Build: candidate search with the Verlet radius (masks as in the direct
-// search), then one walk over the Verlet pairs in cell order that writes the
-// list and sums W over the pairs that pass the exact predicate.
-template <int T, int COMP, int KERN>
-__device__ __forceinline__ void tile_pass_a_build(const StepArgs& a, int w) {
-  __shared__ TileLDS<T> L;
-  __shared__ float2 s_off[TileCfg<T, KERN>::MAXP];
-  __shared__ unsigned long long s_mask[9 * WG];
-  const TileRef t = tile_ref<T>(a, w);
-  const RepDev R = a.reps[t.rep];
-  const int ni = t.ni, nint = t.ni * t.nj, nreg = (t.ni + 2) * (t.nj + 2);
-  const int S = t.S, nin = t.nin;
-  const int tid = threadIdx.x;
-  tile_cells<T>(t, L, R);
-  stage_tile<T, KERN>(t, [&](int g) { return a.off_cur[g]; }, [&](int j, int, float2 o) { s_off[j] = o; });
+// Build: one sweep over the ~144 candidates of the stencil counts the classes,
+// then one sweep per class writes its entries in cell order. Returns the most
+// list words of a particle of the tile (kept in the header). Runs on the steps
+// that need it only (every few thousand at the benchmark's speeds).
+template <int T, int KERN>
+__device__ __forceinline__ int build_list(const StepArgs& a, const TileRef<T>& t, ConstRep& R, const CellLDS<T>& L,
+                                       const int2* s_x, int w) {
+  using F = ListFmt<T, KERN>;
+  constexpr int EPW = F::EPW;
+  __shared__ int most;
+  if (threadIdx.x == 0) most = 0;
   __syncthreads();
-  for (int base = 0; base < nin; base += WG) {
-    const int p = base + tid;
-    if (p >= nin) break;
-    const int st = find_cell(L.cstart, nint, p);
-    const int li = st % ni, lj = st / ni;
-    const float2 oi = s_off[p];
-    int cnt = 0;
-    bool big = false;
+  const int ni = t.ni, nint = t.ni * t.nj;
+  for (int base = 0; base < t.nin; base += WG) {
+    const int p = base + threadIdx.x;
+    const bool act = p < t.nin;
+    int li = 0, lj = 0;
+    int2 xi = make_int2(0, 0);
+    if (act) {
+      const int st = find_cell(L.start, nint, p);
+      li = st % ni; lj = st / ni;
+      xi = s_x[p];
+    }
+    // visit(slot, r2) of every listed candidate, in cell order
+    auto sweep = [&](auto&& visit) {
 #pragma unroll 1
-    for (int cidx = 0; cidx < 9; ++cidx) {
-      const int dy = cidx / 3, dx = cidx % 3;
-      const int sc = L.slot[(lj + dy) * (ni + 2) + (li + dx)];
-      const int j0 = L.cstart[sc];
-      const int nj = L.cstart[sc + 1] - j0;
-      if (nj > CELL_MAX) big = true;
-      const uint32_t code = (uint32_t)dx | ((uint32_t)dy << 2);
-      const float2 sh = L.shift[code];
-      uint32_t mlo = 0u, mhi = 0u;
-      const int n0 = min(nj, 32), n1 = min(nj, CELL_MAX);
-      for (int b = 0; b < n0; ++b) {
-        const float2 oj = s_off[j0 + b];
-        float rx, ry, r2;
-        if (pair_accept(oi.x, oi.y, oj.x, oj.y, sh.x, sh.y, R.R2v, rx, ry, r2)) mlo |= 1u << b;
+      for (int q = 0; q < 9; ++q) {
+        const int sc = L.slot[(lj + q / 3) * (ni + 2) + (li + q % 3)];
+        const int j0 = L.start[sc], n = min(L.start[sc + 1] - j0, CELL_MAX);
+#pragma unroll 1
+        for (int j = j0; j < j0 + n; ++j) {
+          const float r2 = fixed_pair(xi, s_x[j]).r2;
+          if (r2 < R.R2v_fix && j != p) visit(j, r2);
+        }
       }
-      for (int b = 32; b < n1; ++b) {
-        const float2 oj = s_off[j0 + b];
-        float rx, ry, r2;
-        if (pair_accept(oi.x, oi.y, oj.x, oj.y, sh.x, sh.y, R.R2v, rx, ry, r2)) mhi |= 1u << (b - 32);
+    };
+    int all = 0, no = 0, nm = 0;   // listed; outer; outer and middle
+    bool big = false;
+    if (act) {
+#pragma unroll 1
+      for (int q = 0; q < 9; ++q) {
+        const int sc = L.slot[(lj + q / 3) * (ni + 2) + (li + q % 3)];
+        big |= L.start[sc + 1] - L.start[sc] > CELL_MAX;
       }
-      s_mask[cidx * WG + tid] = ((unsigned long long)code << 60) | ((unsigned long long)j0 << 48) |
-                                ((unsigned long long)mhi << 32) | mlo;
-      cnt += __popc(mlo) + __popc(mhi);
+      sweep([&](int, float r2) {
+        ++all;
+        no += r2 > R.R2o_fix;
+        nm += r2 > R.R2m_fix;
+      });
+      if (all > KMAX || big) flag(a.flags, ERR_OVERFLOW);
     }
-    const int vk = min(cnt, KMAX);
-    const int g = L.gstart[st] + (p - L.cstart[st]);
-    if (cnt > KMAX || big) flag(a.flags, ERR_OVERFLOW);
-    Acc<COMP> sw;
-    sw.init();
-    int c = -1;
-    unsigned long long m = 0ull, x = 0ull;
-    uint32_t vword = 0u;
-    uint32_t* vdst = a.vl + g;
-    for (int k = 0; k < vk; ++k) {
-      while (m == 0ull && c < 8) {
-        ++c;
-        x = s_mask[c * WG + tid];
-        m = x & MASK48;
-      }
-      const uint32_t hi = (uint32_t)(x >> 48);
-      const int j = (int)(hi & 0xFFFu) + __builtin_ctzll(m);
-      m &= m - 1ull;
-      const uint32_t e = (uint32_t)j | (hi & 0xF000u);
-      if (k & 1) vdst[(size_t)(k >> 1) * a.ntot] = vword | (e << 16);
-      else vword = e;
-      int jj;
-      float rx, ry, r2;
-      if (verlet_pair(e, L.shift, S - 1, s_off, oi, R.R2, jj, rx, ry, r2)) sw.add(kernel_raw<KERN>(R, r2).W);
-      if ((k & 15) == 15) sw.end_cell();
+    const int kept = min(all, KMAX);
+    // what every particle of the wave can take in a class, and the most entries
+    int go = act ? min(no, kept) / EPW * EPW : 255, gm = act ? min(nm, kept) / EPW * EPW : 255, gx = kept;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      go = min(go, __shfl_xor(go, o, 64));
+      gm = min(gm, __shfl_xor(gm, o, 64));
+      gx = max(gx, __shfl_xor(gx, o, 64));
     }
-    if (vk & 1) vdst[(size_t)(vk >> 1) * a.ntot] = vword;
-    a.vcnt[g] = vk;
-    a.off_build[g] = oi;
-    a.V[g] = 1.0f / (R.a2 * (kernel_w0_raw<KERN>() + sw.value()));
+    if ((threadIdx.x & 63) == 0) atomicMax(&most, gx);
+    if (!act) continue;
+    const int g = t.global(p);
+    uint32_t* dst = a.vl + g;
+    uint32_t word = 0u;
+    int k = 0, i = 0;
+#pragma unroll 1
+    for (int cl = OUTER; cl <= INNER; ++cl)
+      sweep([&](int j, float r2) {
+        if (cl != (r2 > R.R2o_fix ? OUTER : (r2 > R.R2m_fix ? MIDDLE : INNER)) || k >= KMAX) return;
+        word |= F::pack((uint32_t)j, i);
+        ++k;
+        if (++i == EPW) {
+          *dst = F::seal(word);
+          dst += a.ntot;
+          word = 0u;
+          i = 0;
+        }
+      });
+    if (i) *dst = F::seal(word);
+    a.vcnt[g] = (uint32_t)kept | (uint32_t)go << 8 | (uint32_t)gm << 16 | (uint32_t)gx << 24;
+    a.off_build[g] = a.off_cur[g];
   }
+  __syncthreads();
+  const int words = (most + EPW - 1) / EPW;
+  if (threadIdx.x == 0) ((int*)a.hdr)[(size_t)w * HdrCfg<T>::INTS + HDR_WORDS] = words;
+  return words;
 }
 
-// Walk: the volume over the Verlet entries that pass the exact predicate.
+// The list when this step renews it, then the volume over its entries.
 template <int T, int COMP, int KERN>
-__device__ __forceinline__ void tile_pass_a_walk(const StepArgs& a, int w) {
-  __shared__ float2 s_shift[16];
-  __shared__ float2 s_off[TileCfg<T, KERN>::MAXP];
-  const TileRef t = tile_ref<T>(a, w);
-  const RepDev R = a.reps[t.rep];
-  const int S = t.S, nin = t.nin;
-  stage_shift(s_shift, R);
-  stage_tile<T, KERN>(t, [&](int g) { return a.off_cur[g]; }, [&](int j, int, float2 o) { s_off[j] = o; });
+__device__ __forceinline__ void tile_pass_a_step(const StepArgs& a, int w, bool renew) {
+  __shared__ CellLDS<T> L;
+  __shared__ int2 s_x[TileCfg<T, KERN>::MAXP];
+  TileRef<T> t(a, w);
+  ConstRep& R = rep_of_tile(a, t.rep);
+  Lane<T> l;
+  l.begin(a, t, 0, 1, !renew);
+  if (t.over && threadIdx.x == 0) flag(a.flags, ERR_OVERFLOW);
+  if (renew) tile_cells<T>(t, L);
+  stage_tile<T, KERN>(t, [&](int g) { return a.off_cur[g]; },
+                      [&](int j, int e, float2 o) { s_x[j] = fixed_position(R, o, e); });
   __syncthreads();
-  for (int base = 0; base < nin; base += WG) {
-    const int p = base + threadIdx.x;
-    if (p >= nin) break;
-    const int g = t.template global<T>(p);
-    const float2 oi = s_off[p];
+  if (renew) {
+    t.words = build_list<T, KERN>(a, t, R, L, s_x, w);
+    l.lists(a, t);
+  }
+  const float hinv = R.hinv_fix;
+  for (int base = 0; base < t.nin;) {
+    base += WG / l.lpp;
+    const int g = l.g;
+    const int2 xi = s_x[g >= 0 ? l.p : 0];
     Acc<COMP> sw;
     sw.init();
-    each_listed<2>(a.vl, a.ntot, g, min(a.vcnt[g], KMAX), 1, 0, [&](uint32_t e) {
-      int j; float rx, ry, r2;
-      const bool in = verlet_pair(e, s_shift, S - 1, s_off, oi, R.R2, j, rx, ry, r2);
-      const float W = kernel_raw<KERN>(R, r2).W;
-      sw.add(in ? W : 0.0f);                 // exact zero outside the support
+    if (g >= 0)
+    walk_list<T, KERN, 1>(a, l, [&](auto cl, uint32_t at) {
+      constexpr int CL = decltype(cl)::value;
+      const FixPair d = fixed_pair(xi, lds_at(s_x, at));
+      if (CL == INNER && !(d.r2 > 0.0f)) return;   // coincident particles are no neighbours
+      const float r = __builtin_amdgcn_sqrtf(d.r2);
+      if constexpr (KERN == 0 && CL == OUTER) {
+        const Spline k = spline_terms<CL>(r, hinv);
+        sw.fma(k.t34, k.t3);
+      } else {
+        sw.add(class_w<KERN, CL>(r, hinv));   // the terms of W cancel: summed apart they cost V a bit
+      }
     }, [&]() { sw.end_cell(); });
-    a.V[g] = 1.0f / (R.a2 * (kernel_w0_raw<KERN>() + sw.value()));
+    const float sum = wave_sum(sw.value(), l.lpp);
+    if (g >= 0 && l.sub == 0) a.V[g] = 1.0f / (R.a2 * (kernel_w0_raw<KERN>() + sum));
+    if (base < t.nin) l.begin(a, t, base, 1);
   }
 }
 
@@ -379,39 +472,37 @@ __device__ __forceinline__ void tile_pass_a_walk(const StepArgs& a, int w) {
 template <int T, int COMP, int FORM, int EL, int KERN, int Q3>
 __device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w) {
   static_assert(Q3 == 0 || (FORM == 0 && EL == 0), "quasi-2D: corrected form, no lambda terms");
-  __shared__ float2 s_shift[16];
   constexpr int MP = TileCfg<T, KERN>::MAXP;
-  __shared__ float2 s_off[MP];
+  __shared__ int2 s_x[MP];
   __shared__ float2 s_u[MP];
   __shared__ float2 s_q[MP];
-  __shared__ float s_V[MP];                  // V dWc: V_j F = s_V[j] Fr
+  __shared__ float s_V[MP];                  // V dW: V_j F = s_V[j] Fr
   __shared__ float s_rho[FORM == 1 ? MP : 1];
   __shared__ float s_qc[Q3 == 1 ? MP : 1];   // Qyy of the quasi-2D variant
-  const TileRef t = tile_ref<T>(a, w);
-  const RepDev R = a.reps[t.rep];
-  const int S = t.S, nin = t.nin;
-  stage_shift(s_shift, R);
+  const TileRef<T> t(a, w);
+  ConstRep& R = rep_of_tile(a, t.rep);
+  const int nin = t.nin;
+  Lane<T> l;
+  l.begin(a, t, 0, a.lpp);
+  const float hinv = R.hinv_fix;
+  // grad_i W_ij = dWc F r_ij per unit of r for Wendland C2 (F = (1 - q/2)^3); the
+  // quintic's F holds 1/r, in which the unit cancels
+  const float dW = KERN == 1 ? R.dWc * R.unfix : R.dWc;
   struct In { float2 off, u, q; float V, x; };
   stage_tile<T, KERN>(t, [&](int g) {
     return In{a.off_cur[g], a.u[g], a.q_cur[g], a.V[g], Q3 == 1 ? a.qyy_cur[g] : (FORM == 1 ? a.drho[g] : 0.0f)};
-  }, [&](int j, int, const In& v) {
-    s_off[j] = v.off;
+  }, [&](int j, int e, const In& v) {
+    s_x[j] = fixed_position(R, v.off, e);
     s_u[j] = v.u;
     s_q[j] = v.q;
     if constexpr (Q3 == 1) s_qc[j] = v.x;
-    s_V[j] = v.V * R.dWc;
+    s_V[j] = v.V * dW;
     if constexpr (FORM == 1) s_rho[j] = R.rho0 + v.x;
   });
   __syncthreads();
   for (int base = 0; base < nin;) {
-    const int lpp = lanes_for(nin - base, a.lpp);
-    const int p = base + threadIdx.x / lpp;
-    const int sub = threadIdx.x & (lpp - 1);
+    const int lpp = l.lpp, p = l.p, sub = l.sub, g = l.g;
     base += WG / lpp;
-    int g = -1;
-    if (p < nin) {
-      g = t.template global<T>(p);
-    }
     const bool act = g >= 0;
     // raw pair sums (see the epilogue for their meaning)
     Acc<COMP> Sxx, Sxy, Syy, Gxx, Gxy, Gyx, Gyy, Qax, Qay, Qbx, Qby;
@@ -428,45 +519,43 @@ __device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w) {
     float qci = 0.f;
     float ri = 1.0f;
     if (act) {
-      const float2 oi = s_off[p];
+      const int2 xi = s_x[p];
       ui = s_u[p];
       qi = s_q[p];
       if constexpr (Q3 == 1) qci = s_qc[p];
       if constexpr (FORM == 1) ri = s_rho[p];
       const float ri2inv = 1.0f / (ri * ri);
-      const int cnt = min(a.vcnt[g], KMAX);
-      each_listed<2>(a.vl, a.ntot, g, cnt, lpp, sub, [&](uint32_t e) {
-        int j; float rx, ry, r2;
-        // entries outside the support are skipped (a branch measured faster
-        // here than zeroing their terms with selects)
-        if (!verlet_pair(e, s_shift, S - 1, s_off, oi, R.R2, j, rx, ry, r2)) return;
-        const KW k = kernel_raw<KERN>(R, r2);
-        const float2 uj = s_u[j], qj = s_q[j];
-        const float c = s_V[j] * k.F;          // V_j W'(r)/r
-        const float cx = c * rx, cy = c * ry;  // V_j grad_i W_ij
-        const float txx = cx * rx, txy = cx * ry, tyy = cy * ry;
-        Sxx.add(txx); Sxy.add(txy); Syy.add(tyy);
+      walk_list<T, KERN, ListFmt<T, KERN>::CHUNK>(a, l, [&](auto cl, uint32_t at) {
+        constexpr int CL = decltype(cl)::value;
+        const FixPair d = fixed_pair(xi, lds_at(s_x, at));
+        if (CL == INNER && !(d.r2 > 0.0f)) return;   // coincident particles are no neighbours
+        const float rinv = __builtin_amdgcn_rsqf(d.r2);
+        const float F = class_f<KERN, CL>(d.r2 * rinv, rinv, hinv);   // W'(r) per unit, over r and dWc
+        const float2 uj = lds_at(s_u, at), qj = lds_at(s_q, at);
+        const uint32_t at4 = at >> 1;
+        const float c = *(const float*)((const char*)s_V + at4) * F;
+        const float cx = c * d.rx, cy = c * d.ry;    // V_j grad_i W_ij
+        const float e2 = rinv * rinv, ex = cx * e2, ey = cy * e2;
+        const float txx = ex * d.rx, txy = ex * d.ry, tyy = ey * d.ry;   // V_j F r (x) r / r^2, per unit
+        Sxx.fma(cx, d.rx); Sxy.fma(cx, d.ry); Syy.fma(cy, d.ry);
         const float dux = uj.x - ui.x, duy = uj.y - ui.y;
         const float dqa = qj.x - qi.x, dqb = qj.y - qi.y;
         Gxx.fma(dux, cx); Gxy.fma(dux, cy); Gyx.fma(duy, cx); Gyy.fma(duy, cy);
         Qax.fma(dqa, cx); Qay.fma(dqa, cy); Qbx.fma(dqb, cx); Qby.fma(dqb, cy);
-        const float e2 = k.rinv * k.rinv;
-        const float la = -dqa * e2, lb = -dqb * e2;   // (Q_i - Q_j)/r^2
-        Mxx_a.fma(la, txx); Mxy_a.fma(la, txy); Myy_a.fma(la, tyy);
-        Mxx_b.fma(lb, txx); Mxy_b.fma(lb, txy); Myy_b.fma(lb, tyy);
+        Mxx_a.fma(dqa, txx); Mxy_a.fma(dqa, txy); Myy_a.fma(dqa, tyy);
+        Mxx_b.fma(dqb, txx); Mxy_b.fma(dqb, txy); Myy_b.fma(dqb, tyy);
         if constexpr (Q3 == 1) {
-          const float dqc = s_qc[j] - qci;
+          const float dqc = *(const float*)((const char*)s_qc + at4) - qci;
           Qcx.fma(dqc, cx); Qcy.fma(dqc, cy);
-          const float lc = -dqc * e2;
-          Mxx_c.fma(lc, txx); Mxy_c.fma(lc, txy); Myy_c.fma(lc, tyy);
+          Mxx_c.fma(dqc, txx); Mxy_c.fma(dqc, txy); Myy_c.fma(dqc, tyy);
         }
-        const float sv = -(dux * rx + duy * ry) * e2;  // (u_i - u_j).r_ij / r^2
+        const float sv = (dux * d.rx + duy * d.ry) * -e2;  // (u_i - u_j).r_ij / r^2, per unit
         if constexpr (FORM == 0) {
           Vsx.fma(sv, cx); Vsy.fma(sv, cy);
         } else {
-          const float rj = s_rho[j];
-          const float Ft = R.dWc * k.F;
-          const float fx = Ft * rx, fy = Ft * ry;    // grad_i W_ij
+          const float rj = *(const float*)((const char*)s_rho + at4);
+          const float Ft = dW * F;
+          const float fx = Ft * d.rx, fy = Ft * d.ry;    // grad_i W_ij
           Kc.add(-(dux * fx + duy * fy));
           const float svr = sv / rj;
           V1x.fma(svr, fx); V1y.fma(svr, fy);
@@ -507,7 +596,8 @@ __device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w) {
     }
     if (act && sub == 0) {
       // alpha = -sum_j V_j W'/r r_ij (x) r_ij, B = alpha^{-1}
-      const float axx = -sxx, axy = -sxy, ayy = -syy;
+      const float un = -R.unfix;
+      const float axx = un * sxx, axy = un * sxy, ayy = un * syy;
       const float det = axx * ayy - axy * axy;
       const float nrm = axx * axx + 2.0f * axy * axy + ayy * ayy;
       float Bxx = 1.f, Bxy = 0.f, Byy = 1.f;
@@ -529,8 +619,9 @@ __device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w) {
       const float dax = qax * Bxx + qay * Bxy, day = qax * Bxy + qay * Byy;
       const float dbx = qbx * Bxx + qby * Bxy, dby = qbx * Bxy + qby * Byy;
       // Laplacians: 2 sum_j V_j (Q_i - Q_j) (r_ij . g_ij) / r^2
-      const float lapa = 2.0f * (Bxx * mxxa + 2.0f * Bxy * mxya + Byy * myya);
-      const float lapb = 2.0f * (Bxx * mxxb + 2.0f * Bxy * mxyb + Byy * myyb);
+      const float fx2 = -2.0f * R.fix;   // the sums hold Q_j - Q_i, per unit
+      const float lapa = fx2 * (Bxx * mxxa + 2.0f * Bxy * mxya + Byy * myya);
+      const float lapb = fx2 * (Bxx * mxxb + 2.0f * Bxy * mxyb + Byy * myyb);
       const float qa = qi.x, qb = qi.y;
       const float e12 = 0.5f * (G12 + G21), w12 = 0.5f * (G12 - G21);
       float Ha, Hb;
@@ -551,7 +642,7 @@ __device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w) {
         // tensors (its trace is (2 lambda/3) div u from the weak compressibility).
         const float qc = qci, qz = -qa - qc;
         dcy = qcx * Bxy + qcy * Byy;
-        const float lapc = 2.0f * (Bxx * mxxc + 2.0f * Bxy * mxyc + Byy * myyc);
+        const float lapc = fx2 * (Bxx * mxxc + 2.0f * Bxy * mxyc + Byy * myyc);
         const float lapz = -lapa - lapc;
         const float t2 = qa * qa + 2.0f * qb * qb + qc * qc + qz * qz;
         const float cb = R.A + R.C * t2, t3 = t2 * (1.0f / 3.0f);
@@ -576,10 +667,11 @@ __device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w) {
         const float vcx = vsx * Bxx + vsy * Bxy, vcy = vsx * Bxy + vsy * Byy;
         // div Q: (dQxx/dx + dQxy/dy, dQxy/dx + dQyy/dy), Qyy = -Qxx in d = 2
         const float divqx = dax + dby, divqy = (Q3 == 0) ? dbx - day : dbx + dcy;
-        apx = 8.0f * R.eta * vcx - R.zeta * divqx;
-        apy = 8.0f * R.eta * vcy - R.zeta * divqy;
+        const float e8 = 8.0f * R.eta * R.fix;   // the sums are per unit
+        apx = e8 * vcx - R.zeta * divqx;
+        apy = e8 * vcy - R.zeta * divqy;
       } else {
-        const float cv = R.mass * 8.0f * R.eta / ri;
+        const float cv = R.mass * 8.0f * R.eta * R.fix / ri;
         apx = cv * v1x - R.zeta * R.mass * a1x;
         apy = cv * v1y - R.zeta * R.mass * a1y;
       }
@@ -596,54 +688,47 @@ __device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w) {
         f[8] = drho_n * R.inv_rho0; f[9] = R.zeta;
       }
     }
+    if (base < nin) l.begin(a, t, base, a.lpp);
   }
 }
 
 // ------------------------------------------------------------------ pass C
 template <int T, int COMP, int KERN>
 __device__ __forceinline__ void tile_pass_c(const StepArgs& a, int w) {
-  __shared__ float2 s_shift[16];
   constexpr int MP = TileCfg<T, KERN>::MAXP;
-  __shared__ float2 s_off[MP];
+  __shared__ int2 s_x[MP];
   __shared__ float s_dh[MP];
   __shared__ float2 s_u[MP];
-  const TileRef t = tile_ref<T>(a, w);
-  const RepDev R = a.reps[t.rep];
-  const int S = t.S, nin = t.nin;
-  stage_shift(s_shift, R);
+  const TileRef<T> t(a, w);
+  ConstRep& R = rep_of_tile(a, t.rep);
+  const int nin = t.nin;
+  Lane<T> l;
+  l.begin(a, t, 0, a.lpp);
+  const float hinv = R.hinv_fix;
   struct In { float2 off, u; float dh; };
   stage_tile<T, KERN>(t, [&](int g) { return In{a.off_cur[g], a.u[g], a.dh[g]}; },
-                      [&](int j, int, const In& v) { s_off[j] = v.off; s_dh[j] = v.dh; s_u[j] = v.u; });
+                      [&](int j, int e, const In& v) { s_x[j] = fixed_position(R, v.off, e); s_dh[j] = v.dh; s_u[j] = v.u; });
   __syncthreads();
   unsigned umb = 0;
   for (int k = 0; k < UMAX_SLOTS; ++k) umb = max(umb, a.umax_cur[t.rep * UMAX_SLOTS + k]);
   const float c0 = R.c0_factor * __uint_as_float(umb);
   const float pc = R.rho0 * c0 * c0 / R.gamma_eos;
   for (int base = 0; base < nin;) {
-    const int lpp = lanes_for(nin - base, a.lpp);
-    const int p = base + threadIdx.x / lpp;
-    const int sub = threadIdx.x & (lpp - 1);
+    const int lpp = l.lpp, p = l.p, sub = l.sub, g = l.g;
     base += WG / lpp;
-    int g = -1;
-    if (p < nin) {
-      g = t.template global<T>(p);
-    }
     const bool act = g >= 0;
     Acc<COMP> sd, Wux, Wuy;   // in units of a2
     sd.init(); Wux.init(); Wuy.init();
     if (act) {
-      const float2 oi = s_off[p], ui = s_u[p];
-      const int cnt = min(a.vcnt[g], KMAX);
-      each_listed<2>(a.vl, a.ntot, g, cnt, lpp, sub, [&](uint32_t e) {
-        int j; float rx, ry, r2;
-        // entries outside the support add exact zeros (a select: a branch here
-        // splits the four-entry iteration and measured 9% slower); the select
-        // also drops the non-finite W of coincident particles
-        const bool in = verlet_pair(e, s_shift, S - 1, s_off, oi, R.R2, j, rx, ry, r2);
-        const float Wr = kernel_raw<KERN>(R, r2).W;
-        const float W = in ? Wr : 0.0f;
-        const float2 uj = s_u[j];
-        sd.fma(s_dh[j], W);
+      const int2 xi = s_x[p];
+      const float2 ui = s_u[p];
+      walk_list<T, KERN, 4>(a, l, [&](auto cl, uint32_t at) {
+        constexpr int CL = decltype(cl)::value;
+        const FixPair d = fixed_pair(xi, lds_at(s_x, at));
+        if (CL == INNER && !(d.r2 > 0.0f)) return;   // coincident particles are no neighbours
+        const float W = class_w<KERN, CL>(__builtin_amdgcn_sqrtf(d.r2), hinv);
+        const float2 uj = lds_at(s_u, at);
+        sd.fma(*(const float*)((const char*)s_dh + (at >> 1)), W);
         Wux.fma(ui.x - uj.x, W); Wuy.fma(ui.y - uj.y, W);   // sum_j (u_i - u_j) W_ij
       }, [&]() { sd.end_cell(); Wux.end_cell(); Wuy.end_cell(); });
     }
@@ -666,6 +751,7 @@ __device__ __forceinline__ void tile_pass_c(const StepArgs& a, int w) {
       a.drhat[g] = drh;
       a.uv[g] = sqrtf(wux * wux + wuy * wuy) * (R.a2 * Vi);
     }
+    if (base < nin) l.begin(a, t, base, a.lpp);
   }
 }
 
@@ -673,42 +759,37 @@ __device__ __forceinline__ void tile_pass_c(const StepArgs& a, int w) {
 // INTEG: corrector, 0 kick-drift-kick, 1 midpoint (the integrator parameter picks the variant at launch).
 template <int T, int COMP, int FORM, int EL, int KERN, int INTEG>
 __device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w) {
-  __shared__ float2 s_shift[16];
   constexpr int MP = TileCfg<T, KERN>::MAXP;
-  // FORM 0 stages V dWc (V_j F = s_V[j] Fr); without the lambda stress it also
-  // stages s_P = P V dWc, so that (P_i + P_j) V_j F = (P_i s_V[j] + s_P[j]) Fr.
+  // FORM 0 stages V dWc (V_j F = V_j dWc Fr); without the lambda stress it also
+  // stages P V dWc, so that (P_i + P_j) V_j F = (P_i V_j + PV_j) Fr.
   constexpr bool PV = FORM == 0 && EL == 0;
   __shared__ float2 s_off[MP];
-  __shared__ float s_V[MP];
-  __shared__ float s_P[MP];
+  __shared__ float2 s_cell[MP];   // region cell of the particle
+  __shared__ float2 s_VP[MP];     // {V dWc, P V dWc or P}
   __shared__ float2 s_pi[EL == 1 ? MP : 1];
   __shared__ float s_wmax[WG / 64];
-  const TileRef t = tile_ref<T>(a, w);
-  const RepDev R = a.reps[t.rep];
-  const int S = t.S, nin = t.nin;
-  stage_shift(s_shift, R);
+  const TileRef<T> t(a, w);
+  ConstRep& R = rep_of_tile(a, t.rep);
+  const int nin = t.nin;
+  Lane<T> l;
+  l.begin(a, t, 0, a.lpp);
+  const float hinv = R.hinv, cs = R.cs, R2 = R.R2;
   struct In { float2 off, pi; float V, P; };
   stage_tile<T, KERN>(t, [&](int g) {
     return In{a.off_cur[g], EL == 1 ? a.pi[g] : make_float2(0.f, 0.f), a.V[g], a.P[g]};
-  }, [&](int j, int, const In& v) {
+  }, [&](int j, int e, const In& v) {
     s_off[j] = v.off;
+    s_cell[j] = region_cell(e);
     const float Vd = v.V * R.dWc;
-    s_V[j] = Vd;
-    s_P[j] = PV ? v.P * Vd : v.P;
+    s_VP[j] = make_float2(Vd, PV ? v.P * Vd : v.P);
     if constexpr (EL == 1) s_pi[j] = v.pi;
   });
   __syncthreads();
   float umax_l = 0.0f;
   bool rebin = false, bad = false, relist = false;
   for (int base = 0; base < nin;) {
-    const int lpp = lanes_for(nin - base, a.lpp);
-    const int p = base + threadIdx.x / lpp;
-    const int sub = threadIdx.x & (lpp - 1);
+    const int lpp = l.lpp, p = l.p, sub = l.sub, g = l.g;
     base += WG / lpp;
-    int g = -1;
-    if (p < nin) {
-      g = t.template global<T>(p);
-    }
     const bool act = g >= 0;
     Acc<COMP> Px, Py, Exx, Exy, Eyx, Eyy;
     Acc<COMP> Gx, Gy, Gr;   // APD geometry: sum r_ij / r^3, sum r
@@ -718,22 +799,25 @@ __device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w) {
     int nacc = 0;   // accepted neighbours taken by this lane
     if (act) {
       oi = s_off[p];
-      const float Pi = PV ? a.P[g] : s_P[p];
+      const float2 ci = s_cell[p];
+      const float Pi = PV ? a.P[g] : s_VP[p].y;
       float2 pii = {0.f, 0.f};
       if constexpr (EL == 1) pii = s_pi[p];
-      const int cnt = min(a.vcnt[g], KMAX);
-      each_listed<2>(a.vl, a.ntot, g, cnt, lpp, sub, [&](uint32_t e) {
-        int j; float rx, ry, r2;
-        if (!verlet_pair(e, s_shift, S - 1, s_off, oi, R.R2, j, rx, ry, r2)) return;   // as in pass B
+      walk_list<T, KERN, 4>(a, l, [&](auto cl, uint32_t at) {
+        constexpr int CL = decltype(cl)::value;
+        float rx, ry, r2;
+        if (!neighbour<CL == INNER>(oi, ci, lds_at(s_off, at), lds_at(s_cell, at), cs, R2, rx, ry, r2)) return;
         ++nacc;
-        const KW k = kernel_raw<KERN>(R, r2);
-        const float c = (FORM == 0) ? s_V[j] * k.F : R.dWc * k.F;
-        const float f = PV ? fmaf(Pi, s_V[j], s_P[j]) * k.F : (Pi + s_P[j]) * c;
+        const float rinv = __builtin_amdgcn_rsqf(r2), r = r2 * rinv;
+        const float F = class_f<KERN, CL>(r, rinv, hinv);
+        const float2 vp = lds_at(s_VP, at);
+        const float c = (FORM == 0) ? vp.x * F : R.dWc * F;
+        const float f = PV ? fmaf(Pi, vp.x, vp.y) * F : (Pi + vp.y) * c;
         Px.fma(f, rx); Py.fma(f, ry);
-        const float r3 = k.rinv * k.rinv * k.rinv;
-        Gx.fma(rx, r3); Gy.fma(ry, r3); Gr.add(k.r);
+        const float r3 = rinv * rinv * rinv;
+        Gx.fma(rx, r3); Gy.fma(ry, r3); Gr.add(r);
         if constexpr (EL == 1) {
-          const float2 pj = s_pi[j];
+          const float2 pj = lds_at(s_pi, at);
           const float cx = c * rx, cy = c * ry;
           const float dpa = pj.x - pii.x, dpb = pj.y - pii.y;
           Exx.fma(dpa, cx); Exy.fma(dpa, cy); Eyx.fma(dpb, cx); Eyy.fma(dpb, cy);
@@ -795,8 +879,8 @@ __device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w) {
       // r^{n+1} - r^{n+1/2}: u^{n+1} dt/2 (kick-drift-kick) or u^{n+1/2} dt/2
       // (midpoint, r^n + u^{n+1/2} dt), then the next predictor's u^{n+3/2} dt/2
       const float vdx = INTEG == 0 ? u1x : uh.x, vdy = INTEG == 0 ? u1y : uh.y;
-      const float dispx = hdt * vdx + drx + hdt * unx;
-      const float dispy = hdt * vdy + dry + hdt * uny;
+      const float hvx = hdt * vdx, hvy = hdt * vdy, hnx = hdt * unx, hny = hdt * uny;
+      const float dispx = (hvx + hnx) + drx, dispy = (hvy + hny) + dry;
       // compensated position update: (hi, lo) += disp
       const float2 lo = a.offlo[g];
       float2 nh, nl;
@@ -825,6 +909,7 @@ __device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w) {
         rebin = true;
       if (!(isfinite(unx) && isfinite(uny) && isfinite(nh.x) && isfinite(nh.y) && isfinite(dn))) bad = true;
     }
+    if (base < nin) l.begin(a, t, base, a.lpp);
   }
   // max speed: wave shuffles, LDS across waves, one atomic per workgroup into
   // one of UMAX_SLOTS slots of the replica (pass C takes the max of the slots)
@@ -882,7 +967,7 @@ __global__ __launch_bounds__(WG) void k_free_energy(const StepArgs a, double* fe
     Mxxa.init(); Mxya.init(); Myya.init(); Mxxb.init(); Mxyb.init(); Myyb.init();
     Qcx.init(); Qcy.init(); Mxxc.init(); Mxyc.init(); Myyc.init();
     const float qci = R.q3d ? s_qc[p] : 0.0f;
-    each_listed(a.nl, a.ntot, g, min(a.ncnt[g], KMAX), 1, 0, [&](uint32_t e) {
+    each_listed(a.nl, a.ntot, g, min(a.ncnt[g], KMAX), [&](uint32_t e) {
       int j; float rx, ry, r2;
       if (!verlet_pair(e, L.shift, S - 1, s_off, oi, R.R2, j, rx, ry, r2)) return;
       const KW k = kernel_wf<KERN>(R, r2);
@@ -956,38 +1041,41 @@ void launch_free_energy(int T, int kern, const StepArgs& a, double* fe, hipStrea
 // ---------------------------------------------------------- neighbour export
 // The pairs the pair passes sum over, decoded from the Verlet list exactly as
 // they walk it: which = 0 keeps the entries that pass the predicate
-// (verlet_pair, the passes' own decision), which = 1 every entry of the list.
+// (neighbour(), pass D's own decision), which = 1 every entry of the list.
 // mode 0 counts the entries of each particle of replica rep_only into
 // cnt[id]; mode 1 writes the neighbours' ids from row_ptr[id] on.
 template <int T, int KERN>
 __global__ __launch_bounds__(WG) void k_list_export(const StepArgs a, int rep_only, int which, int mode, int* cnt,
                                                     const int64_t* row_ptr, int32_t* col, int64_t cap) {
-  __shared__ float2 s_shift[16];
   constexpr int MP = TileCfg<T, KERN>::MAXP;
   __shared__ float2 s_off[MP];
+  __shared__ float2 s_cell[MP];
   __shared__ int s_id[MP];
-  const TileRef t = tile_ref<T>(a, blockIdx.x);
+  const TileRef<T> t(a, blockIdx.x);
   if (t.rep != rep_only) return;
-  const RepDev R = a.reps[t.rep];
-  const int S = t.S, nin = t.nin;
-  stage_shift(s_shift, R);
+  ConstRep& R = rep_of_tile(a, t.rep);
+  const int nin = t.nin;
   struct In { float2 off; int id; };
   stage_tile<T, KERN>(t, [&](int g) { return In{a.off_cur[g], a.id[g]}; },
-                      [&](int j, int, const In& v) { s_off[j] = v.off; s_id[j] = v.id; });
+                      [&](int j, int e, const In& v) { s_off[j] = v.off; s_cell[j] = region_cell(e); s_id[j] = v.id; });
   __syncthreads();
-  for (int p = threadIdx.x; p < nin; p += WG) {
-    const int g = t.template global<T>(p);
+  Lane<T> l;
+  for (int p0 = 0; p0 < nin; p0 += WG) {
+    const int p = p0 + threadIdx.x;
+    l.p = p; l.lpp = 1; l.sub = 0; l.g = p < nin ? t.global(p) : -1;
+    if (l.g < 0) continue;
+    l.lists(a, t);
     const int idi = s_id[p];
     if (idi < 0 || idi >= R.n) { flag(a.flags, ERR_RANGE); continue; }
-    const float2 oi = s_off[p];
+    const float2 oi = s_off[p], ci = s_cell[p];
     int c = 0;
     const int64_t base = (mode == 1) ? row_ptr[idi] : 0;
-    each_listed(a.vl, a.ntot, g, min(a.vcnt[g], KMAX), 1, 0, [&](uint32_t e) {
-      int j; float rx, ry, r2;
-      const bool in = verlet_pair(e, s_shift, S - 1, s_off, oi, R.R2, j, rx, ry, r2);
+    walk_list<T, KERN, 1>(a, l, [&](auto, uint32_t at) {
+      float rx, ry, r2;
+      const bool in = neighbour<true>(oi, ci, lds_at(s_off, at), lds_at(s_cell, at), R.cs, R.R2, rx, ry, r2);
       if (which == 0 && !in) return;
       if (mode == 1) {
-        if (base + c < cap) col[base + c] = s_id[j];
+        if (base + c < cap) col[base + c] = s_id[at >> 3];
         else flag(a.flags, ERR_RANGE);
       }
       ++c;
@@ -1003,17 +1091,12 @@ template <int T, int COMP, int KERN>
 __global__ __launch_bounds__(WG) void k_pass_a(const StepArgs a) {
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_a<T, COMP, KERN>(a, w); __syncthreads(); }
 }
-// Gated on this step's requests (a rebin also renews the list): exactly one of
-// the two runs its tiles, the other exits at once.
+// One kernel whether or not this step renews the list (the requests; a rebin
+// renews it too).
 template <int T, int COMP, int KERN>
-__global__ __launch_bounds__(WG) void k_pass_a_build(const StepArgs a) {
-  if ((a.req_cur[0] | a.req_cur[1]) == 0u) return;
-  for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_a_build<T, COMP, KERN>(a, w); __syncthreads(); }
-}
-template <int T, int COMP, int KERN>
-__global__ __launch_bounds__(WG) void k_pass_a_walk(const StepArgs a) {
-  if ((a.req_cur[0] | a.req_cur[1]) != 0u) return;
-  for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_a_walk<T, COMP, KERN>(a, w); __syncthreads(); }
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_pass_a_step(const StepArgs a) {
+  const bool renew = (a.req_cur[0] | a.req_cur[1]) != 0u;
+  for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_a_step<T, COMP, KERN>(a, w, renew); __syncthreads(); }
 }
 
 // Occupancy targets (waves per SIMD) of the pair passes: more resident waves
@@ -1022,8 +1105,8 @@ __global__ __launch_bounds__(WG) void k_pass_a_walk(const StepArgs a) {
 template <int T, int COMP, int FORM, int EL, int KERN>
 struct Waves {
   static constexpr int B = ((T == 4 || KERN == 1) && (COMP == 0 || (COMP == 1 && FORM == 0))) ? 5 : 1;
-  static constexpr int C = 8;
-  static constexpr int D = ((T == 4 || KERN == 1) && EL == 0) ? 8 : 1;
+  static constexpr int C = 7;
+  static constexpr int D = ((T == 4 || KERN == 1) && EL == 0) ? 7 : 1;
 };
 
 template <int T, int COMP, int FORM, int EL, int KERN, int Q3>
@@ -1089,9 +1172,7 @@ static bool launch_comp(int pass, const PassCfg& c, const StepArgs& a, hipStream
 template <int T, int COMP, int KERN>
 static void launch_verlet(const StepArgs& a, hipStream_t s) {
   const int full = a.grid > 0 ? std::min(a.grid, a.nwork) : a.nwork;
-  // the build runs rarely: a persistent grid keeps the skipped launch short
-  hipLaunchKernelGGL((k_pass_a_build<T, COMP, KERN>), dim3(std::min(full, 2048)), dim3(WG), 0, s, a);
-  hipLaunchKernelGGL((k_pass_a_walk<T, COMP, KERN>), dim3(full), dim3(WG), 0, s, a);
+  hipLaunchKernelGGL((k_pass_a_step<T, COMP, KERN>), dim3(full), dim3(WG), 0, s, a);
 }
 
 template <int KERN>

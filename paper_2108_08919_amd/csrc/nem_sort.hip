@@ -107,13 +107,22 @@ __device__ void tile_header(const HdrArgs& h, int w) {
     S += v;
   }
   const bool over = S > h.maxp;
-  if (over && c == 0) atomicOr(h.flags, ERR_OVERFLOW);
   int* H = h.hdr + (size_t)w * h.ints;
-  if (c == 0) { H[0] = over ? 0 : nin; H[1] = over ? 0 : S; H[2] = ni; H[3] = nj; H[4] = rep; }
-  if (HDR_CELLS + 2 * c < h.ints) {
+  const int cells = HDR_ROWS + 2 * h.T;
+  if (c == 0) { H[0] = over ? 0 : nin; H[1] = over ? 0 : S; H[2] = ni | nj << 8 | (over ? 1 << 16 : 0); H[3] = rep; H[HDR_WORDS] = KMAX / 2; }
+  if (c < ni * nj && c % ni == 0) {   // first cell of an interior row
+    H[HDR_ROWS + 2 * (c / ni)] = s0 - start;
+    H[HDR_ROWS + 2 * (c / ni) + 1] = start;
+  }
+  if (c >= nj && c < h.T) {           // rows the tile does not have
+    H[HDR_ROWS + 2 * c] = 0;
+    H[HDR_ROWS + 2 * c + 1] = 0x7FFFFFFF;
+  }
+  if (cells + 2 * c < h.ints) {
     int2 e = make_int2(0, over ? 0 : S);
     if (c < nreg && !over) e = make_int2(s0, start | rx << 16 | ry << 20);
-    ((int2*)(H + HDR_CELLS))[c] = e;
+    H[cells + 2 * c] = e.x;
+    H[cells + 2 * c + 1] = e.y;
   }
   __syncthreads();
 }

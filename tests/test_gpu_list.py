@@ -1,0 +1,75 @@
+"""The Verlet list's two word formats (three slots or two a word), its distance
+classes and the list lengths at which a lane's words take a second batch: the
+neighbour sets against the oracle's predicate, and ten steps against the
+oracle's fields; a checkpoint of the older list format."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from gpu_common import check_increments, field_errors, gpu_run, random_state, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2108_08919_amd as P
+    P.lib()
+    yield
+
+
+# h = 1.15 dx: about 38 entries; 1.3: 44; 1.5: 67 (more than 16 words of three,
+# cells of 21 particles); tile 8 of the quintic holds two slots a word; sides
+# with a ragged last tile and the smallest box
+CASES = [(0, 1.15, 4, 1, 37), (0, 1.3, 8, 1, 37), (0, 1.5, 4, 1, 38), (0, 1.5, 8, 2, 33), (0, 1.5, 4, 4, 14),
+         (1, 1.3, 8, 1, 37), (1, 1.3, 4, 1, 22), (1, 1.5, 8, 1, 31), (1, 1.3, 8, 4, 9)]
+
+
+@pytest.mark.parametrize("kernel,h,tile,lpp,L", CASES)
+def test_list_against_oracle(kernel, h, tile, lpp, L):
+    import paper_2108_08919_amd as P
+    p = wl.Params(L=float(L), zeta=0.03, h=h, kernel=kernel)
+    s0 = random_state(L, 5, amp_u=2e-3)
+    print("list", kernel, h, tile, lpp, L, flush=True)
+    o, _ = run_oracle(p, s0, 10)
+    g, sim = gpu_run(p, s0, 10, {P.NEM_OPT_TILE: tile, P.NEM_OPT_LPP: lpp})
+    rp, col, cxy, oxy = sim.neighbor_list(0, 0, offsets=True)
+    nc = int(np.floor(L / (oracle.kappa(kernel) * h + p.skin)))
+    orp, ocol = oracle.neighbors_offsets(p, nc, cxy, oxy)
+    rows = lambda a, b: [sorted(b[a[i]:a[i + 1]]) for i in range(a.size - 1)]
+    assert rows(rp, col) == rows(orp, ocol)
+    e = field_errors(g, o, s0, L, 10)
+    for k in ("u", "Q", "rho", "pos"):
+        assert e[k] <= 1e-5, (k, e[k])
+    check_increments(e)
+    sim.check()
+    sim.close()
+
+
+def test_older_checkpoint_rebuilds_its_list():
+    """A version 1 checkpoint (the list in another format) is accepted: its list
+    is rebuilt by the next step, so the run continues to rounding."""
+    import paper_2108_08919_amd as P
+    L = 24
+    p = wl.Params(L=float(L), zeta=0.03)
+    s0 = random_state(L, 2, amp_u=2e-3)
+    _, a = gpu_run(p, s0, 4)
+    buf = a.save_raw()
+    a.step(6)
+    ref = a.get_state(0)
+    old = buf.copy()
+    old[8:16] = np.frombuffer(np.int64(1).tobytes(), dtype=np.uint8)
+    old[-8 * L * L - 4 * L * L - 4 * 48 * L * L:-12 * L * L] = 0xA5   # no list of this format
+    b = P.Sim([p], [L * L])
+    b.load_raw(old)
+    b.step(6)
+    b.check()
+    g = b.get_state(0)
+    e = field_errors(g, ref, s0, L)
+    assert e["u"] < 1e-6 and e["Q"] < 1e-6 and e["rho"] < 1e-6 and e["pos_abs_max"] < 1e-9
+    a.close()
+    b.close()
