@@ -23,15 +23,14 @@
 namespace nem {
 
 int mlp_nparam();
-int mlp_backward_waves(int64_t B);
+int mlp_backward_parts(int64_t B);
 void launch_mlp_forward(const float* P, const float* norm, const float* X, int64_t n, float* Y, unsigned* maxnorm,
                         hipStream_t s);
-void launch_mlp_backward(const float* P, const float* norm, const float* X, const float* T, const int64_t* idx,
-                         int64_t B, float* partial, float* lossp, int nwaves, hipStream_t s);
-void launch_mlp_reduce(const float* partial, int nw, float* grads, const float* lossp, float* loss, hipStream_t s);
-void launch_mlp_adam(float* P, const float* g, float* m, float* v, float lr, int t, hipStream_t s);
-void launch_mlp_batch(int64_t* idx, int64_t first, int64_t B, int64_t n, int64_t stride, int64_t offset,
-                      hipStream_t s);
+void launch_mlp_backward(const float* P, const float* norm, const float* X, const float* T, int64_t first, int64_t n,
+                         int64_t stride, int64_t offset, int64_t B, float* partial, int parts, hipStream_t s);
+void launch_mlp_reduce(const float* partial, int parts, float* grads, hipStream_t s);
+void launch_mlp_reduce_adam(const float* partial, int parts, float* grads, float* P, float* m, float* v, float lr,
+                            int t, hipStream_t s);
 void launch_mlp_stats(const float* X, const float* T, int64_t n, double* out, hipStream_t s);
 
 __device__ inline int rep_of(const RepDev* reps, int R, int k) {
@@ -273,15 +272,11 @@ struct nem_mlp {
   float* P = nullptr;      // FP32 master weights
   float* m = nullptr;      // Adam moments
   float* v = nullptr;
-  float* g = nullptr;      // gradient
+  float* g = nullptr;      // gradient, then the loss
   float* norm = nullptr;   // x mean[12], x std[12], y mean[5], y std[5] (device)
   float hnorm[34];
   float* partial = nullptr;
-  float* lossp = nullptr;
-  float* loss = nullptr;
-  int64_t* idx = nullptr;
-  int64_t idx_cap = 0;
-  int part_waves = 0;
+  int parts = 0;           // rows of partial
   double* stats = nullptr;
   int adam_t = 0;
   std::string err;
@@ -417,34 +412,13 @@ static int mlp_fail(nem_mlp* m, hipError_t e, const char* what) {
     if (e_ != hipSuccess) return mlp_fail(m, e_, #expr);  \
   } while (0)
 
-static int mlp_ensure_idx(nem_mlp* m, int64_t B) {
-  if (m->idx_cap >= B) return NEM_OK;
-  if (m->idx) hipFree(m->idx);
-  m->idx = nullptr;
-  MLPCHK(hipMalloc((void**)&m->idx, sizeof(int64_t) * B));
-  m->idx_cap = B;
-  return NEM_OK;
-}
-
-static int mlp_ensure_partial(nem_mlp* m, int nw) {
-  if (m->part_waves >= nw) return NEM_OK;
+static int mlp_ensure_partial(nem_mlp* m, int parts) {
+  if (m->parts >= parts) return NEM_OK;
   if (m->partial) hipFree(m->partial);
-  if (m->lossp) hipFree(m->lossp);
-  m->partial = nullptr; m->lossp = nullptr;
-  MLPCHK(hipMalloc((void**)&m->partial, sizeof(float) * (size_t)nw * mlp_nparam()));
-  MLPCHK(hipMalloc((void**)&m->lossp, sizeof(float) * nw));
-  m->part_waves = nw;
-  return NEM_OK;
-}
-
-// Gradient of the mean loss over the index map m->idx[0..B) into m->g.
-static int mlp_grad_batch(nem_mlp* m, const float* X, const float* T, int64_t B) {
-  const int nw = mlp_backward_waves(B);
-  int rc = mlp_ensure_partial(m, nw);
-  if (rc) return rc;
-  launch_mlp_backward(m->P, m->hnorm, X, T, m->idx, B, m->partial, m->lossp, nw, m->stream);
-  launch_mlp_reduce(m->partial, nw, m->g, m->lossp, m->loss, m->stream);
-  MLPCHK(hipGetLastError());
+  m->partial = nullptr;
+  m->parts = 0;
+  MLPCHK(hipMalloc((void**)&m->partial, sizeof(float) * (size_t)parts * (mlp_nparam() + 1)));
+  m->parts = parts;
   return NEM_OK;
 }
 
@@ -460,9 +434,8 @@ int nem_mlp_create(void* hip_stream, nem_mlp** out) {
   bool ok = hipMalloc((void**)&m->P, sizeof(float) * np) == hipSuccess &&
             hipMalloc((void**)&m->m, sizeof(float) * np) == hipSuccess &&
             hipMalloc((void**)&m->v, sizeof(float) * np) == hipSuccess &&
-            hipMalloc((void**)&m->g, sizeof(float) * np) == hipSuccess &&
+            hipMalloc((void**)&m->g, sizeof(float) * (np + 1)) == hipSuccess &&
             hipMalloc((void**)&m->norm, sizeof(float) * 34) == hipSuccess &&
-            hipMalloc((void**)&m->loss, sizeof(float)) == hipSuccess &&
             hipMalloc((void**)&m->stats, sizeof(double) * 34) == hipSuccess;
   if (!ok) { nem_mlp_destroy(m); return NEM_E_NOMEM; }
   for (int i = 0; i < 12; ++i) { m->hnorm[i] = 0.0f; m->hnorm[12 + i] = 1.0f; }
@@ -536,14 +509,15 @@ int nem_mlp_forward(nem_mlp* m, const float* X, int64_t n, float* Y) {
 
 int nem_mlp_grad(nem_mlp* m, const float* X, const float* T, int64_t n, float* grad, double* loss) {
   if (!m || !X || !T || !grad || n < 1) return NEM_E_INVAL;
-  int rc = mlp_ensure_idx(m, n);
+  const int parts = mlp_backward_parts(n);
+  int rc = mlp_ensure_partial(m, parts);
   if (rc) return rc;
-  launch_mlp_batch(m->idx, 0, n, n, 1, 0, m->stream);
-  rc = mlp_grad_batch(m, X, T, n);
-  if (rc) return rc;
+  launch_mlp_backward(m->P, m->hnorm, X, T, 0, n, 1, 0, n, m->partial, parts, m->stream);
+  launch_mlp_reduce(m->partial, parts, m->g, m->stream);
+  MLPCHK(hipGetLastError());
   float l = 0.f;
   MLPCHK(hipMemcpyAsync(grad, m->g, sizeof(float) * mlp_nparam(), hipMemcpyDeviceToHost, m->stream));
-  MLPCHK(hipMemcpyAsync(&l, m->loss, sizeof(float), hipMemcpyDeviceToHost, m->stream));
+  MLPCHK(hipMemcpyAsync(&l, m->g + mlp_nparam(), sizeof(float), hipMemcpyDeviceToHost, m->stream));
   MLPCHK(hipStreamSynchronize(m->stream));
   if (loss) *loss = l;
   return NEM_OK;
@@ -553,9 +527,10 @@ int nem_mlp_train(nem_mlp* m, const float* X, const float* T, int64_t n, int32_t
                   double* final_loss) {
   if (!m || !X || !T || n < 1 || epochs < 1 || batch < 32) return NEM_E_INVAL;
   const int64_t B = std::min<int64_t>(batch, n);
-  int rc = mlp_ensure_idx(m, B);
+  const int parts = mlp_backward_parts(B);
+  int rc = mlp_ensure_partial(m, parts);
   if (rc) return rc;
-  // per-epoch shuffle: idx = (k * stride + offset) mod n with stride coprime to n
+  // per-epoch shuffle: row = (k * stride + offset) mod n with stride coprime to n
   auto gcd = [](int64_t a, int64_t b) { while (b) { int64_t t = a % b; a = b; b = t; } return a; };
   int64_t stride = (int64_t)(0.6180339887 * (double)n) | 1;
   while (gcd(stride, n) != 1) stride += 2;
@@ -563,16 +538,14 @@ int nem_mlp_train(nem_mlp* m, const float* X, const float* T, int64_t n, int32_t
   for (int e = 0; e < epochs; ++e) {
     const int64_t offset = (int64_t)((uint64_t)(e + 1) * 2654435761ull % (uint64_t)n);
     for (int64_t first = 0; first + B <= n; first += B) {
-      launch_mlp_batch(m->idx, first, B, n, stride % n, offset, m->stream);
-      rc = mlp_grad_batch(m, X, T, B);
-      if (rc) return rc;
+      launch_mlp_backward(m->P, m->hnorm, X, T, first, n, stride % n, offset, B, m->partial, parts, m->stream);
       ++m->adam_t;
-      launch_mlp_adam(m->P, m->g, m->m, m->v, (float)lr, m->adam_t, m->stream);
+      launch_mlp_reduce_adam(m->partial, parts, m->g, m->P, m->m, m->v, (float)lr, m->adam_t, m->stream);
     }
     MLPCHK(hipGetLastError());
   }
   float l = 0.f;
-  MLPCHK(hipMemcpyAsync(&l, m->loss, sizeof(float), hipMemcpyDeviceToHost, m->stream));
+  MLPCHK(hipMemcpyAsync(&l, m->g + mlp_nparam(), sizeof(float), hipMemcpyDeviceToHost, m->stream));
   MLPCHK(hipStreamSynchronize(m->stream));
   last = l;
   if (final_loss) *final_loss = last;
@@ -583,7 +556,7 @@ void nem_mlp_destroy(nem_mlp* m) {
   if (!m) return;
   if (m->stream) hipStreamSynchronize(m->stream);
   for (void* p : {(void*)m->P, (void*)m->m, (void*)m->v, (void*)m->g, (void*)m->norm, (void*)m->partial,
-                  (void*)m->lossp, (void*)m->loss, (void*)m->idx, (void*)m->stats})
+                  (void*)m->stats})
     if (p) hipFree(p);
   delete m;
 }

@@ -3,8 +3,9 @@
 // A 12 -> 64 -> 64 -> 5 perceptron (tanh hidden layers, linear output) on
 // z-scored inputs and targets. Every product runs on v_mfma_f32_16x16x32_bf16
 // (BF16 operands, FP32 accumulation); master weights, Adam moments and all
-// element-wise work stay in FP32. A wave owns 32 samples (two 16-row tiles) at
-// a time and keeps its activations in LDS as BF16.
+// element-wise work stay in FP32. Inference keeps a wave's activations in
+// registers; training shares 32 samples between the waves of a workgroup, with
+// the activations in LDS as BF16.
 //
 // MFMA 16x16x32 operand layout (wave64, lane l, i = 0..7 / 0..3):
 //   A (16 x 32): A[l % 16][8 (l / 16) + i]      B (32 x 16): B[8 (l / 16) + i][l % 16]
@@ -21,41 +22,16 @@ namespace nem {
 
 typedef __bf16 bf16;
 typedef bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int NI = 12, NH = 64, NO = 5;
 constexpr int OFF_W1 = 0, OFF_B1 = OFF_W1 + NI * NH, OFF_W2 = OFF_B1 + NH, OFF_B2 = OFF_W2 + NH * NH;
 constexpr int OFF_W3 = OFF_B2 + NH, OFF_B3 = OFF_W3 + NH * NO, NPARAM = OFF_B3 + NO;
-constexpr int ROWS = 32;  // samples per wave iteration
+constexpr int ROWS = 32;  // samples per iteration of the backward kernel
 
 __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-// Fragment loads from row-major BF16 tiles in LDS.
-// A block rows r0.., cols k0..: lane -> S[r0 + l%16][k0 + 8(l/16) + i]
-__device__ __forceinline__ bf16x8 frag_a(const bf16* S, int ld, int r0, int k0, int l) {
-  const bf16* p = S + (r0 + (l & 15)) * ld + k0 + (l >> 4) * 8;
-  bf16x8 v;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) v[i] = p[i];
-  return v;
-}
-// A = S^T: A[m][k] = S[k][m]; lane -> S[k0 + 8(l/16) + i][m0 + l%16]
-__device__ __forceinline__ bf16x8 frag_at(const bf16* S, int ld, int m0, int k0, int l) {
-  const bf16* p = S + (k0 + (l >> 4) * 8) * ld + m0 + (l & 15);
-  bf16x8 v;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) v[i] = p[i * ld];
-  return v;
-}
-// B block rows k0.., cols n0..: lane -> S[k0 + 8(l/16) + i][n0 + l%16]
-__device__ __forceinline__ bf16x8 frag_b(const bf16* S, int ld, int k0, int n0, int l) {
-  return frag_at(S, ld, n0, k0, l);
-}
-// B = S^T: B[k][n] = S[n][k]; lane -> S[n0 + l%16][k0 + 8(l/16) + i]
-__device__ __forceinline__ bf16x8 frag_bt(const bf16* S, int ld, int k0, int n0, int l) {
-  return frag_a(S, ld, n0, k0, l);
 }
 
 struct MlpNorm { float xm[NI], xs[NI], xr[NI], ym[NO], ys[NO]; };  // xr = 1 / xs
@@ -66,99 +42,6 @@ struct MlpNorm { float xm[NI], xs[NI], xr[NI], ym[NO], ys[NO]; };  // xr = 1 / x
 __device__ __forceinline__ float fast_tanh(float x) {
   const float e = __builtin_amdgcn_exp2f(2.8853900817779268f * x);  // 2 log2(e) x
   return 1.0f - 2.0f * __builtin_amdgcn_rcpf(e + 1.0f);
-}
-
-// BF16 copies of the weights in LDS, zero-padded to MFMA shapes.
-struct WLds {
-  bf16 w1[32 * NH];   // rows 12..31 zero (K padding)
-  bf16 w2[NH * NH];
-  bf16 w3[NH * 16];   // cols 5..15 zero (N padding)
-  bf16 w3t[32 * NH];  // W3^T, rows 5..31 zero
-  float b1[NH], b2[NH], b3[16];
-};
-
-__device__ void load_weights(const float* P, WLds& W, bool need_t) {
-  for (int t = threadIdx.x; t < 32 * NH; t += blockDim.x) {
-    const int k = t / NH, n = t % NH;
-    W.w1[t] = (bf16)(k < NI ? P[OFF_W1 + k * NH + n] : 0.0f);
-  }
-  for (int t = threadIdx.x; t < NH * NH; t += blockDim.x) W.w2[t] = (bf16)P[OFF_W2 + t];
-  for (int t = threadIdx.x; t < NH * 16; t += blockDim.x) {
-    const int k = t / 16, n = t % 16;
-    W.w3[t] = (bf16)(n < NO ? P[OFF_W3 + k * NO + n] : 0.0f);
-  }
-  if (need_t)
-    for (int t = threadIdx.x; t < 32 * NH; t += blockDim.x) {
-      const int o = t / NH, k = t % NH;
-      W.w3t[t] = (bf16)(o < NO ? P[OFF_W3 + k * NO + o] : 0.0f);
-    }
-  for (int t = threadIdx.x; t < NH; t += blockDim.x) { W.b1[t] = P[OFF_B1 + t]; W.b2[t] = P[OFF_B2 + t]; }
-  for (int t = threadIdx.x; t < 16; t += blockDim.x) W.b3[t] = t < NO ? P[OFF_B3 + t] : 0.0f;
-}
-
-// Per-wave activation tiles (forward) and the extra tiles of the backward pass.
-struct ActF {
-  bf16 x[ROWS * 32];   // normalised inputs, cols 12..31 zero
-  bf16 h1[ROWS * NH];
-  bf16 h2[ROWS * NH];  // reused for dA1 in the backward pass
-};
-struct Act : ActF {
-  bf16 dy[ROWS * 32];  // dL/dy (cols 5..31 zero)
-  bf16 da2[ROWS * NH];
-};
-
-// Load 32 samples (rows base..base+31 of the index map) normalised into a.x.
-__device__ __forceinline__ void load_x(const float* X, int64_t n, int64_t base, const MlpNorm& nm,
-                                       const int64_t* idx, ActF& a, int l) {
-  for (int t = l; t < ROWS * 32; t += 64) {
-    const int r = t / 32, c = t % 32;
-    float v = 0.0f;
-    const int64_t s = base + r;
-    if (c < NI && s < n) {
-      const int64_t src = idx ? idx[s] : s;
-      v = (X[src * NI + c] - nm.xm[c]) * nm.xr[c];
-    }
-    a.x[t] = (bf16)v;
-  }
-}
-
-// Forward of 32 samples; y (FP32, normalised units) for lane l: rows
-// rt*16 + 4(l/16) + i, col l%16 < 5.
-__device__ __forceinline__ void forward32(const WLds& W, ActF& a, int l, f32x4 y[2]) {
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      acc = mfma(frag_a(a.x, 32, rt * 16, 0, l), frag_b(W.w1, NH, 0, nt * 16, l), acc);
-      const int col = nt * 16 + (l & 15);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a.h1[(rt * 16 + (l >> 4) * 4 + i) * NH + col] = (bf16)fast_tanh(acc[i] + W.b1[col]);
-    }
-  __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int kc = 0; kc < 2; ++kc)
-        acc = mfma(frag_a(a.h1, NH, rt * 16, kc * 32, l), frag_b(W.w2, NH, kc * 32, nt * 16, l), acc);
-      const int col = nt * 16 + (l & 15);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a.h2[(rt * 16 + (l >> 4) * 4 + i) * NH + col] = (bf16)fast_tanh(acc[i] + W.b2[col]);
-    }
-  __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kc = 0; kc < 2; ++kc)
-      acc = mfma(frag_a(a.h2, NH, rt * 16, kc * 32, l), frag_b(W.w3, 16, kc * 32, 0, l), acc);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] += W.b3[l & 15];
-    y[rt] = acc;
-  }
 }
 
 // ---------------------------------------------------------------- forward
@@ -348,186 +231,285 @@ __global__ __launch_bounds__(256) void k_mlp_forward(const float* __restrict__ P
 }
 
 // --------------------------------------------------------------- backward
-// Gradient of L = (1/2B) sum_s |y_s - t_s|^2 (normalised units) over the
-// minibatch idx[0..B) of (X, T). Each wave accumulates its samples into
-// registers and writes one partial gradient vector (partial[wave][NPARAM]) and
-// its partial loss (lossp[wave]).
-__global__ __launch_bounds__(128) void k_mlp_backward(const float* __restrict__ P, MlpNorm nm,
+// Minibatch rows: a deterministic shuffle of [0, n) per epoch, row(k) = (k *
+// stride + offset) mod n with stride coprime to n; k, stride, offset < n < 2^31.
+struct BatchRows { int64_t first, n, stride, offset; double inv_n; };
+__device__ __forceinline__ int64_t batch_row(const BatchRows& m, int64_t k) {
+  const int64_t v = (m.first + k) * m.stride + m.offset;
+  int64_t r = v - (int64_t)((double)v * m.inv_n) * m.n;   // the quotient is at most n: exact to within one
+  if (r < 0) r += m.n;
+  if (r >= m.n) r -= m.n;
+  return r;
+}
+
+// Gradient of L = (1/2B) sum_s |y_s - t_s|^2 (normalised units) over a
+// minibatch of (X, T): workgroup b takes the 32-sample blocks b, b + gridDim.x,
+// ..., accumulates their gradient in registers and writes one partial vector,
+// partial[b][0..NPARAM) and its partial loss at [NPARAM].
+//
+// A batch is a few hundred dependent matrix instructions and three dependent
+// global loads, so it is latency and nothing else. Wave w of four owns the
+// hidden units 16 w..16 w + 15 of both layers: its columns of every product and
+// its rows of the weight gradients. All its weight fragments are loaded into
+// registers at once, beside the samples; every activation is kept in LDS twice,
+// by sample and by unit, so that each operand of the forward, backward and
+// gradient products is one 16-byte read (rows are padded by 8 to spread them over
+// the banks). At 4096 samples a call takes 12.4 us; one wave per block with the
+// weights copied to LDS and operands read two bytes at a time took 38 us.
+constexpr int LDR = NH + 8;     // by sample: [sample][unit]
+constexpr int LDT = ROWS + 8;   // by unit: [unit][sample]
+struct Act {
+  bf16 xr[ROWS * LDT], xt[16 * LDT];   // inputs, units 12.. zero
+  bf16 h1r[ROWS * LDR], h1t[NH * LDT];
+  bf16 h2r[ROWS * LDR], h2t[NH * LDT];
+  bf16 dyr[ROWS * LDT], dyt[16 * LDT]; // dL/dy, outputs 5.. zero
+  bf16 d2r[ROWS * LDR], d2t[NH * LDT]; // dL/d(layer 2 before tanh)
+  bf16 d1t[NH * LDT];
+  int64_t row[ROWS];                   // source rows, -1 past the batch
+};
+
+__device__ __forceinline__ bf16x8 frag(const bf16* S, int ld, int r0, int k0, int l) {
+  return *reinterpret_cast<const bf16x8*>(S + (r0 + (l & 15)) * ld + k0 + (l >> 4) * 8);
+}
+// Store a D tile (rows = samples r0 + 4g + i, column = unit n0 + c) both ways.
+__device__ __forceinline__ void store_t(bf16* T, int r0, int n0, int l, bf16x4 v) {
+  *reinterpret_cast<bf16x4*>(T + (n0 + (l & 15)) * LDT + r0 + (l >> 4) * 4) = v;
+}
+__device__ __forceinline__ void store_r(bf16* S, int ld, int r0, int n0, int l, bf16x4 v) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) S[(r0 + (l >> 4) * 4 + i) * ld + n0 + (l & 15)] = v[i];
+}
+
+__global__ __launch_bounds__(256) void k_mlp_backward(const float* __restrict__ P, MlpNorm nm,
                                                       const float* __restrict__ X, const float* __restrict__ Tg,
-                                                      const int64_t* __restrict__ idx, int64_t B, float* partial,
-                                                      float* lossp) {
-  __shared__ WLds W;
-  __shared__ Act act[2];
-  load_weights(P, W, true);
-  __syncthreads();
-  const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int gw = blockIdx.x * 2 + wv;
-  Act& a = act[wv];
-  f32x4 g1[2][4], g2[4][4], g3[4];
-  float gb1[4] = {0, 0, 0, 0}, gb2[4] = {0, 0, 0, 0}, gb3 = 0.0f, ls = 0.0f;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    g3[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    g1[0][i] = g3[i]; g1[1][i] = g3[i];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) g2[i][j] = g3[i];
-  }
+                                                      BatchRows rows, int64_t B, float* partial) {
+  __shared__ __attribute__((aligned(16))) Act a;
+  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, g = l >> 4, c = l & 15;
+  const int n0 = 16 * wv, col = n0 + c;
+  // this thread's part of the staged inputs: two features of one sample
+  const int xrow = threadIdx.x >> 3, xc = 2 * (threadIdx.x & 7);
   const float invB = 1.0f / (float)B;
   const int64_t nblk = (B + ROWS - 1) / ROWS;
-  for (int64_t b = gw; b < nblk; b += (int64_t)gridDim.x * 2) {
-    const int64_t base = b * ROWS;
-    load_x(X, B, base, nm, idx, a, l);
-    __builtin_amdgcn_wave_barrier();
-    f32x4 y[2];
-    forward32(W, a, l, y);
-    // dL/dy = (y - t) / B in normalised units; padded columns and rows are zero
-    const int col = l & 15;
-    for (int t = l; t < ROWS * 32; t += 64) a.dy[t] = (bf16)0.0f;
-    __builtin_amdgcn_wave_barrier();
+  auto sample = [&](int64_t b) {
+    const int64_t s = b * ROWS + xrow;
+    return s < B ? batch_row(rows, s) : (int64_t)-1;
+  };
+  int64_t src = sample(blockIdx.x);
+  float x0 = 0.0f, x1 = 0.0f;
+  auto load_x = [&]() {
+    if (src >= 0 && xc < NI) { x0 = X[src * NI + xc]; x1 = X[src * NI + xc + 1]; }
+  };
+  load_x();
+  // B operands: lane holds K slots 8g..8g+7 of its column
+  bf16x8 w1, w2[2], w3[2], w3t, w2t[2];
+  {
+    float f1[8], f2[2][8], f3[2][8], f3t[8], f2t[2][8];
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+    for (int i = 0; i < 8; ++i) {
+      const int k = 8 * g + i;
+      f1[i] = k < NI ? P[OFF_W1 + k * NH + col] : 0.0f;
+      f3t[i] = k < NO ? P[OFF_W3 + col * NO + k] : 0.0f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = rt * 16 + (l >> 4) * 4 + i;
-        const int64_t s = base + r;
-        float d = 0.0f;
-        if (col < NO && s < B) {
-          const float t = (Tg[idx[s] * NO + col] - nm.ym[col]) / nm.ys[col];
-          d = y[rt][i] - t;
-          ls += d * d;
-        }
-        d *= invB;
-        gb3 += d;
-        a.dy[r * 32 + col] = (bf16)d;
+      for (int kc = 0; kc < 2; ++kc) {
+        f2[kc][i] = P[OFF_W2 + (kc * 32 + k) * NH + col];
+        f2t[kc][i] = P[OFF_W2 + col * NH + kc * 32 + k];
+        f3[kc][i] = wv == 0 && c < NO ? P[OFF_W3 + (kc * 32 + k) * NO + c] : 0.0f;
       }
-    __builtin_amdgcn_wave_barrier();
-    // gW3 (64 x 16) += H2^T dY
+    }
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) g3[mt] = mfma(frag_at(a.h2, NH, mt * 16, 0, l), frag_b(a.dy, 32, 0, 0, l), g3[mt]);
+    for (int i = 0; i < 8; ++i) {
+      w1[i] = (bf16)f1[i];
+      w3t[i] = (bf16)f3t[i];
+#pragma unroll
+      for (int kc = 0; kc < 2; ++kc) { w2[kc][i] = (bf16)f2[kc][i]; w2t[kc][i] = (bf16)f2t[kc][i]; w3[kc][i] = (bf16)f3[kc][i]; }
+    }
+  }
+  const float b1 = P[OFF_B1 + col], b2 = P[OFF_B2 + col], b3 = c < NO ? P[OFF_B3 + c] : 0.0f;
+  // columns that no sample writes: K padding of the inputs and of dL/dy
+  for (int t = threadIdx.x; t < ROWS * 16; t += 256) {
+    a.xr[(t >> 4) * LDT + 16 + (t & 15)] = (bf16)0.0f;
+    a.dyr[(t >> 4) * LDT + 16 + (t & 15)] = (bf16)0.0f;
+  }
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 g1 = zero, g2[4] = {zero, zero, zero, zero}, g3 = zero;
+  float gb1 = 0.0f, gb2 = 0.0f, gb3 = 0.0f, ls = 0.0f;
+  for (int64_t b = blockIdx.x; b < nblk; b += gridDim.x) {
+    {
+      const bool in = src >= 0 && xc < NI;
+      const bf16 v0 = (bf16)(in ? (x0 - nm.xm[xc]) * nm.xr[xc] : 0.0f);
+      const bf16 v1 = (bf16)(in ? (x1 - nm.xm[xc + 1]) * nm.xr[xc + 1] : 0.0f);
+      a.xr[xrow * LDT + xc] = v0; a.xr[xrow * LDT + xc + 1] = v1;
+      a.xt[xc * LDT + xrow] = v0; a.xt[(xc + 1) * LDT + xrow] = v1;
+      if (xc == 0) a.row[xrow] = src;
+    }
+    __syncthreads();
+    float tv[2][4];
+    if (wv == 0) {   // targets, in flight until the last layer
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int64_t s = a.row[rt * 16 + g * 4 + i];
+          tv[rt][i] = s >= 0 && c < NO ? Tg[s * NO + c] : 0.0f;
+        }
+    }
+    if (b + gridDim.x < nblk) { src = sample(b + gridDim.x); load_x(); }
+    float h1[2][4], h2[2][4];   // this lane's activations, as rounded
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+      const f32x4 acc = mfma(frag(a.xr, LDT, rt * 16, 0, l), w1, zero);
+      bf16x4 h;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { h[i] = (bf16)fast_tanh(acc[i] + b1); h1[rt][i] = (float)h[i]; }
+      store_r(a.h1r, LDR, rt * 16, n0, l, h);
+      store_t(a.h1t, rt * 16, n0, l, h);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+      f32x4 acc = zero;
+#pragma unroll
+      for (int kc = 0; kc < 2; ++kc) acc = mfma(frag(a.h1r, LDR, rt * 16, kc * 32, l), w2[kc], acc);
+      bf16x4 h;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { h[i] = (bf16)fast_tanh(acc[i] + b2); h2[rt][i] = (float)h[i]; }
+      store_r(a.h2r, LDR, rt * 16, n0, l, h);
+      store_t(a.h2t, rt * 16, n0, l, h);
+    }
+    __syncthreads();
+    if (wv == 0) {   // y, and dL/dy = (y - t) / B in normalised units
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) {
+        f32x4 y = zero;
+#pragma unroll
+        for (int kc = 0; kc < 2; ++kc) y = mfma(frag(a.h2r, LDR, rt * 16, kc * 32, l), w3[kc], y);
+        bf16x4 dv;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          y[i] += b3;
+          float d = 0.0f;
+          if (c < NO && a.row[rt * 16 + g * 4 + i] >= 0) {
+            const float t = (tv[rt][i] - nm.ym[c]) / nm.ys[c];
+            d = y[i] - t;
+            ls += d * d;
+          }
+          d *= invB;
+          gb3 += d;
+          dv[i] = (bf16)d;
+        }
+        store_r(a.dyr, LDT, rt * 16, 0, l, dv);
+        store_t(a.dyt, rt * 16, 0, l, dv);
+      }
+    }
+    __syncthreads();
+    // gW3 rows of this wave: H2^T dY
+    g3 = mfma(frag(a.h2t, LDT, n0, 0, l), frag(a.dyt, LDT, 0, 0, l), g3);
     // dA2 = (dY W3^T) * (1 - h2^2)
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+    for (int rt = 0; rt < 2; ++rt) {
+      const f32x4 acc = mfma(frag(a.dyr, LDT, rt * 16, 0, l), w3t, zero);
+      bf16x4 dv;
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        acc = mfma(frag_a(a.dy, 32, rt * 16, 0, l), frag_b(W.w3t, NH, 0, nt * 16, l), acc);
-        const int c = nt * 16 + (l & 15);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = rt * 16 + (l >> 4) * 4 + i;
-          const float h = (float)a.h2[r * NH + c];
-          const float d = acc[i] * (1.0f - h * h);
-          gb2[nt] += d;
-          a.da2[r * NH + c] = (bf16)d;
-        }
+      for (int i = 0; i < 4; ++i) {
+        const float d = acc[i] * (1.0f - h2[rt][i] * h2[rt][i]);
+        gb2 += d;
+        dv[i] = (bf16)d;
       }
-    __builtin_amdgcn_wave_barrier();
-    // gW2 (64 x 64) += H1^T dA2
+      store_r(a.d2r, LDR, rt * 16, n0, l, dv);
+      store_t(a.d2t, rt * 16, n0, l, dv);
+    }
+    __syncthreads();
+    // gW2 columns of this wave: H1^T dA2
+    const bf16x8 d2 = frag(a.d2t, LDT, n0, 0, l);
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int mt = 0; mt < 4; ++mt) g2[mt] = mfma(frag(a.h1t, LDT, mt * 16, 0, l), d2, g2[mt]);
+    // dA1 = (dA2 W2^T) * (1 - h1^2)
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt)
-        g2[mt][nt] = mfma(frag_at(a.h1, NH, mt * 16, 0, l), frag_b(a.da2, NH, 0, nt * 16, l), g2[mt][nt]);
-    // dA1 = (dA2 W2^T) * (1 - h1^2), stored over h2
+    for (int rt = 0; rt < 2; ++rt) {
+      f32x4 acc = zero;
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+      for (int kc = 0; kc < 2; ++kc) acc = mfma(frag(a.d2r, LDR, rt * 16, kc * 32, l), w2t[kc], acc);
+      bf16x4 dv;
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kc = 0; kc < 2; ++kc)
-          acc = mfma(frag_a(a.da2, NH, rt * 16, kc * 32, l), frag_bt(W.w2, NH, kc * 32, nt * 16, l), acc);
-        const int c = nt * 16 + (l & 15);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = rt * 16 + (l >> 4) * 4 + i;
-          const float h = (float)a.h1[r * NH + c];
-          const float d = acc[i] * (1.0f - h * h);
-          gb1[nt] += d;
-          a.h2[r * NH + c] = (bf16)d;
-        }
+      for (int i = 0; i < 4; ++i) {
+        const float d = acc[i] * (1.0f - h1[rt][i] * h1[rt][i]);
+        gb1 += d;
+        dv[i] = (bf16)d;
       }
-    __builtin_amdgcn_wave_barrier();
-    // gW1 (32 x 64, rows >= 12 unused) += X^T dA1
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt)
-        g1[mt][nt] = mfma(frag_at(a.x, 32, mt * 16, 0, l), frag_b(a.h2, NH, 0, nt * 16, l), g1[mt][nt]);
-    __builtin_amdgcn_wave_barrier();
+      store_t(a.d1t, rt * 16, n0, l, dv);
+    }
+    __syncthreads();
+    // gW1 columns of this wave: X^T dA1 (rows 12.. unused)
+    g1 = mfma(frag(a.xt, LDT, 0, 0, l), frag(a.d1t, LDT, n0, 0, l), g1);
+    if (b + gridDim.x < nblk) __syncthreads();
   }
-  // bias sums: lanes with the same l%16 hold the same column
+  // bias sums: lanes with the same l % 16 hold the same column
 #pragma unroll
   for (int o = 16; o < 64; o <<= 1) {
     gb3 += __shfl_xor(gb3, o, 64);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) { gb1[k] += __shfl_xor(gb1[k], o, 64); gb2[k] += __shfl_xor(gb2[k], o, 64); }
+    gb1 += __shfl_xor(gb1, o, 64);
+    gb2 += __shfl_xor(gb2, o, 64);
   }
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) ls += __shfl_xor(ls, o, 64);
-  float* out = partial + (size_t)gw * NPARAM;
-  const int col = l & 15;
+  float* out = partial + (size_t)blockIdx.x * (NPARAM + 1);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int rr = (l >> 4) * 4 + i;
+    const int k = 4 * g + i;
+    if (k < NI) out[OFF_W1 + k * NH + col] = g1[i];
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-      const int k = mt * 16 + rr;
-      if (k < NI)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) out[OFF_W1 + k * NH + nt * 16 + col] = g1[mt][nt][i];
-    }
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const int k = mt * 16 + rr;
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) out[OFF_W2 + k * NH + nt * 16 + col] = g2[mt][nt][i];
-      if (col < NO) out[OFF_W3 + k * NO + col] = g3[mt][i];
-    }
+    for (int mt = 0; mt < 4; ++mt) out[OFF_W2 + (mt * 16 + k) * NH + col] = g2[mt][i];
+    if (c < NO) out[OFF_W3 + (n0 + k) * NO + c] = g3[i];
   }
   if (l < 16) {
+    out[OFF_B1 + col] = gb1;
+    out[OFF_B2 + col] = gb2;
+    if (wv == 0 && l < NO) out[OFF_B3 + l] = gb3;
+  }
+  if (wv == 0 && l == 0) out[NPARAM] = 0.5f * ls * invB;
+}
+
+// grads[p] = sum over workgroups of partial[w][p] in their order, the loss at
+// [NPARAM] likewise; with ADAM, then one Adam step on the FP32 master weights.
+// The order is a chain of additions, but not of loads: a workgroup takes 64
+// parameters, its four waves load 32 rows each ahead of the first addition. At
+// 128 rows 4.4 us with the Adam step; a thread per parameter that loaded and added
+// in turn took 37 us and another launch of 5 us.
+struct AdamStep { float *P, *m, *v; float lr, b1, b2, eps, c1, c2; };
+constexpr int RED_ROWS = 32;   // rows a wave loads at a time
+template <bool ADAM>
+__global__ __launch_bounds__(256) void k_mlp_reduce(const float* __restrict__ partial, int nw, float* grads, AdamStep A) {
+  __shared__ float sh[4 * RED_ROWS][64];
+  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int p = blockIdx.x * 64 + l;
+  const bool in = p <= NPARAM;
+  float pp = 0.0f, pm = 0.0f, pv = 0.0f;
+  if (ADAM && wv == 0 && p < NPARAM) { pp = A.P[p]; pm = A.m[p]; pv = A.v[p]; }
+  float s = 0.0f;
+  for (int w0 = 0; w0 < nw; w0 += 4 * RED_ROWS) {
+    const int r0 = w0 + wv * RED_ROWS;
+    float v[RED_ROWS];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) { out[OFF_B1 + k * 16 + l] = gb1[k]; out[OFF_B2 + k * 16 + l] = gb2[k]; }
-    if (l < NO) out[OFF_B3 + l] = gb3;
+    for (int j = 0; j < RED_ROWS; ++j) v[j] = in && r0 + j < nw ? partial[(size_t)(r0 + j) * (NPARAM + 1) + p] : 0.0f;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < RED_ROWS; ++j) sh[wv * RED_ROWS + j][l] = v[j];
+    __syncthreads();
+    if (wv == 0) {
+      const int n = min(4 * RED_ROWS, nw - w0);
+#pragma unroll 8
+      for (int j = 0; j < n; ++j) s += sh[j][l];
+    }
   }
-  if (l == 0) lossp[gw] = 0.5f * ls * invB;
-}
-
-// grads[p] = sum over waves of partial[w][p], in wave order.
-__global__ void k_mlp_reduce(const float* partial, int nw, float* grads, const float* lossp, float* loss) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < NPARAM) {
-    float s = 0.0f;
-    for (int w = 0; w < nw; ++w) s += partial[(size_t)w * NPARAM + p];
-    grads[p] = s;
+  if (wv != 0 || !in) return;
+  grads[p] = s;
+  if (ADAM && p < NPARAM) {
+    const float mm = A.b1 * pm + (1.0f - A.b1) * s;
+    const float vv = A.b2 * pv + (1.0f - A.b2) * s * s;
+    A.m[p] = mm;
+    A.v[p] = vv;
+    A.P[p] = pp - A.lr * (mm / A.c1) / (sqrtf(vv / A.c2) + A.eps);
   }
-  if (p == 0 && loss) {
-    float s = 0.0f;
-    for (int w = 0; w < nw; ++w) s += lossp[w];
-    *loss = s;
-  }
-}
-
-// One Adam step on the FP32 master weights.
-__global__ void k_mlp_adam(float* P, const float* g, float* m, float* v, float lr, float b1, float b2, float eps,
-                           float c1, float c2) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= NPARAM) return;
-  const float gg = g[p];
-  const float mm = b1 * m[p] + (1.0f - b1) * gg;
-  const float vv = b2 * v[p] + (1.0f - b2) * gg * gg;
-  m[p] = mm;
-  v[p] = vv;
-  P[p] -= lr * (mm / c1) / (sqrtf(vv / c2) + eps);
-}
-
-// Minibatch indices: a deterministic shuffle of [0, n) per epoch,
-// idx[i] = (i * stride + offset) mod n with stride coprime to n.
-__global__ void k_mlp_batch(int64_t* idx, int64_t first, int64_t B, int64_t n, int64_t stride, int64_t offset) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= B) return;
-  const int64_t k = first + i;
-  idx[i] = (int64_t)(((uint64_t)k * (uint64_t)stride + (uint64_t)offset) % (uint64_t)n);  // n, stride < 2^31
 }
 
 // Column means and standard deviations of X (n x NI) and T (n x NO) in FP64,
@@ -554,7 +536,7 @@ __global__ __launch_bounds__(256) void k_mlp_stats(const float* X, const float* 
 
 // ---------------------------------------------------------------- launchers
 int mlp_nparam() { return NPARAM; }
-int mlp_backward_waves(int64_t B) {
+int mlp_backward_parts(int64_t B) {
   const int64_t nblk = (B + ROWS - 1) / ROWS;
   return (int)std::min<int64_t>(std::max<int64_t>(nblk, 2), 1024) / 2 * 2;
 }
@@ -572,27 +554,25 @@ void launch_mlp_forward(const float* P, const float* norm, const float* X, int64
     hipLaunchKernelGGL(k_mlp_forward<false>, dim3(grid), dim3(256), 0, s, P, nm, X, n, Y, maxnorm);
 }
 
-void launch_mlp_backward(const float* P, const float* norm, const float* X, const float* T, const int64_t* idx,
-                         int64_t B, float* partial, float* lossp, int nwaves, hipStream_t s) {
+void launch_mlp_backward(const float* P, const float* norm, const float* X, const float* T, int64_t first, int64_t n,
+                         int64_t stride, int64_t offset, int64_t B, float* partial, int parts, hipStream_t s) {
   MlpNorm nm;
   for (int i = 0; i < NI; ++i) { nm.xm[i] = norm[i]; nm.xs[i] = norm[NI + i]; nm.xr[i] = 1.0f / norm[NI + i]; }
   for (int i = 0; i < NO; ++i) { nm.ym[i] = norm[2 * NI + i]; nm.ys[i] = norm[2 * NI + NO + i]; }
-  hipLaunchKernelGGL(k_mlp_backward, dim3(nwaves / 2), dim3(128), 0, s, P, nm, X, T, idx, B, partial, lossp);
+  const BatchRows rows = {first, n, stride, offset, 1.0 / (double)n};
+  hipLaunchKernelGGL(k_mlp_backward, dim3(parts), dim3(256), 0, s, P, nm, X, T, rows, B, partial);
 }
 
-void launch_mlp_reduce(const float* partial, int nw, float* grads, const float* lossp, float* loss, hipStream_t s) {
-  hipLaunchKernelGGL(k_mlp_reduce, dim3((NPARAM + 255) / 256), dim3(256), 0, s, partial, nw, grads, lossp, loss);
+void launch_mlp_reduce(const float* partial, int parts, float* grads, hipStream_t s) {
+  hipLaunchKernelGGL(k_mlp_reduce<false>, dim3(NPARAM / 64 + 1), dim3(256), 0, s, partial, parts, grads, AdamStep{});
 }
 
-void launch_mlp_adam(float* P, const float* g, float* m, float* v, float lr, int t, hipStream_t s) {
+void launch_mlp_reduce_adam(const float* partial, int parts, float* grads, float* P, float* m, float* v, float lr,
+                            int t, hipStream_t s) {
   const float b1 = 0.9f, b2 = 0.999f;
   const float c1 = 1.0f - powf(b1, (float)t), c2 = 1.0f - powf(b2, (float)t);
-  hipLaunchKernelGGL(k_mlp_adam, dim3((NPARAM + 255) / 256), dim3(256), 0, s, P, g, m, v, lr, b1, b2, 1e-8f, c1, c2);
-}
-
-void launch_mlp_batch(int64_t* idx, int64_t first, int64_t B, int64_t n, int64_t stride, int64_t offset,
-                      hipStream_t s) {
-  hipLaunchKernelGGL(k_mlp_batch, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, s, idx, first, B, n, stride, offset);
+  hipLaunchKernelGGL(k_mlp_reduce<true>, dim3(NPARAM / 64 + 1), dim3(256), 0, s, partial, parts, grads,
+                     AdamStep{P, m, v, lr, b1, b2, 1e-8f, c1, c2});
 }
 
 void launch_mlp_stats(const float* X, const float* T, int64_t n, double* out, hipStream_t s) {

@@ -86,6 +86,49 @@ def test_gradient_matches_reference(n):
     m.close()
 
 
+# one sample, the edges of a 32-sample block, three blocks over two partial
+# sums, an odd count over several, and more blocks than the 1024 partial sums
+@pytest.mark.parametrize("n", [1, 31, 33, 96, 4133, 32 * 1024 + 37])
+def test_gradient_at_block_edges(n):
+    """The bound of test_gradient_matches_reference (BF16 operands: 2^-8 per rounding,
+    a handful of roundings on the way) at the edges of the kernel's blocks."""
+    m, Xt, Tt, pb, Xb, T = setup(n, 4)
+    g, loss = m.grad(Xt, Tt)
+    g_ref = ref.flatten(ref.grad(pb, Xb, T))
+    rel = np.linalg.norm(g - g_ref) / np.linalg.norm(g_ref)
+    print("grad", n, "rel", rel, flush=True)
+    assert rel <= 2e-2
+    assert loss == pytest.approx(ref.loss(pb, Xb, T), rel=2e-2)
+    m.close()
+
+
+@pytest.mark.parametrize("n,batch", [(32, 32), (1001, 333), (70001, 34000)])
+def test_one_batch_of_training_is_an_adam_step_on_its_rows(n, batch):
+    """The rows of a batch are (k stride + offset) mod n, and its update is one
+    Adam step on the gradient of those rows: the same kernels on the rows in
+    that order give the same gradient, so only the step's own rounding (a few
+    2^-24 of a weight and of lr) is between the two."""
+    import math
+    import torch
+    m, Xt, Tt, *_ = setup(n, 6)
+    w0 = m.get_weights()
+    stride = int(0.6180339887 * n) | 1
+    while math.gcd(stride, n) != 1:
+        stride += 2
+    off = 2654435761 % n
+    # the largest batch of which an epoch holds one is n // 2 + 1 rows
+    batch = max(batch, n // 2 + 1)
+    rows = torch.tensor([(k * (stride % n) + off) % n for k in range(batch)], device="cuda")
+    g, _ = m.grad(Xt[rows].contiguous(), Tt[rows].contiguous())
+    m.train(Xt, Tt, epochs=1, batch=batch, lr=1e-2)
+    w1 = m.get_weights().astype(np.float64)
+    g = g.astype(np.float64)
+    step = 1e-2 * g / (np.abs(g) + 1e-8)
+    print("train", n, batch, np.abs(w1 - (w0 - step)).max(), flush=True)
+    assert np.abs(w1 - (w0 - step)).max() <= 2.0 ** -22 * max(1.0, np.abs(w0).max()) + 1e-2 * 1e-4
+    m.close()
+
+
 def test_training_reduces_loss():
     import torch
     import paper_2108_08919_amd as P
