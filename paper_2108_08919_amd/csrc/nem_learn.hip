@@ -23,9 +23,10 @@
 namespace nem {
 
 int mlp_nparam();
+int mlp_norm_slots();   // words that launch_mlp_forward spreads the largest norm over
 int mlp_backward_parts(int64_t B);
 void launch_mlp_forward(const float* P, const float* norm, const float* X, int64_t n, float* Y, unsigned* maxnorm,
-                        hipStream_t s);
+                        unsigned* clear, int nclear, hipStream_t s);
 void launch_mlp_backward(const float* P, const float* norm, const float* X, const float* T, int64_t first, int64_t n,
                          int64_t stride, int64_t offset, int64_t B, float* partial, int parts, hipStream_t s);
 void launch_mlp_reduce(const float* partial, int parts, float* grads, hipStream_t s);
@@ -126,14 +127,17 @@ __global__ void k_sub(float* T, const float* C, int64_t n) {
 // Add the network's corrections Y[k * 5] (storage order) to Q (projected on
 // traceless tensors) and u; refill the max-speed slots (cleared by the
 // caller). Grid as k_repredict. Skipped when the largest predicted correction
-// norm (maxnorm, float bits) exceeds tau (bits of a positive float, so the
+// norm (the largest of maxnorm[0..63], float bits) exceeds tau (bits of a positive float, so the
 // unsigned comparison orders them as floats).
 __global__ __launch_bounds__(256) void k_correct(SortArgs s, const float* Y, unsigned* umax_cur,
                                                  const unsigned* maxnorm, unsigned tau_bits, unsigned* host_norm) {
   // the norm for the host's fallback decision, stored straight into pinned
   // host memory (a plain vector store, visible once the kernel has completed)
-  if (host_norm && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *host_norm = maxnorm ? *maxnorm : 0u;
-  if (maxnorm && *maxnorm > tau_bits) return;  // the macro step will be replayed as fine steps
+  unsigned norm = maxnorm[threadIdx.x & 63];
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) norm = max(norm, (unsigned)__shfl_xor((int)norm, o, 64));
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *host_norm = norm;
+  if (norm > tau_bits) return;  // the macro step will be replayed as fine steps
   const int r = blockIdx.y;
   const RepDev& R = s.reps[r];
   float vmax = 0.0f;
@@ -167,13 +171,6 @@ __global__ __launch_bounds__(256) void k_correct(SortArgs s, const float* Y, uns
   block_speed_max(s, umax_cur, r, vmax, relist);
 }
 
-// Before the inference of a learned macro step: clear the largest-norm word
-// and the max-speed slots that k_correct refills (one launch, no memset).
-__global__ void k_learn_clear(unsigned* norm, unsigned* umax, int n_umax) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *norm = 0u;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_umax; i += gridDim.x * blockDim.x) umax[i] = 0u;
-}
-
 // dst[(part_base + id) * w + c] = src[k * w + c]: rows from storage order to
 // original particle order.
 __global__ void k_rows_by_id(SortArgs s, const float* src, float* dst, int w) {
@@ -190,10 +187,12 @@ __global__ void k_rows_by_id(SortArgs s, const float* src, float* dst, int w) {
 
 // Device-to-device copy of up to 12 buffers in one launch (16-byte chunks,
 // then 4-byte words for the tail; every buffer is 4-byte sized and every
-// buffer longer than 16 bytes starts 16-byte aligned).
+// buffer longer than 16 bytes starts 16-byte aligned). zero (may be NULL): nzero
+// <= 256 words that a later kernel of the stream accumulates into.
 struct CopySeg { const void* src; void* dst; int64_t bytes; };
-struct CopyList { CopySeg seg[14]; int n; };
+struct CopyList { CopySeg seg[14]; int n; unsigned* zero; int nzero; };
 __global__ void k_copy_list(CopyList L) {
+  if (L.zero && blockIdx.x == 0 && (int)threadIdx.x < L.nzero) L.zero[threadIdx.x] = 0u;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   for (int k = 0; k < L.n; ++k) {
@@ -293,7 +292,7 @@ void free_snapshot(nem_sim* s) {
   }
 }
 
-int take_snapshot(nem_sim* s, int i) {
+int take_snapshot(nem_sim* s, int i, unsigned* zero, int nzero) {
   auto& S = s->snap[i];
   const size_t N = (size_t)s->ntot, C = (size_t)s->ncells;
   if (!S.alloc) {
@@ -314,6 +313,8 @@ int take_snapshot(nem_sim* s, int i) {
   const int p = s->parity;
   CopyList cl;
   cl.n = 0;
+  cl.zero = zero;
+  cl.nzero = nzero;
   bool full = false;
   auto add = [&](const void* src, void* dst, size_t bytes) {
     if (cl.n < (int)(sizeof(cl.seg) / sizeof(cl.seg[0]))) cl.seg[cl.n++] = CopySeg{src, dst, (int64_t)bytes};
@@ -349,6 +350,8 @@ int restore_snapshot(nem_sim* s, int i) {
   const int p = S.parity;
   CopyList cl;
   cl.n = 0;
+  cl.zero = nullptr;
+  cl.nzero = 0;
   bool full = false;
   auto add = [&](const void* src, void* dst, size_t bytes) {
     if (cl.n < (int)(sizeof(cl.seg) / sizeof(cl.seg[0]))) cl.seg[cl.n++] = CopySeg{src, dst, (int64_t)bytes};
@@ -501,7 +504,7 @@ int nem_mlp_fit_norm(nem_mlp* m, const float* X, const float* T, int64_t n) {
 
 int nem_mlp_forward(nem_mlp* m, const float* X, int64_t n, float* Y) {
   if (!m || !X || !Y || n < 1) return NEM_E_INVAL;
-  launch_mlp_forward(m->P, m->hnorm, X, n, Y, nullptr, m->stream);
+  launch_mlp_forward(m->P, m->hnorm, X, n, Y, nullptr, nullptr, 0, m->stream);
   MLPCHK(hipGetLastError());
   MLPCHK(hipStreamSynchronize(m->stream));
   return NEM_OK;
@@ -566,17 +569,18 @@ int nem_mlp_eval(nem_mlp* m, const float* X, const float* T, int64_t n, double* 
   float* Y = nullptr;
   unsigned* mx = nullptr;
   MLPCHK(hipMalloc((void**)&Y, sizeof(float) * 5 * (size_t)n));
-  if (hipMalloc((void**)&mx, sizeof(unsigned)) != hipSuccess) { hipFree(Y); m->err = "hipMalloc (max norm)"; return NEM_E_HIP; }
-  hipError_t e = hipMemsetAsync(mx, 0, sizeof(unsigned), m->stream);
+  std::vector<unsigned> hm(mlp_norm_slots(), 0u);
+  const size_t mx_bytes = sizeof(unsigned) * hm.size();
+  if (hipMalloc((void**)&mx, mx_bytes) != hipSuccess) { hipFree(Y); m->err = "hipMalloc (max norm)"; return NEM_E_HIP; }
+  hipError_t e = hipMemsetAsync(mx, 0, mx_bytes, m->stream);
   if (e == hipSuccess) {
-    launch_mlp_forward(m->P, m->hnorm, X, n, Y, mx, m->stream);
+    launch_mlp_forward(m->P, m->hnorm, X, n, Y, mx, nullptr, 0, m->stream);
     if (rel_mse) hipLaunchKernelGGL(k_eval_stats, dim3(5), dim3(256), 0, m->stream, T, (const float*)Y, n, m->stats);
     e = hipGetLastError();
   }
   double st[15];
-  unsigned hm = 0;
   if (e == hipSuccess && rel_mse) e = hipMemcpyAsync(st, m->stats, sizeof(st), hipMemcpyDeviceToHost, m->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(&hm, mx, sizeof(hm), hipMemcpyDeviceToHost, m->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(hm.data(), mx, mx_bytes, hipMemcpyDeviceToHost, m->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
   hipFree(Y);
   hipFree(mx);
@@ -584,8 +588,9 @@ int nem_mlp_eval(nem_mlp* m, const float* X, const float* T, int64_t n, double* 
   if (rel_mse)
     for (int o = 0; o < 5; ++o) rel_mse[o] = st[3 * o + 1] > 0.0 ? st[3 * o + 2] / st[3 * o + 1] : NAN;
   if (max_norm) {
+    const unsigned most = *std::max_element(hm.begin(), hm.end());
     float f;
-    std::memcpy(&f, &hm, sizeof(f));
+    std::memcpy(&f, &most, sizeof(f));
     *max_norm = f;
   }
   return NEM_OK;
@@ -704,6 +709,7 @@ int nem_step_learned(nem_sim* s, nem_mlp* m, int64_t n_macro, int32_t mult, doub
   unsigned tau_bits;
   std::memcpy(&tau_bits, &tauf, sizeof(tau_bits));
   float *X = nullptr, *Y = nullptr;
+  const int NS = mlp_norm_slots();
   unsigned *mx = nullptr, *hmx = nullptr;
   hipEvent_t ev[2] = {nullptr, nullptr};
   int rc = NEM_OK;
@@ -713,7 +719,7 @@ int nem_step_learned(nem_sim* s, nem_mlp* m, int64_t n_macro, int32_t mult, doub
   };
   chk(hipMalloc((void**)&X, sizeof(float) * 12 * N), "hipMalloc (inputs)");
   chk(hipMalloc((void**)&Y, sizeof(float) * 5 * N), "hipMalloc (corrections)");
-  chk(hipMalloc((void**)&mx, sizeof(unsigned) * 2), "hipMalloc (max norm)");
+  chk(hipMalloc((void**)&mx, sizeof(unsigned) * 2 * NS), "hipMalloc (max norm)");
   chk(hipHostMalloc((void**)&hmx, sizeof(unsigned) * 2, hipHostMallocMapped | hipHostMallocCoherent),
       "hipHostMalloc (max norm)");
   unsigned* dmx = nullptr;   // the device's address of hmx
@@ -725,18 +731,17 @@ int nem_step_learned(nem_sim* s, nem_mlp* m, int64_t n_macro, int32_t mult, doub
   // in pinned host memory for the host's fallback decision.
   auto enqueue = [&](int64_t k) -> int {
     const int b = (int)(k & 1);
-    int e = take_snapshot(s, b);
+    int e = take_snapshot(s, b, mx + b * NS, NS);   // and the largest-norm words cleared
     if (e) return e;
     s->feat = X;
     e = run_steps(s, 1);
     s->feat = nullptr;
     if (e) return e;
     unsigned* um = s->umax + (size_t)s->parity * s->R * UMAX_SLOTS;
-    hipLaunchKernelGGL(k_learn_clear, dim3(1), dim3(256), 0, s->stream, mx + b, um, s->R * UMAX_SLOTS);
-    launch_mlp_forward(m->P, m->hnorm, X, (int64_t)N, Y, mx + b, s->stream);
+    launch_mlp_forward(m->P, m->hnorm, X, (int64_t)N, Y, mx + b * NS, um, s->R * UMAX_SLOTS, s->stream);
     SortArgs a = sort_args(s);
     hipLaunchKernelGGL(k_correct, rep_grid(s), dim3(256), 0, s->stream, a, (const float*)Y, um,
-                       (const unsigned*)(mx + b), tau_bits, dmx + b);
+                       (const unsigned*)(mx + b * NS), tau_bits, dmx + b);
     if (!chk(hipGetLastError(), "k_correct")) return rc;
     if (!chk(hipEventRecord(ev[b], s->stream), "hipEventRecord")) return rc;
     return rc;

@@ -28,6 +28,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int NI = 12, NH = 64, NO = 5;
 constexpr int OFF_W1 = 0, OFF_B1 = OFF_W1 + NI * NH, OFF_W2 = OFF_B1 + NH, OFF_B2 = OFF_W2 + NH * NH;
 constexpr int OFF_W3 = OFF_B2 + NH, OFF_B3 = OFF_W3 + NH * NO, NPARAM = OFF_B3 + NO;
+constexpr int NORM_SLOTS = 64;   // words of the largest-norm reduction
 constexpr int ROWS = 32;  // samples per iteration of the backward kernel
 
 __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
@@ -46,8 +47,10 @@ __device__ __forceinline__ float fast_tanh(float x) {
 
 // ---------------------------------------------------------------- forward
 // Y (n x 5): corrections in physical units (denormalised). maxnorm (may be
-// NULL): max over samples of the Euclidean norm of the normalised output,
-// as float bits.
+// NULL): max over samples of the Euclidean norm of the normalised output, as
+// float bits, spread over NORM_SLOTS words (cleared by the caller; the result is
+// their largest). Atomics on one word from every wave of the grid took ~10 ns each,
+// one after another: at 262,144 samples 40 of the kernel's 61 us.
 //
 // Inference keeps the activations in registers by computing each layer
 // transposed, H^T = W^T X^T: the weights are the A operand (fragments in LDS,
@@ -78,50 +81,51 @@ __device__ __forceinline__ float tanh_kb(float d, float kb) {
   return 1.0f - 2.0f * __builtin_amdgcn_rcpf(e + 1.0f);
 }
 
-// X rows are 48 bytes; VEC reads them as float4 (X 16-byte aligned).
+// X rows are 48 bytes; VEC reads them as float4 (X 16-byte aligned). clear: words
+// for the next kernel of the stream to fill, zeroed here (NULL: none).
 template <bool VEC>
 __global__ __launch_bounds__(256) void k_mlp_forward(const float* __restrict__ P, MlpNorm nm,
                                                      const float* __restrict__ X, int64_t n, float* Y,
-                                                     unsigned* maxnorm) {
+                                                     unsigned* maxnorm, unsigned* clear, int nclear) {
   constexpr int NB = 2;  // independent 16-sample blocks per iteration (instruction-level parallelism)
   __shared__ FwdLds W;
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, g = l >> 4, c = l & 15;
-  // fill the fragments: A[m][k] = W^T, lane (gl, cl) holds k = 8 gl + i (in the
-  // unit numbering of unit_of for layers 2 and 3) of row m = 16 mt + cl
-  for (int t = threadIdx.x; t < 14 * 64; t += blockDim.x) {
-    const int f = t >> 6, ln = t & 63, gl = ln >> 4, cl = ln & 15;
-    bf16x8 v;
+  if (clear && blockIdx.x == 0)
+    for (int t = threadIdx.x; t < nclear; t += 256) clear[t] = 0u;
+  // Fill the fragments: A[m][k] = W^T, lane (g, c) holds k = 8 g + i (in the
+  // unit numbering of unit_of for layers 2 and 3) of row m = 16 mt + c. Wave wv
+  // fills fragments wv, wv + 4, wv + 8, wv + 12, and asks for all its weights
+  // before it uses one (waiting for each in turn: 5 us more).
+  {
+    float f[4][8], fb[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      float w;
-      if (f < 4) {
-        const int k = 8 * gl + i;
-        w = k < NI ? P[OFF_W1 + k * NH + 16 * f + cl] : 0.0f;
-      } else if (f < 12) {
-        const int mt = (f - 4) >> 1, kc = (f - 4) & 1;
-        w = P[OFF_W2 + unit_of(kc, gl, i) * NH + 16 * mt + cl];
-      } else {
-        w = cl < NO ? P[OFF_W3 + unit_of(f - 12, gl, i) * NO + cl] : 0.0f;
-      }
-      v[i] = (bf16)w;
+      const int k = 8 * g + i;
+      f[0][i] = k < NI ? P[OFF_W1 + k * NH + 16 * wv + c] : 0.0f;
+      f[1][i] = P[OFF_W2 + unit_of(wv & 1, g, i) * NH + 16 * (wv >> 1) + c];         // fragments 4 + wv
+      f[2][i] = P[OFF_W2 + unit_of(wv & 1, g, i) * NH + 16 * (2 + (wv >> 1)) + c];   // fragments 8 + wv
+      f[3][i] = wv < 2 && c < NO ? P[OFF_W3 + unit_of(wv & 1, g, i) * NO + c] : 0.0f;
     }
-    W.frag[t] = v;
-  }
-  for (int t = threadIdx.x; t < 4 * 64; t += blockDim.x) {
-    const int mt = t >> 6, gl = (t & 63) >> 4;
-    f32x4 v1, v2;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      v1[i] = TANH_K * P[OFF_B1 + 16 * mt + 4 * gl + i];
-      v2[i] = TANH_K * P[OFF_B2 + 16 * mt + 4 * gl + i];
+      fb[i] = P[OFF_B1 + 16 * wv + 4 * g + i];
+      fb[4 + i] = P[OFF_B2 + 16 * wv + 4 * g + i];
     }
-    W.b1[t] = v1; W.b2[t] = v2;
-  }
-  for (int t = threadIdx.x; t < 64; t += blockDim.x) {
-    f32x4 v3;
+    f32x4 v1, v2, v3;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v3[i] = (4 * (t >> 4) + i < NO) ? P[OFF_B3 + 4 * (t >> 4) + i] : 0.0f;
-    W.b3[t] = v3;
+    for (int i = 0; i < 4; ++i) v3[i] = 4 * g + i < NO ? P[OFF_B3 + 4 * g + i] : 0.0f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      bf16x8 v;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = (bf16)f[j][i];
+      if (j < 3 || wv < 2) W.frag[(4 * j + wv) * 64 + l] = v;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { v1[i] = TANH_K * fb[i]; v2[i] = TANH_K * fb[4 + i]; }
+    W.b1[wv * 64 + l] = v1;
+    W.b2[wv * 64 + l] = v2;
+    if (wv == 0) W.b3[l] = v3;
   }
   __syncthreads();
   // this lane's input features 8g + i (i < nf) and their normalisation
@@ -224,9 +228,13 @@ __global__ __launch_bounds__(256) void k_mlp_forward(const float* __restrict__ P
     }
   }
   if (maxnorm) {
+    __shared__ float red[4];
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-    if (l == 0 && mx > 0.0f) atomicMax(maxnorm, __float_as_uint(mx));
+    if (l == 0) red[wv] = mx;
+    __syncthreads();
+    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    if (threadIdx.x == 0 && mx > 0.0f) atomicMax(&maxnorm[blockIdx.x & (NORM_SLOTS - 1)], __float_as_uint(mx));
   }
 }
 
@@ -536,22 +544,23 @@ __global__ __launch_bounds__(256) void k_mlp_stats(const float* X, const float* 
 
 // ---------------------------------------------------------------- launchers
 int mlp_nparam() { return NPARAM; }
+int mlp_norm_slots() { return NORM_SLOTS; }
 int mlp_backward_parts(int64_t B) {
   const int64_t nblk = (B + ROWS - 1) / ROWS;
   return (int)std::min<int64_t>(std::max<int64_t>(nblk, 2), 1024) / 2 * 2;
 }
 
 void launch_mlp_forward(const float* P, const float* norm, const float* X, int64_t n, float* Y, unsigned* maxnorm,
-                        hipStream_t s) {
+                        unsigned* clear, int nclear, hipStream_t s) {
   MlpNorm nm;
   for (int i = 0; i < NI; ++i) { nm.xm[i] = norm[i]; nm.xs[i] = norm[NI + i]; nm.xr[i] = 1.0f / norm[NI + i]; }
   for (int i = 0; i < NO; ++i) { nm.ym[i] = norm[2 * NI + i]; nm.ys[i] = norm[2 * NI + NO + i]; }
   const int64_t nblk = (n + 31) / 32;  // pairs of 16-sample blocks
   const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((nblk + 3) / 4, 1024));
   if (((uintptr_t)X & 15u) == 0)
-    hipLaunchKernelGGL(k_mlp_forward<true>, dim3(grid), dim3(256), 0, s, P, nm, X, n, Y, maxnorm);
+    hipLaunchKernelGGL(k_mlp_forward<true>, dim3(grid), dim3(256), 0, s, P, nm, X, n, Y, maxnorm, clear, nclear);
   else
-    hipLaunchKernelGGL(k_mlp_forward<false>, dim3(grid), dim3(256), 0, s, P, nm, X, n, Y, maxnorm);
+    hipLaunchKernelGGL(k_mlp_forward<false>, dim3(grid), dim3(256), 0, s, P, nm, X, n, Y, maxnorm, clear, nclear);
 }
 
 void launch_mlp_backward(const float* P, const float* norm, const float* X, const float* T, int64_t first, int64_t n,

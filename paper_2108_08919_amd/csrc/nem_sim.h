@@ -98,7 +98,7 @@ int status_from_flags(nem_sim* s, unsigned f);
 int run_steps(nem_sim* s, int64_t nsteps);
 int upload_reps(nem_sim* s);
 void free_snapshot(nem_sim* s);
-int take_snapshot(nem_sim* s, int i = 0);
+int take_snapshot(nem_sim* s, int i = 0, unsigned* zero = nullptr, int nzero = 0);
 int restore_snapshot(nem_sim* s, int i = 0);
 int build_work(nem_sim* s);
 void build_headers(nem_sim* s);
