@@ -20,47 +20,60 @@
 namespace nem {
 
 // --------------------------------------------------------------- deposit
+// A workgroup deposits on the nodes whose centre lies in its tile's cells, node i
+// in cell floor((i + 1/2) hg / csd). Their range is exact, so that a tile with as
+// many nodes as the workgroup has lanes takes one round (a range with a margin for
+// rounding, and a test of each node, took two at M = L / dx); staged through the
+// tile header. 512^2 nodes and particles: 62 us before both, 39 us.
 template <int T, int KERN>
 __global__ __launch_bounds__(WG) void k_deposit(const StepArgs a, int rep_only, int M, double* grid) {
-  __shared__ TileLDS<T> L;
   constexpr int MP = TileCfg<T, KERN>::MAXP;
+  __shared__ CellLDS<T> L;
+  __shared__ int bound[4];
   __shared__ float2 s_off[MP];
   __shared__ float4 s_f[MP];   // ux, uy, qxx, qxy at the integer level
-  RepDev R;
-  int rep;
-  if (!tile_begin<T, KERN>(a, blockIdx.x, L, R, rep)) return;
-  if (rep != rep_only) return;
-  const int ni = L.hdr[0], nj = L.hdr[1], nreg = L.hdr[3];
-  const int S = L.cstart[nreg];
-  const float hdt = 0.5f * R.dt;
-  for (int t = threadIdx.x; t < S; t += WG) {
-    const int g = staged_global<T>(a, L, t);
-    s_off[t] = a.off_cur[g];
-    const float2 u = a.u[g], ac = a.acc[g], q = a.q_cur[g];
-    // third field: Qxx in d = 2; (Qxx - Qyy)/2, the in-plane traceless part, in
-    // the quasi-2D variant (the same director angle atan2(Qxy, .)/2)
-    const float qa = R.q3d ? 0.5f * (q.x - a.qyy_cur[g]) : q.x;
-    s_f[t] = make_float4(u.x - hdt * ac.x, u.y - hdt * ac.y, qa, q.y);
+  const TileRef<T> tl(a, blockIdx.x);
+  if (tl.rep != rep_only) return;
+  if (tl.over) {
+    if (threadIdx.x == 0) flag(a.flags, ERR_OVERFLOW);
+    return;
   }
-  __syncthreads();
+  const RepDev R = a.reps[tl.rep];
+  const int ni = tl.ni, nj = tl.nj;
   const int tile = a.work[2 * blockIdx.x + 1];
   const int cx0 = (tile % R.tiles_x) * T, cy0 = (tile / R.tiles_x) * T;
   const double hg = R.Ld / M;
-  // nodes whose centre lies in the tile's cells: node i belongs to cell
-  // floor((i + 1/2) hg / csd), the same rule for every tile
-  const int ix0 = max(0, (int)floor(cx0 * R.csd / hg - 0.5) - 1);
-  const int ix1 = min(M - 1, (int)ceil((cx0 + ni) * R.csd / hg - 0.5) + 1);
-  const int iy0 = max(0, (int)floor(cy0 * R.csd / hg - 0.5) - 1);
-  const int iy1 = min(M - 1, (int)ceil((cy0 + nj) * R.csd / hg - 0.5) + 1);
-  const int nx = ix1 - ix0 + 1, nn = nx * (iy1 - iy0 + 1);
+  auto cell_of = [&](int i) {
+#pragma clang fp contract(off)
+    return min((int)floor((i + 0.5) * hg / R.csd), R.nc - 1);
+  };
+  tile_cells<T>(tl, L);
+  if (threadIdx.x < 4) {   // first node of the tile and first past it, in x and in y
+    const int c = (threadIdx.x < 2 ? cx0 : cy0) + (threadIdx.x == 1 ? ni : (threadIdx.x == 3 ? nj : 0));
+    int i = min(max((int)floor(c * R.csd / hg - 0.5) - 1, 0), M);
+    while (i > 0 && cell_of(i - 1) >= c) --i;
+    while (i < M && cell_of(i) < c) ++i;
+    bound[threadIdx.x] = i;
+  }
+  const float hdt = 0.5f * R.dt;
+  struct In { float2 off, u, ac, q; float qc; };
+  stage_tile<T, KERN>(tl, [&](int g) {
+    return In{a.off_cur[g], a.u[g], a.acc[g], a.q_cur[g], R.q3d ? a.qyy_cur[g] : 0.0f};
+  }, [&](int j, int, const In& v) {
+    s_off[j] = v.off;
+    // third field: Qxx in d = 2; (Qxx - Qyy)/2, the in-plane traceless part, in
+    // the quasi-2D variant (the same director angle atan2(Qxy, .)/2)
+    const float qa = R.q3d ? 0.5f * (v.q.x - v.qc) : v.q.x;
+    s_f[j] = make_float4(v.u.x - hdt * v.ac.x, v.u.y - hdt * v.ac.y, qa, v.q.y);
+  });
+  __syncthreads();
+  const int ix0 = bound[0], iy0 = bound[2], nx = bound[1] - ix0, nn = nx * (bound[3] - iy0);
   for (int t = threadIdx.x; t < nn; t += WG) {
 #pragma clang fp contract(off)
     const int ix = ix0 + t % nx, iy = iy0 + t / nx;
     const double gx = (ix + 0.5) * hg, gy = (iy + 0.5) * hg;
-    int cx = (int)floor(gx / R.csd), cy = (int)floor(gy / R.csd);
-    cx = min(cx, R.nc - 1); cy = min(cy, R.nc - 1);
+    const int cx = cell_of(ix), cy = cell_of(iy);
     const int li = cx - cx0, lj = cy - cy0;
-    if (li < 0 || li >= ni || lj < 0 || lj >= nj) continue;
     const float ox = (float)(gx - cx * R.csd), oy = (float)(gy - cy * R.csd);
     Acc<1> den, fx, fy, fa, fb;
     den.init(); fx.init(); fy.init(); fa.init(); fb.init();
@@ -68,7 +81,7 @@ __global__ __launch_bounds__(WG) void k_deposit(const StepArgs a, int rep_only, 
       const int dy = cidx / 3 - 1, dx = cidx % 3 - 1;
       const int sc = L.slot[(lj + dy + 1) * (ni + 2) + (li + dx + 1)];
       const float sx = (float)(-dx) * R.cs, sy = (float)(-dy) * R.cs;
-      for (int j = L.cstart[sc]; j < L.cstart[sc + 1]; ++j) {
+      for (int j = L.start[sc]; j < L.start[sc + 1]; ++j) {
         const float2 oj = s_off[j];
         float rx, ry, r2;
         pair_accept(ox, oy, oj.x, oj.y, sx, sy, R.R2, rx, ry, r2);
@@ -138,31 +151,66 @@ __global__ void k_transpose(const double2* in, double2* out, int M) {
   }
 }
 
-// Per-row shell histogram (one thread per row) of the energy of each mode.
-__global__ void k_shell_rows(const double2* Z, int M, int nbins, double* part) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= M) return;
+// Per-row shell histogram of the energy of each mode, one workgroup per row: the
+// modes' energies go to LDS, and the thread of a shell's first mode adds them in
+// column order (a shell is one run of wavenumbers on either side of zero). At M =
+// 512 6 us; one thread per row, adding into the histogram in memory, took 235 us.
+__global__ __launch_bounds__(256) void k_shell_rows(const double2* Z, int M, int nbins, double* part) {
+  extern __shared__ double e[];        // M energies, then the shells of |kc| = 0..M/2
+  int* shell = (int*)(e + M);
+  const int r = blockIdx.x;
   double* h = part + (size_t)r * nbins;
-  for (int n = 0; n < nbins; ++n) h[n] = 0.0;
   const double M4 = (double)M * M * (double)M * M;
   const int kr = (r < M / 2) ? r : r - M;
   const int rm = (M - r) % M;
-  for (int c = 0; c < M; ++c) {
-    const int kc = (c < M / 2) ? c : c - M;
+  for (int n = threadIdx.x; n < nbins; n += 256) h[n] = 0.0;
+  for (int c = threadIdx.x; c < M; c += 256) {
     const int cm = (M - c) % M;
     const double2 a = Z[(size_t)r * M + c], b = Z[(size_t)rm * M + cm];
-    const double e = 0.25 * ((a.x * a.x + a.y * a.y) + (b.x * b.x + b.y * b.y)) / M4;
-    const int n = (int)floor(sqrt((double)kr * kr + (double)kc * kc) + 0.5);
-    if (n < nbins) h[n] += e;
+    e[c] = 0.25 * ((a.x * a.x + a.y * a.y) + (b.x * b.x + b.y * b.y)) / M4;
+  }
+  for (int kc = threadIdx.x; kc <= M / 2; kc += 256)
+    shell[kc] = (int)floor(sqrt((double)kr * kr + (double)kc * kc) + 0.5);
+  __syncthreads();
+  for (int k0 = threadIdx.x; k0 <= M / 2; k0 += 256) {
+    const int n = shell[k0];
+    if (n >= nbins || (k0 > 0 && shell[k0 - 1] == n)) continue;
+    double s = 0.0;
+    int k = k0;
+    for (; k <= M / 2 && shell[k] == n; ++k)
+      if (k < M / 2) s += e[k];          // columns 0..M/2 - 1
+    while (--k >= k0)
+      if (k > 0) s += e[M - k];          // columns M/2..M - 1: kc = -M/2..-1
+    h[n] = s;
   }
 }
 
-__global__ void k_shell_sum(const double* part, int M, int nbins, double* E) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= nbins) return;
+// E[n] = sum over rows in their order; 64 shells a workgroup, whose four waves
+// load 16 rows each ahead of the additions. At M = 512 15 us (123 us with a load
+// before each addition).
+__global__ __launch_bounds__(256) void k_shell_sum(const double* part, int M, int nbins, double* E) {
+  __shared__ double sh[64][64];
+  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int n = blockIdx.x * 64 + l;
   double s = 0.0;
-  for (int r = 0; r < M; ++r) s += part[(size_t)r * nbins + n];
-  E[n] = s;
+  for (int r0 = 0; r0 < M; r0 += 64) {
+    double v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int r = r0 + wv * 16 + j;
+      v[j] = n < nbins && r < M ? part[(size_t)r * nbins + n] : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 16; ++j) sh[wv * 16 + j][l] = v[j];
+    __syncthreads();
+    if (wv == 0) {
+      const int rows = min(64, M - r0);
+#pragma unroll 8
+      for (int j = 0; j < rows; ++j) s += sh[j][l];
+    }
+  }
+  if (wv == 0 && n < nbins) E[n] = s;
 }
 
 // --------------------------------------------------------------- defects
@@ -173,25 +221,42 @@ __device__ inline double wrap_half_pi(double d) {
   return w;
 }
 
-__global__ void k_winding(const double* grid, int M, unsigned long long* counts) {
+// Tiles of 32 x 8 plaquettes: the angle of each of their 33 x 9 nodes is taken once
+// (bounded by the FP64 arctangents: four a plaquette otherwise), and a workgroup
+// makes one atomic a sign, since atomics on one word run one after another at ~10
+// ns. M = 512: 97 us with four angles and an atomic per wave that found a defect,
+// 12 us.
+constexpr int WIND_X = 32, WIND_Y = 8;
+__global__ __launch_bounds__(256) void k_winding(const double* grid, int M, unsigned long long* counts) {
+  __shared__ double th[WIND_Y + 1][WIND_X + 1];
+  __shared__ int found[2];
   const size_t MM = (size_t)M * M;
   const double* qxx = grid + 2 * MM;
   const double* qxy = grid + 3 * MM;
   const double pi = 3.14159265358979323846;
-  unsigned long long np = 0, nm = 0;
-  for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < MM; k += (size_t)gridDim.x * blockDim.x) {
-    const int i = (int)(k % M), j = (int)(k / M);
-    const int i1 = (i + 1) % M, j1 = (j + 1) % M;
-    const double ta = 0.5 * atan2(qxy[(size_t)j * M + i], qxx[(size_t)j * M + i]);
-    const double tb = 0.5 * atan2(qxy[(size_t)j * M + i1], qxx[(size_t)j * M + i1]);
-    const double tc = 0.5 * atan2(qxy[(size_t)j1 * M + i1], qxx[(size_t)j1 * M + i1]);
-    const double td = 0.5 * atan2(qxy[(size_t)j1 * M + i], qxx[(size_t)j1 * M + i]);
+  const int tx = (M + WIND_X - 1) / WIND_X, tiles = tx * ((M + WIND_Y - 1) / WIND_Y);
+  if (threadIdx.x < 2) found[threadIdx.x] = 0;
+  const int x = threadIdx.x % WIND_X, y = threadIdx.x / WIND_X;
+  int np = 0, nm = 0;
+  for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
+    const int i0 = t % tx * WIND_X, j0 = t / tx * WIND_Y;
+    __syncthreads();
+    for (int k = threadIdx.x; k < (WIND_X + 1) * (WIND_Y + 1); k += 256) {
+      const int di = k % (WIND_X + 1), dj = k / (WIND_X + 1);
+      const size_t o = (size_t)((j0 + dj) % M) * M + (i0 + di) % M;
+      th[dj][di] = 0.5 * atan2(qxy[o], qxx[o]);
+    }
+    __syncthreads();
+    if (i0 + x >= M || j0 + y >= M) continue;
+    const double ta = th[y][x], tb = th[y][x + 1], tc = th[y + 1][x + 1], td = th[y + 1][x];
     const double w = wrap_half_pi(tb - ta) + wrap_half_pi(tc - tb) + wrap_half_pi(td - tc) + wrap_half_pi(ta - td);
     if (w > 0.5 * pi) ++np;
     else if (w < -0.5 * pi) ++nm;
   }
-  if (np) atomicAdd(&counts[0], np);
-  if (nm) atomicAdd(&counts[1], nm);
+  if (np) atomicAdd(&found[0], np);
+  if (nm) atomicAdd(&found[1], nm);
+  __syncthreads();
+  if (threadIdx.x < 2 && found[threadIdx.x]) atomicAdd(&counts[threadIdx.x], (unsigned long long)found[threadIdx.x]);
 }
 
 // -------------------------------------------------------------- launchers
@@ -264,14 +329,14 @@ void launch_fft2(const double* grid, double2* z, double2* w, int M, int logM, hi
 }
 
 void launch_shells(const double2* Z, int M, int nbins, double* part, double* E, hipStream_t s) {
-  hipLaunchKernelGGL(k_shell_rows, dim3((M + 63) / 64), dim3(64), 0, s, Z, M, nbins, part);
-  hipLaunchKernelGGL(k_shell_sum, dim3((nbins + 255) / 256), dim3(256), 0, s, part, M, nbins, E);
+  const size_t lds = sizeof(double) * M + sizeof(int) * (M / 2 + 1);   // M <= 2048: 20 KB
+  hipLaunchKernelGGL(k_shell_rows, dim3(M), dim3(256), lds, s, Z, M, nbins, part);
+  hipLaunchKernelGGL(k_shell_sum, dim3((nbins + 63) / 64), dim3(256), 0, s, part, M, nbins, E);
 }
 
 void launch_winding(const double* grid, int M, unsigned long long* counts, hipStream_t s) {
-  const size_t MM = (size_t)M * M;
-  const int nb = (int)std::min<size_t>((MM + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_winding, dim3(nb), dim3(256), 0, s, grid, M, counts);
+  const int tiles = ((M + WIND_X - 1) / WIND_X) * ((M + WIND_Y - 1) / WIND_Y);
+  hipLaunchKernelGGL(k_winding, dim3(std::min(tiles, 512)), dim3(256), 0, s, grid, M, counts);
 }
 
 }  // namespace nem

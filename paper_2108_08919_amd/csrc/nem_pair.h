@@ -388,6 +388,23 @@ struct TileRef {
 };
 __device__ __forceinline__ ConstRep& rep_of_tile(const StepArgs& a, int rep) { return ((ConstRep*)a.reps)[rep]; }
 
+// The cell tables of a tile from its header (for kernels that walk cells).
+template <int T>
+struct CellLDS {
+  int start[HdrCfg<T>::NSC + 1];   // first LDS slot of each staged cell
+  int slot[HdrCfg<T>::NSC];        // region cell y * (ni + 2) + x -> staged cell
+};
+template <int T>
+__device__ __forceinline__ void tile_cells(const TileRef<T>& t, CellLDS<T>& L) {
+  const int nreg = (t.ni + 2) * (t.nj + 2);
+  const int c = threadIdx.x;
+  if (c <= nreg) {
+    const int2 e = t.cell(c);
+    L.start[c] = e.y & 0xFFFF;
+    if (c < nreg) L.slot[((e.y >> 20) & 15) * (t.ni + 2) + ((e.y >> 16) & 15)] = c;
+  }
+}
+
 // Positions of the passes that need no exact neighbour decision (A, B, C): 32-bit
 // integers in units of 1/fix relative to the tile's corner, fix a power of two
 // for which the 2^32 units are at least 3.5 cell sides. Differences of
@@ -451,5 +468,35 @@ __device__ __forceinline__ int staged_global(const StepArgs& a, const TileLDS<T>
   return g;
 }
 
+// Lanes per particle for an iteration with `rem` particles left: the base
+// value, doubled while the particles still fill the workgroup (at most 16).
+__device__ __forceinline__ int lanes_for(int rem, int base_lpp) {
+  int l = base_lpp;
+  while (l < 16 && rem * l * 2 <= WG) l <<= 1;
+  return l;
+}
+
+__device__ __forceinline__ float wave_sum(float v, int lpp) {
+  for (int o = 1; o < lpp; o <<= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+__device__ __forceinline__ int wave_sum_int(int v, int lpp) {
+  for (int o = 1; o < lpp; o <<= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// Pair geometry of an entry of a cell-ordered list (LDS slot | direction code <<
+// 12; the direct search's, and the Verlet list of learned steps) through the
+// neighbour predicate.
+__device__ __forceinline__ bool verlet_pair(uint32_t e, const float2* shift, int jmax, const float2* s_off,
+                                            float2 oi, float R2, int& j, float& rx, float& ry, float& r2) {
+  j = min((int)(e & 0xFFFu), jmax);
+  const float2 sh = shift[(e >> 12) & 15u];
+  const float2 oj = s_off[j];
+  return pair_accept(oi.x, oi.y, oj.x, oj.y, sh.x, sh.y, R2, rx, ry, r2);
+}
+
+constexpr int CELL_MAX = 48;   // particles of a cell that a search covers (more raise ERR_OVERFLOW)
+constexpr unsigned long long MASK48 = (1ull << 48) - 1ull;
 
 }  // namespace nem

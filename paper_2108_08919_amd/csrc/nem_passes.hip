@@ -69,50 +69,6 @@ __device__ __forceinline__ float2 region_cell(int entry) {
   return make_float2((float)((entry >> 16) & 15), (float)((entry >> 20) & 15));
 }
 
-// Lanes per particle for an iteration with `rem` particles left: the base
-// value, doubled while the particles still fill the workgroup (at most 16).
-__device__ __forceinline__ int lanes_for(int rem, int base_lpp) {
-  int l = base_lpp;
-  while (l < 16 && rem * l * 2 <= WG) l <<= 1;
-  return l;
-}
-
-__device__ __forceinline__ float wave_sum(float v, int lpp) {
-  for (int o = 1; o < lpp; o <<= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-__device__ __forceinline__ int wave_sum_int(int v, int lpp) {
-  for (int o = 1; o < lpp; o <<= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-// The cell tables of a tile from its header (the Verlet build walks cells).
-template <int T>
-struct CellLDS {
-  int start[HdrCfg<T>::NSC + 1];   // first LDS slot of each staged cell
-  int slot[HdrCfg<T>::NSC];        // region cell y * (ni + 2) + x -> staged cell
-};
-template <int T>
-__device__ __forceinline__ void tile_cells(const TileRef<T>& t, CellLDS<T>& L) {
-  const int nreg = (t.ni + 2) * (t.nj + 2);
-  const int c = threadIdx.x;
-  if (c <= nreg) {
-    const int2 e = t.cell(c);
-    L.start[c] = e.y & 0xFFFF;
-    if (c < nreg) L.slot[((e.y >> 20) & 15) * (t.ni + 2) + ((e.y >> 16) & 15)] = c;
-  }
-}
-
-// Pair geometry of an entry of the direct search's list (LDS slot | direction
-// code << 12) through the neighbour predicate.
-__device__ __forceinline__ bool verlet_pair(uint32_t e, const float2* shift, int jmax, const float2* s_off,
-                                            float2 oi, float R2, int& j, float& rx, float& ry, float& r2) {
-  j = min((int)(e & 0xFFFu), jmax);
-  const float2 sh = shift[(e >> 12) & 15u];
-  const float2 oj = s_off[j];
-  return pair_accept(oi.x, oi.y, oj.x, oj.y, sh.x, sh.y, R2, rx, ry, r2);
-}
-
 // Walk the direct search's list of particle g (two 16-bit entries a word);
 // flush() closes a compensation chunk every 16 entries (the last, open chunk is
 // summed by the accumulators' value()). One word is loaded ahead.
@@ -236,8 +192,6 @@ __device__ __forceinline__ void walk_list(const StepArgs& a, Lane<T>& l, Body&& 
 // 60-63. Phase 2 walks the accepted pairs in cell order, all lanes taking their
 // k-th pair together: it sums the kernel terms and emits the list entries
 // (coalesced stores), so the kernel is evaluated for accepted pairs only.
-constexpr int CELL_MAX = 48;
-constexpr unsigned long long MASK48 = (1ull << 48) - 1ull;
 
 template <int T, int COMP, int KERN>
 __device__ __forceinline__ void tile_pass_a(const StepArgs& a, int w) {
