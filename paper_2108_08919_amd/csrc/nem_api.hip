@@ -323,6 +323,13 @@ void build_headers(nem_sim* s) { launch_tile_headers(hdr_args(s), s->stream); }
 // The next step rebuilds the Verlet list.
 void request_relist(nem_sim* s) { launch_set_requests(s->flags, s->parity, 1, 1, s->stream); }
 
+// The steps that follow walk the list in this order; it is rebuilt if it is in the other one.
+void use_list_order(nem_sim* s, bool cells) {
+  if (s->cell_order == cells) return;
+  s->cell_order = cells;
+  request_relist(s);
+}
+
 int read_flags(nem_sim* s, unsigned* f) {
   HIPCHK(hipMemcpyAsync(f, s->flags, sizeof(unsigned) * 2, hipMemcpyDeviceToHost, s->stream));
   HIPCHK(hipStreamSynchronize(s->stream));
@@ -387,6 +394,14 @@ PassCfg pass_cfg(const nem_sim* s) {
                  s->hp[0].integrator};
 }
 
+// A pass of a step in the current list order (pass 1: the list when requested, then the volumes).
+bool enqueue_pass(nem_sim* s, int pass, hipStream_t st) {
+  const PassCfg cfg = pass_cfg(s);
+  const StepArgs a = step_args(s);
+  if (s->cell_order) return launch_pass_learn(pass, cfg, a, st);
+  return pass == 1 ? launch_pass_a_verlet(cfg, a, st) : launch_pass(pass, cfg, a, st);
+}
+
 // The start of a step on stream st: the rebin kernels (they return at once
 // unless a rebin was requested) and pass A (Verlet build or walk: the list
 // every pass walks, and the volumes).
@@ -396,7 +411,7 @@ int enqueue_prologue(nem_sim* s, hipStream_t st) {
     launch_rebin(sort_args(s), hdr_args(s), st);
   }
   Timed t(s, 1);
-  if (!launch_pass_a_verlet(pass_cfg(s), step_args(s), st)) { s->err = "unsupported kernel configuration"; return NEM_E_INVAL; }
+  if (!enqueue_pass(s, 1, st)) { s->err = "unsupported kernel configuration"; return NEM_E_INVAL; }
   return NEM_OK;
 }
 
@@ -405,11 +420,9 @@ int enqueue_prologue(nem_sim* s, hipStream_t st) {
 int enqueue_step(nem_sim* s, hipStream_t st) {
   int rc = enqueue_prologue(s, st);
   if (rc) return rc;
-  const PassCfg cfg = pass_cfg(s);
-  StepArgs a = step_args(s);
   for (int pass = 2; pass <= 4; ++pass) {
     Timed t(s, pass);
-    if (!launch_pass(pass, cfg, a, st)) { s->err = "unsupported kernel configuration"; return NEM_E_INVAL; }
+    if (!enqueue_pass(s, pass, st)) { s->err = "unsupported kernel configuration"; return NEM_E_INVAL; }
   }
   HIPCHK(hipGetLastError());
   return NEM_OK;
@@ -489,7 +502,7 @@ int deposit_grid(nem_sim* s, int r, int M) {
 }
 
 int run_steps(nem_sim* s, int64_t nsteps) {
-  const bool graph = s->use_graph && !s->timing && !s->feat;
+  const bool graph = s->use_graph && !s->timing && !s->feat && !s->cell_order;
   if (graph && !s->graph[0]) {
     int rc = capture_graphs(s);
     if (rc) { drop_graphs(s); return rc; }
@@ -706,6 +719,7 @@ int nem_step(nem_sim* s, int64_t nsteps) {
   if (!s || nsteps < 0) return NEM_E_INVAL;
   for (int r = 0; r < s->R; ++r)
     if (!s->has_state[r]) { s->err = "nem_set_state was not called for every replica"; return NEM_E_STATE; }
+  if (nsteps > 0) use_list_order(s, false);
   return run_steps(s, nsteps);
 }
 
@@ -730,7 +744,8 @@ int nem_sync(nem_sim* s) {
 // step reads before writing it is there, so a load continues bit for bit.
 namespace {
 constexpr char RAW_MAGIC[8] = {'N', 'E', 'M', 'R', 'A', 'W', '0', '1'};
-constexpr int64_t RAW_VERSION = 2;
+// Versions: the order of the saved Verlet list
+constexpr int64_t RAW_BY_CELL = 1, RAW_BY_DISTANCE = 2;
 constexpr int RAW_PD = 17, RAW_PI = 7;  // doubles and integers of nem_params
 
 struct RawSeg { void* dev; size_t bytes; };
@@ -779,7 +794,7 @@ int nem_save_raw(nem_sim* s, void* host, uint64_t bytes) {
   if (bytes < raw_total(s)) { s->err = "checkpoint buffer smaller than nem_raw_bytes"; return NEM_E_NOMEM; }
   char* b = (char*)host;
   std::memcpy(b, RAW_MAGIC, 8);
-  const int64_t hw[8] = {RAW_VERSION, s->R, s->ntot, s->ncells, s->parity, s->T, s->LPP, s->COMP};
+  const int64_t hw[8] = {s->cell_order ? RAW_BY_CELL : RAW_BY_DISTANCE, s->R, s->ntot, s->ncells, s->parity, s->T, s->LPP, s->COMP};
   std::memcpy(b + 8, hw, sizeof(hw));
   char* w = b + 8 + sizeof(hw);
   for (int r = 0; r < s->R; ++r) {
@@ -812,8 +827,7 @@ int nem_load_raw(nem_sim* s, const void* host, uint64_t bytes) {
   if (bytes < raw_header_bytes(s->R) || std::memcmp(b, RAW_MAGIC, 8) != 0) return bad("not a checkpoint of this library");
   int64_t hw[8];
   std::memcpy(hw, b + 8, sizeof(hw));
-  // version 1 held the Verlet list in another format: it is rebuilt by the next step
-  if (hw[0] != 1 && hw[0] != RAW_VERSION) return bad("unknown checkpoint version");
+  if (hw[0] != RAW_BY_CELL && hw[0] != RAW_BY_DISTANCE) return bad("unknown checkpoint version");
   if (hw[1] != s->R || hw[2] != s->ntot || hw[3] != s->ncells) return bad("replica count or sizes differ");
   if (!(hw[4] == 0 || hw[4] == 1) || !(hw[5] == 4 || hw[5] == 8) || !(hw[6] == 1 || hw[6] == 2 || hw[6] == 4) ||
       hw[7] < 0 || hw[7] > 2)
@@ -847,6 +861,7 @@ int nem_load_raw(nem_sim* s, const void* host, uint64_t bytes) {
     if (rc) return rc;
   }
   s->parity = (int)hw[4];
+  s->cell_order = hw[0] == RAW_BY_CELL;
   unsigned fw[FLAG_WORDS] = {0};
   for (const RawSeg& g : raw_segments(s)) {
     if (g.dev) {
@@ -856,7 +871,7 @@ int nem_load_raw(nem_sim* s, const void* host, uint64_t bytes) {
       std::memcpy(fs, w, sizeof(fs));
       fw[0] = fs[0];
       fw[FLAG_REQ + 2 * s->parity] = fs[1];
-      fw[FLAG_REQ + 2 * s->parity + 1] = hw[0] == 1 ? 1u : fs[2];
+      fw[FLAG_REQ + 2 * s->parity + 1] = fs[2];
       HIPCHK(hipMemcpyAsync(s->flags, fw, sizeof(fw), hipMemcpyHostToDevice, s->stream));
     }
     w += g.bytes;
@@ -877,6 +892,7 @@ int nem_neighbor_list(nem_sim* s, int32_t r, int32_t which, int64_t* row_ptr, in
   if (!s->has_state[r]) return NEM_E_STATE;
   const int n = (int)s->n[r];
   // the next step's own start: rebin if requested, then the Verlet build or walk
+  use_list_order(s, false);
   const int timing = s->timing;
   s->timing = 0;
   int rc = enqueue_prologue(s, s->stream);

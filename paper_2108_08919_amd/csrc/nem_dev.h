@@ -102,8 +102,9 @@ struct StepArgs {
   float* feat;               // NULL, or 12 features per particle at [g] (storage order)
   uint32_t* vl;              // Verlet list (pairs within the Verlet radius at the last build): word w of
                              // particle g at vl[w*ntot + g], entries as ListFmt (nem_pair.h) packs them,
-                             // outer pairs first, then middle, then inner
-  uint32_t* vcnt;            // its counts (vc_total ... in nem_pair.h)
+                             // outer pairs first, then middle, then inner; in learned steps the layout
+                             // of nl, in cell order
+  uint32_t* vcnt;            // its counts (vc_total ... in nem_pair.h; in learned steps the length)
   float2* off_build;         // offset of each particle when the Verlet list was built
   const int* id;             // particle ids (sorted order)
 };
@@ -149,6 +150,7 @@ bool launch_pass(int pass, const PassCfg& c, const StepArgs& a, hipStream_t s);
 void tile_header_shape(int T, int kern, int* maxp, int* ints);
 void launch_tile_headers(const HdrArgs& h, hipStream_t s);
 bool launch_pass_a_verlet(const PassCfg& c, const StepArgs& a, hipStream_t s);
+bool launch_pass_learn(int pass, const PassCfg& c, const StepArgs& a, hipStream_t s);
 void launch_set_requests(unsigned* flags, int parity, int keep_rebin, int relist, hipStream_t st);
 void launch_list_export(int T, int kern, const StepArgs& a, int rep, int which, int mode, int* cnt,
                         const int64_t* row_ptr, int32_t* col, int64_t cap, hipStream_t s);

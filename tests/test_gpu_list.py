@@ -73,3 +73,51 @@ def test_older_checkpoint_rebuilds_its_list():
     assert e["u"] < 1e-6 and e["Q"] < 1e-6 and e["rho"] < 1e-6 and e["pos_abs_max"] < 1e-9
     a.close()
     b.close()
+
+
+# variants of the learned steps' own passes: tile, lanes, kernel, momentum form,
+# elastic stress, corrector; ragged last tiles and cells of 7 to 21 particles
+LEARN = [(4, 1, 37, {}), (8, 2, 33, {}), (4, 4, 22, dict(kernel=1)), (8, 1, 37, dict(kernel=1)),
+         (4, 1, 38, dict(form=1, h=1.5)), (4, 2, 24, dict(elastic=1)), (4, 1, 31, dict(integrator=1))]
+
+
+@pytest.mark.parametrize("tile,lpp,L,kw", LEARN)
+def test_learned_steps_and_ordinary_ones_take_turns(tile, lpp, L, kw):
+    """Learned steps with a network of zeros are steps of mult dt, so they agree
+    with ordinary ones to rounding although they walk their list in another
+    order; ordinary steps, a neighbour export and a checkpoint follow either."""
+    import paper_2108_08919_amd as P
+    from paper_2108_08919_amd import learned
+    p = wl.Params(L=float(L), zeta=0.03, **kw)
+    print("learned", tile, lpp, L, kw, flush=True)
+    s0 = random_state(L, 4, amp_u=2e-3)
+    z = learned.zero_network()
+    opts = {P.NEM_OPT_TILE: tile, P.NEM_OPT_LPP: lpp}
+    ref, r = gpu_run(p.replace(dt=4 * p.dt), s0, 6, opts)
+    a = P.Sim([p], [L * L])
+    for k, v in opts.items():
+        a.set_option(k, v)
+    a.set_state(0, s0)
+    assert a.step_learned(z, 6, 4, 1.0)[0] == 0
+    e = field_errors(a.get_state(0), ref, s0, L)
+    assert e["u"] < 1e-5 and e["Q"] < 1e-6 and e["rho"] < 1e-7 and e["pos_abs_max"] < 1e-7
+    # a checkpoint between learned steps continues bit for bit, in learned and in ordinary steps
+    b = P.Sim([p], [L * L])
+    b.load_raw(a.save_raw())
+    for s in (a, b):
+        s.step_learned(z, 3, 4, 1.0)
+        s.step(2)
+        s.step_learned(z, 1, 4, 1.0)
+    # the export rebuilds the list in its own order
+    rp, col, cxy, oxy = a.neighbor_list(0, 0, offsets=True)
+    nc = int(np.floor(L / (oracle.kappa(p.kernel) * p.h + p.skin)))
+    orp, ocol = oracle.neighbors_offsets(p, nc, cxy, oxy)
+    rows = lambda x, y: [sorted(y[x[i]:x[i + 1]]) for i in range(x.size - 1)]
+    assert rows(rp, col) == rows(orp, ocol)
+    for s in (a, b):
+        s.step(3)
+        s.check()
+    ga, gb = a.get_state(0), b.get_state(0)
+    assert all(np.array_equal(ga[k], gb[k]) for k in ga)
+    for s in (a, b, r, z):
+        s.close()
