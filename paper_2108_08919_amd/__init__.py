@@ -238,7 +238,7 @@ def nem_set_state(h, r, x, y, ux, uy, qxx, qxy, rho, ax=None, ay=None):
 
 
 def nem_get_state(h, r, n) -> Dict[str, np.ndarray]:
-    out = {k: np.zeros(n) for k in ("x", "y", "ux", "uy", "qxx", "qxy", "rho", "ax", "ay")}
+    out = {k: np.empty(n) for k in ("x", "y", "ux", "uy", "qxx", "qxy", "rho", "ax", "ay")}
     _check(h, lib().nem_get_state(C.c_void_p(h), r, *[_dp(out[k]) for k in
                                                      ("x", "y", "ux", "uy", "qxx", "qxy", "rho", "ax", "ay")]),
            "nem_get_state")

@@ -8,11 +8,13 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/nematic_sph.h"
@@ -331,8 +333,115 @@ void use_list_order(nem_sim* s, bool cells) {
 }
 
 int read_flags(nem_sim* s, unsigned* f) {
-  HIPCHK(hipMemcpyAsync(f, s->flags, sizeof(unsigned) * 2, hipMemcpyDeviceToHost, s->stream));
+  unsigned* to = s->pin_flags ? s->pin_flags : f;
+  HIPCHK(hipMemcpyAsync(to, s->flags, sizeof(unsigned) * 2, hipMemcpyDeviceToHost, s->stream));
   HIPCHK(hipStreamSynchronize(s->stream));
+  if (to != f) std::memcpy(f, to, sizeof(unsigned) * 2);
+  return NEM_OK;
+}
+
+// Read-back of nf arrays of n doubles (contiguous at src) into the caller's
+// memory (dst[f], NULL: skipped). Pageable copies of the runtime wrote the caller's
+// pages, most of them touched for the first time, from one thread: 9.5 GB/s, and 30
+// us for each array however small. Here the arrays go through PIN_SLOTS pinned
+// chunks, large enough that the cost of a copy (some 30 us) is small beside it, and
+// are written out in pieces by up to PIN_THREADS threads behind the copies, one a
+// megabyte. Below two megabytes it is one copy and one thread: starting threads
+// would cost more than they save.
+constexpr size_t PIN_CHUNK = 4 << 20, PIN_PIECE = 256 << 10, PIN_SMALL = 2 << 20;
+constexpr int PIN_SLOTS = 4, PIN_THREADS = 8;
+
+void alloc_pin(nem_sim* s) {
+  const size_t all = sizeof(double) * 9 * (size_t)s->stage_n;
+  s->pin_slots = (int)std::min<size_t>(PIN_SLOTS, (all + PIN_CHUNK - 1) / PIN_CHUNK);
+  const size_t bytes = (std::min(all, PIN_CHUNK * s->pin_slots) + 63) / 64 * 64;
+  if (hipHostMalloc((void**)&s->pin, bytes + 64, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    s->pin = nullptr;
+    return;
+  }
+  s->pin_flags = (unsigned*)(s->pin + bytes);
+}
+
+void free_pin(nem_sim* s) {
+  for (hipEvent_t e : s->pin_ev) hipEventDestroy(e);
+  s->pin_ev.clear();
+  if (s->pin) hipHostFree(s->pin);
+  s->pin = nullptr;
+  s->pin_flags = nullptr;
+}
+
+int copy_out(nem_sim* s, int nf, double* const* dst, const double* src, size_t n) {
+  const size_t fb = sizeof(double) * n, all = fb * nf;
+  if (s->pin && all <= PIN_SMALL) {   // within the first chunk, which holds nine arrays of the largest box or PIN_CHUNK
+    HIPCHK(hipMemcpyAsync(s->pin, src, all, hipMemcpyDeviceToHost, s->stream));
+    HIPCHK(hipStreamSynchronize(s->stream));
+    for (int f = 0; f < nf; ++f)
+      if (dst[f]) std::memcpy(dst[f], s->pin + fb * f, fb);
+    return NEM_OK;
+  }
+  while (s->pin && (int)s->pin_ev.size() < s->pin_slots) {
+    hipEvent_t e;
+    HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    s->pin_ev.push_back(e);
+  }
+  if (!s->pin) {
+    for (int f = 0; f < nf; ++f)
+      if (dst[f]) HIPCHK(hipMemcpyAsync(dst[f], src + n * f, fb, hipMemcpyDeviceToHost, s->stream));
+    HIPCHK(hipStreamSynchronize(s->stream));
+    return NEM_OK;
+  }
+  const int nc = (int)((all + PIN_CHUNK - 1) / PIN_CHUNK), slots = s->pin_slots;
+  const int np = (int)((all + PIN_PIECE - 1) / PIN_PIECE), per = (int)(PIN_CHUNK / PIN_PIECE);
+  std::vector<std::atomic<int>> left(nc);   // pieces of a chunk not yet written out
+  for (int c = 0; c < nc; ++c) left[c].store(std::min(per, np - c * per), std::memory_order_relaxed);
+  std::atomic<int> ready{0}, next{0};       // chunks that have arrived; pieces taken
+  std::atomic<bool> stop{false};
+  auto write = [&](int p) {
+    const int c = p / per;
+    const char* from = s->pin + PIN_CHUNK * (c % slots) + PIN_PIECE * (p % per);
+    for (size_t o = PIN_PIECE * p, end = std::min(all, o + PIN_PIECE); o < end;) {   // a piece may span two arrays
+      const size_t f = o / fb, k = std::min(end, (f + 1) * fb) - o;
+      if (dst[f]) std::memcpy((char*)dst[f] + (o - f * fb), from, k);
+      from += k;
+      o += k;
+    }
+    left[c].fetch_sub(1, std::memory_order_release);
+  };
+  auto work = [&]() {
+    for (int p = next++; p < np; p = next++) {
+      while (ready.load(std::memory_order_acquire) <= p / per)
+        if (stop.load()) return;
+        else std::this_thread::yield();
+      write(p);
+    }
+  };
+  std::vector<std::thread> pool;
+  try {
+    const int want = (int)std::min<size_t>(PIN_THREADS, all >> 20);
+    for (int t = 0; t < want; ++t) pool.emplace_back(work);
+  } catch (...) {
+    // as many as there are; with none, this thread writes
+  }
+  hipError_t e = hipSuccess;
+  int sent = 0;
+  for (int c = 0; c < nc && e == hipSuccess; ++c) {
+    for (; sent < nc && sent < c + slots && e == hipSuccess; ++sent) {
+      while (sent >= slots && left[sent - slots].load(std::memory_order_acquire)) std::this_thread::yield();
+      const size_t o = PIN_CHUNK * sent;
+      e = hipMemcpyAsync(s->pin + PIN_CHUNK * (sent % slots), (const char*)src + o, std::min(PIN_CHUNK, all - o),
+                         hipMemcpyDeviceToHost, s->stream);
+      if (e == hipSuccess) e = hipEventRecord(s->pin_ev[sent % slots], s->stream);
+    }
+    if (e == hipSuccess) e = hipEventSynchronize(s->pin_ev[c % slots]);
+    if (e != hipSuccess) break;
+    ready.store(c + 1, std::memory_order_release);
+    if (pool.empty())
+      for (int p = c * per; p < std::min(np, (c + 1) * per); ++p) write(p);
+  }
+  if (e != hipSuccess) stop.store(true);
+  for (auto& t : pool) t.join();
+  if (e != hipSuccess) return hip_fail(s, e, "read-back");
   return NEM_OK;
 }
 
@@ -634,6 +743,7 @@ int nem_create(const nem_params* p, const int64_t* n, int32_t R, void* dev_arena
   if (e != hipSuccess) { hip_fail(s, e, "arena init"); nem_destroy(s); return NEM_E_HIP; }
   rc = build_work(s);
   if (rc) { nem_destroy(s); return rc; }
+  alloc_pin(s);
   *out = s;
   return NEM_OK;
 }
@@ -689,10 +799,10 @@ int nem_get_qyy(nem_sim* s, int32_t r, double* qyy) {
   SortArgs a = sort_args(s);
   launch_qyy_io(a, r, n, s->stage, 0, s->stream);
   HIPCHK(hipGetLastError());
-  HIPCHK(hipMemcpyAsync(qyy, s->stage, sizeof(double) * n, hipMemcpyDeviceToHost, s->stream));
-  HIPCHK(hipStreamSynchronize(s->stream));
+  int rc = copy_out(s, 1, &qyy, s->stage, (size_t)n);
+  if (rc) return rc;
   unsigned f[2];
-  int rc = read_flags(s, f);
+  rc = read_flags(s, f);
   if (rc) return rc;
   return status_from_flags(s, f[0]);
 }
@@ -706,11 +816,10 @@ int nem_get_state(nem_sim* s, int32_t r, double* x, double* y, double* ux, doubl
   launch_export(a, r, s->stage, n, s->stream);
   HIPCHK(hipGetLastError());
   double* dst[9] = {x, y, ux, uy, qxx, qxy, rho, ax, ay};
-  for (int f = 0; f < 9; ++f)
-    if (dst[f]) HIPCHK(hipMemcpyAsync(dst[f], s->stage + (size_t)f * n, sizeof(double) * n, hipMemcpyDeviceToHost, s->stream));
-  HIPCHK(hipStreamSynchronize(s->stream));
+  int rc = copy_out(s, 9, dst, s->stage, (size_t)n);
+  if (rc) return rc;
   unsigned f[2];
-  int rc = read_flags(s, f);
+  rc = read_flags(s, f);
   if (rc) return rc;
   return status_from_flags(s, f[0]);
 }
@@ -1282,6 +1391,7 @@ void nem_destroy(nem_sim* s) {
   free_grid(s);
   if (s->g_mix) hipFree(s->g_mix);
   free_snapshot(s);
+  free_pin(s);
   if (s->own && s->arena) hipFree(s->arena);
   delete s;
 }

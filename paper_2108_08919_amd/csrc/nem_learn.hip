@@ -290,6 +290,27 @@ void free_snapshot(nem_sim* s) {
       if (p) hipFree(p);
     S = nem_sim::Snap();
   }
+  auto& W = s->learn;
+  for (void* p : {(void*)W.X, (void*)W.Y, (void*)W.mx})
+    if (p) hipFree(p);
+  if (W.hmx) hipHostFree(W.hmx);
+  for (auto& e : W.ev)
+    if (e) hipEventDestroy(e);
+  W = nem_sim::Learn();
+}
+
+// The buffers of learned steps (six allocations and releases a call cost 0.4 ms).
+static int ensure_learn(nem_sim* s) {
+  auto& W = s->learn;
+  const size_t N = (size_t)s->ntot, NS = (size_t)mlp_norm_slots();
+  if (!W.X) HIPCHK(hipMalloc((void**)&W.X, sizeof(float) * 12 * N));
+  if (!W.Y) HIPCHK(hipMalloc((void**)&W.Y, sizeof(float) * 5 * N));
+  if (!W.mx) HIPCHK(hipMalloc((void**)&W.mx, sizeof(unsigned) * 2 * NS));
+  if (!W.hmx) HIPCHK(hipHostMalloc((void**)&W.hmx, sizeof(unsigned) * 2, hipHostMallocMapped | hipHostMallocCoherent));
+  if (!W.dmx) HIPCHK(hipHostGetDevicePointer((void**)&W.dmx, W.hmx, 0));
+  for (auto& e : W.ev)
+    if (!e) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+  return NEM_OK;
 }
 
 int take_snapshot(nem_sim* s, int i, unsigned* zero, int nzero) {
@@ -709,23 +730,16 @@ int nem_step_learned(nem_sim* s, nem_mlp* m, int64_t n_macro, int32_t mult, doub
   const float tauf = (float)tau;
   unsigned tau_bits;
   std::memcpy(&tau_bits, &tauf, sizeof(tau_bits));
-  float *X = nullptr, *Y = nullptr;
   const int NS = mlp_norm_slots();
-  unsigned *mx = nullptr, *hmx = nullptr;
-  hipEvent_t ev[2] = {nullptr, nullptr};
-  int rc = NEM_OK;
+  int rc = ensure_learn(s);
+  if (rc) return rc;
+  float *X = s->learn.X, *Y = s->learn.Y;
+  unsigned *mx = s->learn.mx, *hmx = s->learn.hmx, *dmx = s->learn.dmx;
+  hipEvent_t* ev = s->learn.ev;
   auto chk = [&](hipError_t e, const char* what) {
     if (e != hipSuccess && rc == NEM_OK) rc = hip_fail(s, e, what);
     return e == hipSuccess;
   };
-  chk(hipMalloc((void**)&X, sizeof(float) * 12 * N), "hipMalloc (inputs)");
-  chk(hipMalloc((void**)&Y, sizeof(float) * 5 * N), "hipMalloc (corrections)");
-  chk(hipMalloc((void**)&mx, sizeof(unsigned) * 2 * NS), "hipMalloc (max norm)");
-  chk(hipHostMalloc((void**)&hmx, sizeof(unsigned) * 2, hipHostMallocMapped | hipHostMallocCoherent),
-      "hipHostMalloc (max norm)");
-  unsigned* dmx = nullptr;   // the device's address of hmx
-  if (hmx) chk(hipHostGetDevicePointer((void**)&dmx, hmx, 0), "hipHostGetDevicePointer");
-  for (auto& e : ev) chk(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
   // One macro step, enqueued without waiting: snapshot, a step of mult*dt with
   // the inputs captured, inference, and the correction (skipped on the device
   // when the largest correction norm exceeds tau), which also stores that norm
@@ -775,10 +789,6 @@ int nem_step_learned(nem_sim* s, nem_mlp* m, int64_t n_macro, int32_t mult, doub
   }
   if (!rc) rc = scale_dt(s, 1.0f / (float)mult);
   hipStreamSynchronize(s->stream);
-  for (auto& e : ev)
-    if (e) hipEventDestroy(e);
-  hipFree(X); hipFree(Y); hipFree(mx);
-  if (hmx) hipHostFree(hmx);
   if (n_fallback) *n_fallback = nfb;
   if (max_norm) *max_norm = worst;
   if (rc) return rc;

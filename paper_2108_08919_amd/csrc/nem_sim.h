@@ -42,6 +42,10 @@ struct nem_sim {
   bool cell_order = false;
   double* stage = nullptr; int64_t stage_n = 0;
   double* red = nullptr;
+  // pinned host memory that results are read back through: PIN_SLOTS chunks (fewer
+  // for small boxes), then the flag words; NULL: none could be had
+  char* pin = nullptr; unsigned* pin_flags = nullptr; int pin_slots = 0;
+  std::vector<hipEvent_t> pin_ev;
   int parity = 0;
   std::vector<char> has_state;
   int T = 4, LPP = 1, COMP = 1;
@@ -76,6 +80,13 @@ struct nem_sim {
     int parity = 0;
     std::vector<float> dt;
   } snap[2];  // two, so that a learned macro step can run while the previous one is checked
+  // buffers of learned steps, allocated by the first: inputs, corrections, largest
+  // norms (two macro steps in flight) on the device and in pinned host memory
+  struct Learn {
+    float *X = nullptr, *Y = nullptr;
+    unsigned *mx = nullptr, *hmx = nullptr, *dmx = nullptr;   // dmx: the device's address of hmx
+    hipEvent_t ev[2] = {nullptr, nullptr};
+  } learn;
   int device = 0;            // device current at nem_create
   void* scratch = nullptr;   // that device's copy of the no-allocation scratch
   std::string err;
