@@ -255,10 +255,13 @@ SortArgs sort_args(nem_sim* s) {
   return a;
 }
 
+
 StepArgs step_args(nem_sim* s) {
   StepArgs a;
   const int c = s->parity, x = 1 - s->parity;
-  a.reps = s->d_reps; a.work = s->d_work; a.nwork = s->nwork; a.T = s->T; a.lpp = s->LPP; a.grid = s->persist;
+  a.reps = s->d_reps; a.work = s->d_work; a.nwork = s->nwork; a.T = s->T; a.grid = s->persist;
+  a.parts = s->cell_order ? 1 : s->parts;
+  a.lpp = s->LPP;
   a.hdr = s->d_hdr; a.cell_start = s->cell_start; a.ncells = s->ncells; a.ntot = s->ntot;
   a.off_cur = s->off[c]; a.off_nxt = s->off[x]; a.offlo = s->offlo; a.u = s->u;
   a.q_cur = s->q[c]; a.q_nxt = s->q[x]; a.acc = s->acc; a.drho = s->drho; a.cell = s->cell;
@@ -271,6 +274,27 @@ StepArgs step_args(nem_sim* s) {
   a.feat = s->feat; a.id = s->id;
   a.vl = s->vl; a.vcnt = s->vcnt; a.off_build = s->off_build;
   return a;
+}
+
+// Where tiles hold more than the 256 particles of a workgroup's round and there are
+// few of them, a pass is the latency of two rounds or more (box sides that are no
+// multiple of the cell's 4 dx: a few more than 256 at T = 4; Wendland C2 at T = 8:
+// about 470; the quintic at T = 8: 1024). Each round then goes to a workgroup of its
+// own, with the same lanes per particle and the same groups of 64: the same bits. It
+// costs staging the tile once more, which pays up to five workgroups a CU, or two and
+// a half where the last round holds few particles. us a step without / with: T = 4
+// 97^2 70 / 55, 137^2 69 / 55, 211^2 71 / 61, 275^2 75 / 71 and, beyond the line, 330^2
+// 76 / 83, 514^2 106 / 142; Wendland T = 8 96^2 54 / 38, 300^2 56 / 45, 512^2 72 / 67
+// and, beyond, 700^2 89 / 103; quintic T = 8 64^2 165 / 60, 300^2 174 / 71.
+void choose_parts(nem_sim* s) {
+  double most = 0.0;   // mean particles of a full tile, of the fullest replica
+  for (const RepDev& R : s->reps) {
+    const double row = std::min(s->T, R.nc) / (double)R.nc;
+    most = std::max(most, row * row * R.n);
+  }
+  const int P = std::min(MAX_PARTS, std::max(1, (int)std::ceil(most / WG - 2e-4)));
+  const double last = most - (double)WG * (P - 1);
+  s->parts = s->nwork * P <= (last < WG / 4 ? 640 : 1280) ? P : 1;
 }
 
 int build_work(nem_sim* s) {
@@ -286,6 +310,7 @@ int build_work(nem_sim* s) {
   }
   if ((int)(w.size() / 2) > s->work_cap) { s->err = "work list larger than its buffer"; return NEM_E_INVAL; }
   s->nwork = (int)(w.size() / 2);
+  choose_parts(s);
   {
     // Full tiles first, the ragged edge tiles of boxes whose cell count is not
     // a multiple of T (fewer cells, less work) last, so that the end of each
@@ -1335,6 +1360,7 @@ int nem_set_option(nem_sim* s, int32_t key, int64_t value) {
       if (value < 0 || value > 2) return NEM_E_INVAL;
       drop_graphs(s);
       s->COMP = (int)value;
+      if (s->parts > 1) request_relist(s);   // the header's word counts are by part with COMP 1 only
       return NEM_OK;
     case NEM_OPT_TIMING:
       collect_times(s);

@@ -10,6 +10,7 @@ constexpr int WG = 256;          // threads per workgroup of every pair pass
 constexpr int MAXT = 8;          // largest tile side in cells
 constexpr int MAXSC = (MAXT + 2) * (MAXT + 2);  // staged cells per tile (interior + halo)
 constexpr int KMAX = 96;         // list capacity: entries per particle of the Verlet and direct-search lists
+constexpr int MAX_PARTS = 4;     // most workgroups that share a tile (words of the tile header)
 constexpr int UMAX_SLOTS = 64;   // per-replica slots of the max-speed reduction
 
 // Sticky device error bits (flags[0]).
@@ -67,6 +68,7 @@ struct StepArgs {
   int nwork, T;           // work items, tile side in cells
   int lpp;                // lanes per particle in passes B-D (1, 2, 4)
   int grid;               // 0: one workgroup per tile; > 0: persistent grid size
+  int parts;              // workgroups that share a tile's particles in passes A to D
   const int* hdr;         // tile headers (layout in nem_pair.h), one per work item
   const int* cell_start;  // [ncells + 1], particles sorted by (replica, cell, id)
   int ncells, ntot;

@@ -31,7 +31,8 @@ struct TileLDS {
 // Tile header, built by k_tile_headers whenever the cells or the tiles change
 // (new state, rebin, tile option, restored state) and read by every pair pass:
 //   {interior particles nin, staged particles S, ni | nj << 8 | over
-//   << 16, replica, most list words of a particle (HDR_WORDS, set by the Verlet build)}, padded to 8 ints;
+//   << 16, replica, most list words of a particle of each part of the tile
+//   (HDR_WORDS, set by the Verlet build; MAX_PARTS)};
 //   per interior row {global index - LDS slot, first LDS slot} (the cells of an
 //   interior row are contiguous in the sorted arrays);
 //   per staged cell {first global particle, first LDS slot | region x << 16 |
@@ -45,6 +46,7 @@ struct TileLDS {
 // waited for a load of its own.
 // A tile over the LDS capacity has nin = S = 0 (pass A raises ERR_OVERFLOW).
 constexpr int HDR_ROWS = 8, HDR_WORDS = 4;
+static_assert(MAX_PARTS <= HDR_ROWS - HDR_WORDS, "a word per part");
 template <int T>
 struct HdrCfg {
   static constexpr int NSC = (T + 2) * (T + 2);
@@ -367,10 +369,14 @@ template <int T>
 struct TileRef {
   ConstInt* H;
   int nin, S, ni, nj, rep, words;
+  int lo, hi;   // interior particles of this part
   bool over;
-  __device__ __forceinline__ TileRef(const StepArgs& a, int w) {
+  __device__ __forceinline__ TileRef(const StepArgs& a, int w, int part = 0, int parts = 1) {
     H = (ConstInt*)(a.hdr + (size_t)w * HdrCfg<T>::INTS);
-    nin = H[0]; S = H[1]; ni = H[2] & 255; nj = (H[2] >> 8) & 255; over = H[2] >> 16; rep = H[3]; words = H[HDR_WORDS];
+    nin = H[0]; S = H[1]; ni = H[2] & 255; nj = (H[2] >> 8) & 255; over = H[2] >> 16; rep = H[3];
+    words = H[HDR_WORDS + part];
+    lo = part * WG;
+    hi = part + 1 < parts ? min(lo + WG, nin) : nin;
   }
   __device__ __forceinline__ int2 cell(int c) const {
     return make_int2(H[HdrCfg<T>::CELLS + 2 * c], H[HdrCfg<T>::CELLS + 2 * c + 1]);

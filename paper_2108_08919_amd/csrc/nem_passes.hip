@@ -111,10 +111,10 @@ struct Lane {
   }
   // list = false: the lists are not built yet (pass A of a step that renews them)
   __device__ __forceinline__ void begin(const StepArgs& a, const TileRef<T>& t, int base, int base_lpp, bool list = true) {
-    lpp = lanes_for(t.nin - base, base_lpp);
+    lpp = lanes_for(t.hi - base, base_lpp);
     p = base + threadIdx.x / lpp;
     sub = threadIdx.x & (lpp - 1);
-    g = p < t.nin ? t.global(p) : -1;
+    g = p < t.hi ? t.global(p) : -1;
     nw = 0;
     vc = 0u;
     if (list) lists(a, t);
@@ -292,16 +292,16 @@ __device__ __forceinline__ void tile_pass_a(const StepArgs& a, int w) {
 // that need it only (every few thousand at the benchmark's speeds).
 template <int T, int KERN>
 __device__ __forceinline__ int build_list(const StepArgs& a, const TileRef<T>& t, ConstRep& R, const CellLDS<T>& L,
-                                       const int2* s_x, int w) {
+                                       const int2* s_x, int w, int part) {
   using F = ListFmt<T, KERN>;
   constexpr int EPW = F::EPW;
   __shared__ int most;
   if (threadIdx.x == 0) most = 0;
   __syncthreads();
   const int ni = t.ni, nint = t.ni * t.nj;
-  for (int base = 0; base < t.nin; base += WG) {
+  for (int base = t.lo; base < t.hi; base += WG) {
     const int p = base + threadIdx.x;
-    const bool act = p < t.nin;
+    const bool act = p < t.hi;
     int li = 0, lj = 0;
     int2 xi = make_int2(0, 0);
     if (act) {
@@ -371,30 +371,30 @@ __device__ __forceinline__ int build_list(const StepArgs& a, const TileRef<T>& t
   }
   __syncthreads();
   const int words = (most + EPW - 1) / EPW;
-  if (threadIdx.x == 0) ((int*)a.hdr)[(size_t)w * HdrCfg<T>::INTS + HDR_WORDS] = words;
+  if (threadIdx.x == 0) ((int*)a.hdr)[(size_t)w * HdrCfg<T>::INTS + HDR_WORDS + part] = words;
   return words;
 }
 
 // The list when this step renews it, then the volume over its entries.
 template <int T, int COMP, int KERN>
-__device__ __forceinline__ void tile_pass_a_step(const StepArgs& a, int w, bool renew) {
+__device__ __forceinline__ void tile_pass_a_step(const StepArgs& a, int w, int part, int parts, bool renew) {
   __shared__ CellLDS<T> L;
   __shared__ int2 s_x[TileCfg<T, KERN>::MAXP];
-  TileRef<T> t(a, w);
+  TileRef<T> t(a, w, part, parts);
   ConstRep& R = rep_of_tile(a, t.rep);
   Lane<T> l;
-  l.begin(a, t, 0, 1, !renew);
+  l.begin(a, t, t.lo, 1, !renew);
   if (t.over && threadIdx.x == 0) flag(a.flags, ERR_OVERFLOW);
   if (renew) tile_cells<T>(t, L);
   stage_tile<T, KERN>(t, [&](int g) { return a.off_cur[g]; },
                       [&](int j, int e, float2 o) { s_x[j] = fixed_position(R, o, e); });
   __syncthreads();
   if (renew) {
-    t.words = build_list<T, KERN>(a, t, R, L, s_x, w);
+    t.words = build_list<T, KERN>(a, t, R, L, s_x, w, part);
     l.lists(a, t);
   }
   const float hinv = R.hinv_fix;
-  for (int base = 0; base < t.nin;) {
+  for (int base = t.lo; base < t.hi;) {
     base += WG / l.lpp;
     const int g = l.g;
     const int2 xi = s_x[g >= 0 ? l.p : 0];
@@ -415,7 +415,7 @@ __device__ __forceinline__ void tile_pass_a_step(const StepArgs& a, int w, bool 
     }, [&]() { sw.end_cell(); });
     const float sum = wave_sum(sw.value(), l.lpp);
     if (g >= 0 && l.sub == 0) a.V[g] = 1.0f / (R.a2 * (kernel_w0_raw<KERN>() + sum));
-    if (base < t.nin) l.begin(a, t, base, 1);
+    if (base < t.hi) l.begin(a, t, base, 1);
   }
 }
 
@@ -424,7 +424,7 @@ __device__ __forceinline__ void tile_pass_a_step(const StepArgs& a, int w, bool 
 // Qzz = -Qxx - Qyy) with the printed I/3 in the co-rotation and the molecular
 // field; corrected momentum form without the lambda stress terms only.
 template <int T, int COMP, int FORM, int EL, int KERN, int Q3>
-__device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w) {
+__device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w, int part, int parts) {
   static_assert(Q3 == 0 || (FORM == 0 && EL == 0), "quasi-2D: corrected form, no lambda terms");
   constexpr int MP = TileCfg<T, KERN>::MAXP;
   __shared__ int2 s_x[MP];
@@ -433,11 +433,10 @@ __device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w) {
   __shared__ float s_V[MP];                  // V dW: V_j F = s_V[j] Fr
   __shared__ float s_rho[FORM == 1 ? MP : 1];
   __shared__ float s_qc[Q3 == 1 ? MP : 1];   // Qyy of the quasi-2D variant
-  const TileRef<T> t(a, w);
+  const TileRef<T> t(a, w, part, parts);
   ConstRep& R = rep_of_tile(a, t.rep);
-  const int nin = t.nin;
   Lane<T> l;
-  l.begin(a, t, 0, a.lpp);
+  l.begin(a, t, t.lo, a.lpp);
   const float hinv = R.hinv_fix;
   // grad_i W_ij = dWc F r_ij per unit of r for Wendland C2 (F = (1 - q/2)^3); the
   // quintic's F holds 1/r, in which the unit cancels
@@ -454,7 +453,7 @@ __device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w) {
     if constexpr (FORM == 1) s_rho[j] = R.rho0 + v.x;
   });
   __syncthreads();
-  for (int base = 0; base < nin;) {
+  for (int base = t.lo; base < t.hi;) {
     const int lpp = l.lpp, p = l.p, sub = l.sub, g = l.g;
     base += WG / lpp;
     const bool act = g >= 0;
@@ -642,22 +641,21 @@ __device__ __forceinline__ void tile_pass_b(const StepArgs& a, int w) {
         f[8] = drho_n * R.inv_rho0; f[9] = R.zeta;
       }
     }
-    if (base < nin) l.begin(a, t, base, a.lpp);
+    if (base < t.hi) l.begin(a, t, base, a.lpp);
   }
 }
 
 // ------------------------------------------------------------------ pass C
 template <int T, int COMP, int KERN>
-__device__ __forceinline__ void tile_pass_c(const StepArgs& a, int w) {
+__device__ __forceinline__ void tile_pass_c(const StepArgs& a, int w, int part, int parts) {
   constexpr int MP = TileCfg<T, KERN>::MAXP;
   __shared__ int2 s_x[MP];
   __shared__ float s_dh[MP];
   __shared__ float2 s_u[MP];
-  const TileRef<T> t(a, w);
+  const TileRef<T> t(a, w, part, parts);
   ConstRep& R = rep_of_tile(a, t.rep);
-  const int nin = t.nin;
   Lane<T> l;
-  l.begin(a, t, 0, a.lpp);
+  l.begin(a, t, t.lo, a.lpp);
   const float hinv = R.hinv_fix;
   struct In { float2 off, u; float dh; };
   stage_tile<T, KERN>(t, [&](int g) { return In{a.off_cur[g], a.u[g], a.dh[g]}; },
@@ -667,7 +665,7 @@ __device__ __forceinline__ void tile_pass_c(const StepArgs& a, int w) {
   for (int k = 0; k < UMAX_SLOTS; ++k) umb = max(umb, a.umax_cur[t.rep * UMAX_SLOTS + k]);
   const float c0 = R.c0_factor * __uint_as_float(umb);
   const float pc = R.rho0 * c0 * c0 / R.gamma_eos;
-  for (int base = 0; base < nin;) {
+  for (int base = t.lo; base < t.hi;) {
     const int lpp = l.lpp, p = l.p, sub = l.sub, g = l.g;
     base += WG / lpp;
     const bool act = g >= 0;
@@ -705,14 +703,14 @@ __device__ __forceinline__ void tile_pass_c(const StepArgs& a, int w) {
       a.drhat[g] = drh;
       a.uv[g] = sqrtf(wux * wux + wuy * wuy) * (R.a2 * Vi);
     }
-    if (base < nin) l.begin(a, t, base, a.lpp);
+    if (base < t.hi) l.begin(a, t, base, a.lpp);
   }
 }
 
 // ------------------------------------------------------------------ pass D
 // INTEG: corrector, 0 kick-drift-kick, 1 midpoint (the integrator parameter picks the variant at launch).
 template <int T, int COMP, int FORM, int EL, int KERN, int INTEG>
-__device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w) {
+__device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w, int part, int parts) {
   constexpr int MP = TileCfg<T, KERN>::MAXP;
   // FORM 0 stages V dWc (V_j F = V_j dWc Fr); without the lambda stress it also
   // stages P V dWc, so that (P_i + P_j) V_j F = (P_i V_j + PV_j) Fr.
@@ -722,11 +720,10 @@ __device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w) {
   __shared__ float2 s_VP[MP];     // {V dWc, P V dWc or P}
   __shared__ float2 s_pi[EL == 1 ? MP : 1];
   __shared__ float s_wmax[WG / 64];
-  const TileRef<T> t(a, w);
+  const TileRef<T> t(a, w, part, parts);
   ConstRep& R = rep_of_tile(a, t.rep);
-  const int nin = t.nin;
   Lane<T> l;
-  l.begin(a, t, 0, a.lpp);
+  l.begin(a, t, t.lo, a.lpp);
   const float hinv = R.hinv, cs = R.cs, R2 = R.R2;
   struct In { float2 off, pi; float V, P; };
   stage_tile<T, KERN>(t, [&](int g) {
@@ -741,7 +738,7 @@ __device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w) {
   __syncthreads();
   float umax_l = 0.0f;
   bool rebin = false, bad = false, relist = false;
-  for (int base = 0; base < nin;) {
+  for (int base = t.lo; base < t.hi;) {
     const int lpp = l.lpp, p = l.p, sub = l.sub, g = l.g;
     base += WG / lpp;
     const bool act = g >= 0;
@@ -863,7 +860,7 @@ __device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w) {
         rebin = true;
       if (!(isfinite(unx) && isfinite(uny) && isfinite(nh.x) && isfinite(nh.y) && isfinite(dn))) bad = true;
     }
-    if (base < nin) l.begin(a, t, base, a.lpp);
+    if (base < t.hi) l.begin(a, t, base, a.lpp);
   }
   // max speed: wave shuffles, LDS across waves, one atomic per workgroup into
   // one of UMAX_SLOTS slots of the replica (pass C takes the max of the slots)
@@ -993,8 +990,7 @@ void launch_free_energy(int T, int kern, const StepArgs& a, double* fe, hipStrea
 }
 
 // ---------------------------------------------------------- neighbour export
-// The pairs the pair passes sum over, decoded from the Verlet list exactly as
-// they walk it: which = 0 keeps the entries that pass the predicate
+// The pairs the pair passes sum over, from the Verlet list: which = 0 keeps the entries that pass the predicate
 // (neighbour(), pass D's own decision), which = 1 every entry of the list.
 // mode 0 counts the entries of each particle of replica rep_only into
 // cnt[id]; mode 1 writes the neighbours' ids from row_ptr[id] on.
@@ -1005,7 +1001,8 @@ __global__ __launch_bounds__(WG) void k_list_export(const StepArgs a, int rep_on
   __shared__ float2 s_off[MP];
   __shared__ float2 s_cell[MP];
   __shared__ int s_id[MP];
-  const TileRef<T> t(a, blockIdx.x);
+  TileRef<T> t(a, blockIdx.x);
+  t.words = KMAX / 2;
   if (t.rep != rep_only) return;
   ConstRep& R = rep_of_tile(a, t.rep);
   const int nin = t.nin;
@@ -1019,6 +1016,7 @@ __global__ __launch_bounds__(WG) void k_list_export(const StepArgs a, int rep_on
     l.p = p; l.lpp = 1; l.sub = 0; l.g = p < nin ? t.global(p) : -1;
     if (l.g < 0) continue;
     l.lists(a, t);
+    l.vc = vc_total(l.vc) | (uint32_t)KMAX << 24;   // every entry in the general form: the waves here are not the passes' own
     const int idi = s_id[p];
     if (idi < 0 || idi >= R.n) { flag(a.flags, ERR_RANGE); continue; }
     const float2 oi = s_off[p], ci = s_cell[p];
@@ -1040,17 +1038,22 @@ __global__ __launch_bounds__(WG) void k_list_export(const StepArgs a, int rep_on
 
 // ---------------------------------------------------------------- kernels
 // One workgroup per tile, or fewer workgroups looping over the tiles
-// (persistent launch: StepArgs::grid > 0).
+// (persistent launch: StepArgs::grid > 0). PARTS: blockIdx.y is the part of the tile
+// (choose_parts); without, the part is a constant, which a pass of the 64^2 box is
+// 0.6 us shorter for.
 template <int T, int COMP, int KERN>
 __global__ __launch_bounds__(WG) void k_pass_a(const StepArgs a) {
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_a<T, COMP, KERN>(a, w); __syncthreads(); }
 }
 // One kernel whether or not this step renews the list (the requests; a rebin
 // renews it too).
-template <int T, int COMP, int KERN>
+template <int T, int COMP, int KERN, bool PARTS>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_pass_a_step(const StepArgs a) {
   const bool renew = (a.req_cur[0] | a.req_cur[1]) != 0u;
-  for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_a_step<T, COMP, KERN>(a, w, renew); __syncthreads(); }
+  for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) {
+    tile_pass_a_step<T, COMP, KERN>(a, w, PARTS ? blockIdx.y : 0, PARTS ? a.parts : 1, renew);
+    __syncthreads();
+  }
 }
 
 // Occupancy targets (waves per SIMD) of the pair passes: more resident waves
@@ -1063,43 +1066,58 @@ struct Waves {
   static constexpr int D = ((T == 4 || KERN == 1) && EL == 0) ? 7 : 1;
 };
 
-template <int T, int COMP, int FORM, int EL, int KERN, int Q3>
+template <int T, int COMP, int FORM, int EL, int KERN, int Q3, bool PARTS>
 __global__ __launch_bounds__(WG)
 __attribute__((amdgpu_waves_per_eu(Q3 == 0 ? Waves<T, COMP, FORM, EL, KERN>::B : 1)))
 void k_pass_b(const StepArgs a) {
   // the max-speed slots that this step's pass D fills (last read by the
   // previous step's pass C)
   for (int i = blockIdx.x * WG + threadIdx.x; i < a.nrep * UMAX_SLOTS; i += gridDim.x * WG) a.umax_nxt[i] = 0u;
-  for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_b<T, COMP, FORM, EL, KERN, Q3>(a, w); __syncthreads(); }
+  for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) {
+    tile_pass_b<T, COMP, FORM, EL, KERN, Q3>(a, w, PARTS ? blockIdx.y : 0, PARTS ? a.parts : 1);
+    __syncthreads();
+  }
 }
-template <int T, int COMP, int KERN>
+template <int T, int COMP, int KERN, bool PARTS>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(Waves<T, COMP, 0, 0, KERN>::C)))
 void k_pass_c(const StepArgs a) {
   if (blockIdx.x == 0 && threadIdx.x < 2) a.req_cur[threadIdx.x] = 0u;   // served
-  for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_c<T, COMP, KERN>(a, w); __syncthreads(); }
+  for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) {
+    tile_pass_c<T, COMP, KERN>(a, w, PARTS ? blockIdx.y : 0, PARTS ? a.parts : 1);
+    __syncthreads();
+  }
 }
-template <int T, int COMP, int FORM, int EL, int KERN, int INTEG>
+template <int T, int COMP, int FORM, int EL, int KERN, int INTEG, bool PARTS>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(Waves<T, COMP, FORM, EL, KERN>::D)))
 void k_pass_d(const StepArgs a) {
-  for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_d<T, COMP, FORM, EL, KERN, INTEG>(a, w); __syncthreads(); }
+  for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) {
+    tile_pass_d<T, COMP, FORM, EL, KERN, INTEG>(a, w, PARTS ? blockIdx.y : 0, PARTS ? a.parts : 1);
+    __syncthreads();
+  }
 }
 
 // ------------------------------------------------------------- dispatch
-template <int T, int COMP, int FORM, int EL, int KERN>
+// PARTS only with the default compensation: with the others one workgroup takes a tile.
+template <int T, int COMP, int FORM, int EL, int KERN, bool PARTS>
 static void launch4(int pass, int q3, int integ, const StepArgs& a, hipStream_t s) {
-  const dim3 grid(a.grid > 0 ? std::min(a.grid, a.nwork) : a.nwork), block(WG);
+  if constexpr (COMP == 1 && !PARTS)
+    if (a.parts > 1 && pass != 1) return launch4<T, COMP, FORM, EL, KERN, true>(pass, q3, integ, a, s);
+  const int full = a.grid > 0 ? std::min(a.grid, a.nwork) : a.nwork;
+  const dim3 grid(full, PARTS ? a.parts : 1), block(WG);
   switch (pass) {
-    case 1: hipLaunchKernelGGL((k_pass_a<T, COMP, KERN>), grid, block, 0, s, a); break;
+    case 1:
+      if constexpr (!PARTS) hipLaunchKernelGGL((k_pass_a<T, COMP, KERN>), grid, block, 0, s, a);
+      break;
     case 2:
       if constexpr (FORM == 0 && EL == 0) {
-        if (q3) { hipLaunchKernelGGL((k_pass_b<T, COMP, 0, 0, KERN, 1>), grid, block, 0, s, a); break; }
+        if (q3) { hipLaunchKernelGGL((k_pass_b<T, COMP, 0, 0, KERN, 1, PARTS>), grid, block, 0, s, a); break; }
       }
-      hipLaunchKernelGGL((k_pass_b<T, COMP, FORM, EL, KERN, 0>), grid, block, 0, s, a);
+      hipLaunchKernelGGL((k_pass_b<T, COMP, FORM, EL, KERN, 0, PARTS>), grid, block, 0, s, a);
       break;
-    case 3: hipLaunchKernelGGL((k_pass_c<T, COMP, KERN>), grid, block, 0, s, a); break;
+    case 3: hipLaunchKernelGGL((k_pass_c<T, COMP, KERN, PARTS>), grid, block, 0, s, a); break;
     case 4:
-      if (integ) hipLaunchKernelGGL((k_pass_d<T, COMP, FORM, EL, KERN, 1>), grid, block, 0, s, a);
-      else hipLaunchKernelGGL((k_pass_d<T, COMP, FORM, EL, KERN, 0>), grid, block, 0, s, a);
+      if (integ) hipLaunchKernelGGL((k_pass_d<T, COMP, FORM, EL, KERN, 1, PARTS>), grid, block, 0, s, a);
+      else hipLaunchKernelGGL((k_pass_d<T, COMP, FORM, EL, KERN, 0, PARTS>), grid, block, 0, s, a);
       break;
   }
 }
@@ -1107,9 +1125,9 @@ static void launch4(int pass, int q3, int integ, const StepArgs& a, hipStream_t 
 template <int T, int COMP, int KERN>
 static bool launch_phys(int pass, const PassCfg& c, const StepArgs& a, hipStream_t s) {
   if (c.Q3 && (c.FORM != 0 || c.EL != 0)) return false;
-  if (c.FORM == 0 && c.EL == 0) { launch4<T, COMP, 0, 0, KERN>(pass, c.Q3, c.INTEG, a, s); return true; }
-  if (c.FORM == 1 && c.EL == 0) { launch4<T, COMP, 1, 0, KERN>(pass, c.Q3, c.INTEG, a, s); return true; }
-  if (c.FORM == 0 && c.EL == 1) { launch4<T, COMP, 0, 1, KERN>(pass, c.Q3, c.INTEG, a, s); return true; }
+  if (c.FORM == 0 && c.EL == 0) { launch4<T, COMP, 0, 0, KERN, false>(pass, c.Q3, c.INTEG, a, s); return true; }
+  if (c.FORM == 1 && c.EL == 0) { launch4<T, COMP, 1, 0, KERN, false>(pass, c.Q3, c.INTEG, a, s); return true; }
+  if (c.FORM == 0 && c.EL == 1) { launch4<T, COMP, 0, 1, KERN, false>(pass, c.Q3, c.INTEG, a, s); return true; }
   return false;
 }
 
@@ -1126,7 +1144,12 @@ static bool launch_comp(int pass, const PassCfg& c, const StepArgs& a, hipStream
 template <int T, int COMP, int KERN>
 static void launch_verlet(const StepArgs& a, hipStream_t s) {
   const int full = a.grid > 0 ? std::min(a.grid, a.nwork) : a.nwork;
-  hipLaunchKernelGGL((k_pass_a_step<T, COMP, KERN>), dim3(full), dim3(WG), 0, s, a);
+  if constexpr (COMP == 1)
+    if (a.parts > 1) {
+      hipLaunchKernelGGL((k_pass_a_step<T, COMP, KERN, true>), dim3(full, a.parts), dim3(WG), 0, s, a);
+      return;
+    }
+  hipLaunchKernelGGL((k_pass_a_step<T, COMP, KERN, false>), dim3(full), dim3(WG), 0, s, a);
 }
 
 template <int KERN>

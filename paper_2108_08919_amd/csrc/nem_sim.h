@@ -49,6 +49,7 @@ struct nem_sim {
   int parity = 0;
   std::vector<char> has_state;
   int T = 4, LPP = 1, COMP = 1;
+  int parts = 1;          // workgroups that share a tile (build_work)
   int persist = 0;        // > 0: persistent pass kernels with this many workgroups
   int graph_steps = 1;    // steps per captured graph
   int timing = 0;

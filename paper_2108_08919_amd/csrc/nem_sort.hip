@@ -109,7 +109,9 @@ __device__ void tile_header(const HdrArgs& h, int w) {
   const bool over = S > h.maxp;
   int* H = h.hdr + (size_t)w * h.ints;
   const int cells = HDR_ROWS + 2 * h.T;
-  if (c == 0) { H[0] = over ? 0 : nin; H[1] = over ? 0 : S; H[2] = ni | nj << 8 | (over ? 1 << 16 : 0); H[3] = rep; H[HDR_WORDS] = KMAX / 2; }
+  if (c == 0) { H[0] = over ? 0 : nin; H[1] = over ? 0 : S; H[2] = ni | nj << 8 | (over ? 1 << 16 : 0); H[3] = rep; 
+    for (int k = 0; k < MAX_PARTS; ++k) H[HDR_WORDS + k] = KMAX / 2;
+  }
   if (c < ni * nj && c % ni == 0) {   // first cell of an interior row
     H[HDR_ROWS + 2 * (c / ni)] = s0 - start;
     H[HDR_ROWS + 2 * (c / ni) + 1] = start;

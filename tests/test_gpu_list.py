@@ -121,3 +121,24 @@ def test_learned_steps_and_ordinary_ones_take_turns(tile, lpp, L, kw):
     assert all(np.array_equal(ga[k], gb[k]) for k in ga)
     for s in (a, b, r, z):
         s.close()
+
+
+# a tile shared by several workgroups: sides around the lines of the rule (275 and
+# 299 at T = 4, 537 and 559 at T = 8 of Wendland C2), tiles of four
+# rounds, and persistent grids of fewer workgroups than parts
+@pytest.mark.parametrize("kernel,L,tile,persist,lpp", [
+    (0, 275, 4, 0, 1), (0, 299, 4, 0, 1), (0, 97, 4, 0, 2), (0, 37, 4, 7, 4), (1, 537, 8, 0, 1), (1, 559, 8, 0, 1),
+    (1, 64, 8, 5, 2), (0, 45, 8, 0, 1), (0, 14, 8, 3, 4)])
+def test_shared_tiles_against_oracle(kernel, L, tile, persist, lpp):
+    """The bounds of test_list_against_oracle."""
+    import paper_2108_08919_amd as P
+    p = wl.Params(L=float(L), zeta=0.03, kernel=kernel)
+    s0 = random_state(L, 7, amp_u=2e-3)
+    print("shared", kernel, L, tile, persist, lpp, flush=True)
+    o, _ = run_oracle(p, s0, 2)
+    g, sim = gpu_run(p, s0, 2, {P.NEM_OPT_TILE: tile, P.NEM_OPT_PERSIST: persist, P.NEM_OPT_LPP: lpp})
+    e = field_errors(g, o, s0, L, 2)
+    for k in ("u", "Q", "rho", "pos"):
+        assert e[k] <= 1e-5, (k, e[k])
+    sim.check()
+    sim.close()
