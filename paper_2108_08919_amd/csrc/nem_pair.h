@@ -339,7 +339,7 @@ struct ListFmt {
   static constexpr int EPW = TileCfg<T, KERN>::MAXP <= 1024 ? 3 : 2;
   static constexpr int SH = EPW == 3 ? 10 : 16;
   static constexpr uint32_t MASK = (EPW == 3 ? 0x3FFu : 0xFFFu) << 3;
-    static constexpr int CHUNK = EPW == 3 ? 5 : 8;   // words per compensation chunk of pass B (15 or 16 pairs)
+  static constexpr int CHUNK = EPW == 3 ? 5 : 8;   // words per compensation chunk of pass B (15 or 16 pairs)
   static_assert(TileCfg<T, KERN>::MAXP <= 4096, "slot must fit its field");
   __device__ __forceinline__ static uint32_t pack(uint32_t slot, int i) { return slot << (SH * i); }
   __device__ __forceinline__ static uint32_t seal(uint32_t w) { return (w << 3) | (w >> 29); }
