@@ -348,14 +348,7 @@ HdrArgs hdr_args(nem_sim* s) {
 void build_headers(nem_sim* s) { launch_tile_headers(hdr_args(s), s->stream); }
 
 // The next step rebuilds the Verlet list.
-void request_relist(nem_sim* s) { launch_set_requests(s->flags, s->parity, 1, 1, s->stream); }
-
-// The steps that follow walk the list in this order; it is rebuilt if it is in the other one.
-void use_list_order(nem_sim* s, bool cells) {
-  if (s->cell_order == cells) return;
-  s->cell_order = cells;
-  request_relist(s);
-}
+void request_relist(nem_sim* s) { launch_set_requests(s->flags, s->parity, 1, 1, LIST_NONE, s->stream); }
 
 int read_flags(nem_sim* s, unsigned* f) {
   unsigned* to = s->pin_flags ? s->pin_flags : f;
@@ -853,7 +846,7 @@ int nem_step(nem_sim* s, int64_t nsteps) {
   if (!s || nsteps < 0) return NEM_E_INVAL;
   for (int r = 0; r < s->R; ++r)
     if (!s->has_state[r]) { s->err = "nem_set_state was not called for every replica"; return NEM_E_STATE; }
-  if (nsteps > 0) use_list_order(s, false);
+  s->cell_order = false;
   return run_steps(s, nsteps);
 }
 
@@ -928,7 +921,11 @@ int nem_save_raw(nem_sim* s, void* host, uint64_t bytes) {
   if (bytes < raw_total(s)) { s->err = "checkpoint buffer smaller than nem_raw_bytes"; return NEM_E_NOMEM; }
   char* b = (char*)host;
   std::memcpy(b, RAW_MAGIC, 8);
-  const int64_t hw[8] = {s->cell_order ? RAW_BY_CELL : RAW_BY_DISTANCE, s->R, s->ntot, s->ncells, s->parity, s->T, s->LPP, s->COMP};
+  unsigned fw[FLAG_WORDS];
+  HIPCHK(hipMemcpyAsync(fw, s->flags, sizeof(fw), hipMemcpyDeviceToHost, s->stream));
+  HIPCHK(hipStreamSynchronize(s->stream));
+  const int64_t hw[8] = {fw[FLAG_ORDER] == LIST_BY_CELL ? RAW_BY_CELL : RAW_BY_DISTANCE, s->R, s->ntot, s->ncells,
+                         s->parity, s->T, s->LPP, s->COMP};
   std::memcpy(b + 8, hw, sizeof(hw));
   char* w = b + 8 + sizeof(hw);
   for (int r = 0; r < s->R; ++r) {
@@ -937,10 +934,6 @@ int nem_save_raw(nem_sim* s, void* host, uint64_t bytes) {
     params_fields(s->hp[r], (double*)(w + 8), (int64_t*)(w + 8 + 8 * RAW_PD));
     w += 8 + 8 * RAW_PD + 8 * RAW_PI;
   }
-  HIPCHK(hipStreamSynchronize(s->stream));
-  unsigned fw[FLAG_WORDS];
-  HIPCHK(hipMemcpyAsync(fw, s->flags, sizeof(fw), hipMemcpyDeviceToHost, s->stream));
-  HIPCHK(hipStreamSynchronize(s->stream));
   const unsigned fs[4] = {fw[0], fw[FLAG_REQ + 2 * s->parity], fw[FLAG_REQ + 2 * s->parity + 1], 0u};
   for (const RawSeg& g : raw_segments(s)) {
     if (g.dev) HIPCHK(hipMemcpyAsync(w, g.dev, g.bytes, hipMemcpyDeviceToHost, s->stream));
@@ -995,7 +988,6 @@ int nem_load_raw(nem_sim* s, const void* host, uint64_t bytes) {
     if (rc) return rc;
   }
   s->parity = (int)hw[4];
-  s->cell_order = hw[0] == RAW_BY_CELL;
   unsigned fw[FLAG_WORDS] = {0};
   for (const RawSeg& g : raw_segments(s)) {
     if (g.dev) {
@@ -1006,6 +998,7 @@ int nem_load_raw(nem_sim* s, const void* host, uint64_t bytes) {
       fw[0] = fs[0];
       fw[FLAG_REQ + 2 * s->parity] = fs[1];
       fw[FLAG_REQ + 2 * s->parity + 1] = fs[2];
+      fw[FLAG_ORDER] = hw[0] == RAW_BY_CELL ? LIST_BY_CELL : LIST_BY_DISTANCE;
       HIPCHK(hipMemcpyAsync(s->flags, fw, sizeof(fw), hipMemcpyHostToDevice, s->stream));
     }
     w += g.bytes;
@@ -1026,13 +1019,13 @@ int nem_neighbor_list(nem_sim* s, int32_t r, int32_t which, int64_t* row_ptr, in
   if (!s->has_state[r]) return NEM_E_STATE;
   const int n = (int)s->n[r];
   // the next step's own start: rebin if requested, then the Verlet build or walk
-  use_list_order(s, false);
+  s->cell_order = false;
   const int timing = s->timing;
   s->timing = 0;
   int rc = enqueue_prologue(s, s->stream);
   s->timing = timing;
   if (rc) return rc;
-  launch_set_requests(s->flags, s->parity, 0, 0, s->stream);   // served: the next step walks this list
+  launch_set_requests(s->flags, s->parity, 0, 0, LIST_BY_DISTANCE, s->stream);   // served: the next step walks this list
   // counts, row pointers and offsets in the staging area (9 * max n doubles)
   char* st = (char*)s->stage;
   int* d_cnt = (int*)st;

@@ -23,10 +23,17 @@ enum : unsigned {
 
 // Device flag words: [0] sticky error bits; [2 + 2 p], [3 + 2 p] rebin and
 // Verlet rebuild requests of a step of parity p; [6] ticket of the rebin's
-// last workgroup (zero between rebins). Requests alternate with the parity, so
-// that no kernel has to clear them between one step's pass D and the next
-// step's rebin check.
-constexpr int FLAG_WORDS = 8, FLAG_REQ = 2, FLAG_TICKET = 6;
+// last workgroup (zero between rebins); [7] order of the Verlet list. Requests
+// alternate with the parity, so that no kernel has to clear them between one
+// step's pass D and the next step's rebin check.
+constexpr int FLAG_WORDS = 8, FLAG_REQ = 2, FLAG_TICKET = 6, FLAG_ORDER = 7;
+
+// Orders of the Verlet list: ordinary steps walk it by distance, learned macro
+// steps by cell (nem_passes_learn.hip). Pass A renews a list that is not in its
+// own order. The device keeps the order beside the list: a caller may capture
+// steps of one kind and replay them after steps of the other, which the host does
+// not see.
+enum : unsigned { LIST_NONE = 0u, LIST_BY_DISTANCE = 1u, LIST_BY_CELL = 2u };
 
 // One periodic box. All per-pair constants are FP32; csd and Ld keep the
 // double-precision geometry used when positions enter or leave the library.
@@ -153,7 +160,7 @@ void tile_header_shape(int T, int kern, int* maxp, int* ints);
 void launch_tile_headers(const HdrArgs& h, hipStream_t s);
 bool launch_pass_a_verlet(const PassCfg& c, const StepArgs& a, hipStream_t s);
 bool launch_pass_learn(int pass, const PassCfg& c, const StepArgs& a, hipStream_t s);
-void launch_set_requests(unsigned* flags, int parity, int keep_rebin, int relist, hipStream_t st);
+void launch_set_requests(unsigned* flags, int parity, int keep_rebin, int relist, unsigned order, hipStream_t st);
 void launch_list_export(int T, int kern, const StepArgs& a, int rep, int which, int mode, int* cnt,
                         const int64_t* row_ptr, int32_t* col, int64_t cap, hipStream_t s);
 void launch_export_offsets(const SortArgs& s, int r, int n, int* cxy, float* oxy, hipStream_t st);

@@ -679,7 +679,7 @@ static int samples_into(nem_sim* s, int32_t mult, float* X, float* T) {
   if (s->hp[0].q3d) { s->err = "the learned corrector covers the 2x2 Q only"; return NEM_E_INVAL; }
   for (int r = 0; r < s->R; ++r)
     if (!s->has_state[r]) return NEM_E_STATE;
-  use_list_order(s, true);
+  s->cell_order = true;
   int rc = take_snapshot(s);
   if (rc) return rc;
   float *coarse = nullptr, *xs = nullptr;
@@ -763,7 +763,7 @@ int nem_step_learned(nem_sim* s, nem_mlp* m, int64_t n_macro, int32_t mult, doub
   };
   int64_t nfb = 0;
   float worst = 0.0f;
-  if (!rc && n_macro > 0) use_list_order(s, true);
+  s->cell_order = true;
   if (!rc) rc = scale_dt(s, (float)mult);
   // Macro step k+1 is enqueued before the host looks at step k's norm, so the
   // device never waits for the host. If step k needs the fallback, step k+1

@@ -1045,11 +1045,11 @@ template <int T, int COMP, int KERN>
 __global__ __launch_bounds__(WG) void k_pass_a(const StepArgs a) {
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_a<T, COMP, KERN>(a, w); __syncthreads(); }
 }
-// One kernel whether or not this step renews the list (the requests; a rebin
-// renews it too).
+// One kernel whether or not this step renews the list (the requests, where a rebin
+// renews it too, or a list in the other order).
 template <int T, int COMP, int KERN, bool PARTS>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_pass_a_step(const StepArgs a) {
-  const bool renew = (a.req_cur[0] | a.req_cur[1]) != 0u;
+  const bool renew = (a.req_cur[0] | a.req_cur[1]) != 0u || a.flags[FLAG_ORDER] != LIST_BY_DISTANCE;
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) {
     tile_pass_a_step<T, COMP, KERN>(a, w, PARTS ? blockIdx.y : 0, PARTS ? a.parts : 1, renew);
     __syncthreads();
@@ -1082,6 +1082,7 @@ template <int T, int COMP, int KERN, bool PARTS>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(Waves<T, COMP, 0, 0, KERN>::C)))
 void k_pass_c(const StepArgs a) {
   if (blockIdx.x == 0 && threadIdx.x < 2) a.req_cur[threadIdx.x] = 0u;   // served
+  if (blockIdx.x == 0 && threadIdx.x == 2) a.flags[FLAG_ORDER] = LIST_BY_DISTANCE;
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) {
     tile_pass_c<T, COMP, KERN>(a, w, PARTS ? blockIdx.y : 0, PARTS ? a.parts : 1);
     __syncthreads();

@@ -626,16 +626,20 @@ __device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w) {
 
 
 // ------------------------------------------------------------- kernels
-// Gated on this step's requests (a rebin also renews the list): exactly one of
-// the two runs its tiles, the other exits at once.
+// Gated on whether this step renews the list (its requests, where a rebin also renews
+// it, or a list in the other order): exactly one of the two runs its tiles, the
+// other exits at once.
+__device__ __forceinline__ bool renew_list(const StepArgs& a) {
+  return (a.req_cur[0] | a.req_cur[1]) != 0u || a.flags[FLAG_ORDER] != LIST_BY_CELL;
+}
 template <int T, int COMP, int KERN>
 __global__ __launch_bounds__(WG) void k_learn_a_build(const StepArgs a) {
-  if ((a.req_cur[0] | a.req_cur[1]) == 0u) return;
+  if (!renew_list(a)) return;
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_a_build<T, COMP, KERN>(a, w); __syncthreads(); }
 }
 template <int T, int COMP, int KERN>
 __global__ __launch_bounds__(WG) void k_learn_a_walk(const StepArgs a) {
-  if ((a.req_cur[0] | a.req_cur[1]) != 0u) return;
+  if (renew_list(a)) return;
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_a_walk<T, COMP, KERN>(a, w); __syncthreads(); }
 }
 
@@ -659,6 +663,7 @@ template <int T, int COMP, int KERN>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(Waves<T, COMP, 0, 0, KERN>::C)))
 void k_learn_c(const StepArgs a) {
   if (blockIdx.x == 0 && threadIdx.x < 2) a.req_cur[threadIdx.x] = 0u;   // served
+  if (blockIdx.x == 0 && threadIdx.x == 2) a.flags[FLAG_ORDER] = LIST_BY_CELL;
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_c<T, COMP, KERN>(a, w); __syncthreads(); }
 }
 template <int T, int COMP, int FORM, int EL, int KERN, int INTEG>

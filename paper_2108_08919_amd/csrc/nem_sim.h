@@ -37,8 +37,8 @@ struct nem_sim {
   unsigned* flags = nullptr; unsigned* umax = nullptr;
   uint32_t* nl = nullptr; int* ncnt = nullptr; double* fe = nullptr;
   uint32_t* vl = nullptr; uint32_t* vcnt = nullptr; float2* off_build = nullptr;  // Verlet list
-  // Order of the Verlet list, and with it the passes that walk it: by distance
-  // (ordinary steps) or by cell (learned macro steps, nem_passes_learn.hip)
+  // The passes of the steps being enqueued walk the list by cell (learned macro steps,
+  // nem_passes_learn.hip) or by distance; set by every entry point that runs steps
   bool cell_order = false;
   double* stage = nullptr; int64_t stage_n = 0;
   double* red = nullptr;
@@ -118,7 +118,6 @@ int restore_snapshot(nem_sim* s, int i = 0);
 int build_work(nem_sim* s);
 void build_headers(nem_sim* s);
 void request_relist(nem_sim* s);
-void use_list_order(nem_sim* s, bool cells);
 void drop_graphs(nem_sim* s);
 
 }  // namespace nem_host

@@ -402,9 +402,10 @@ __global__ void k_gather(SortArgs s, int k0, int n, int c0, int nc) {
 
 // Requests of the next step (parity p): a Verlet rebuild when relist is set
 // (new state, tile change, restore), the rebin request kept or cleared; the
-// other parity's words are cleared.
-__global__ void k_set_requests(unsigned* flags, int p, int keep_rebin, int relist) {
+// other parity's words are cleared. order: of the list just built (LIST_NONE: as it was).
+__global__ void k_set_requests(unsigned* flags, int p, int keep_rebin, int relist, unsigned order) {
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
+  if (order != LIST_NONE) flags[FLAG_ORDER] = order;
   unsigned* req = flags + FLAG_REQ;
   if (!keep_rebin) req[2 * p] = 0u;
   req[2 * p + 1] = relist ? 1u : 0u;
@@ -628,8 +629,8 @@ void launch_sort_tail(const SortArgs& s, int k0, int n, int c0, int nc, int base
   hipLaunchKernelGGL(k_cellsort, dim3(grid_for(nc)), dim3(256), 0, st, s, c0, nc);
   hipLaunchKernelGGL(k_gather, dim3(grid_for(max(n, nc))), dim3(256), 0, st, s, k0, n, c0, nc);
 }
-void launch_set_requests(unsigned* flags, int parity, int keep_rebin, int relist, hipStream_t st) {
-  hipLaunchKernelGGL(k_set_requests, dim3(1), dim3(64), 0, st, flags, parity, keep_rebin, relist);
+void launch_set_requests(unsigned* flags, int parity, int keep_rebin, int relist, unsigned order, hipStream_t st) {
+  hipLaunchKernelGGL(k_set_requests, dim3(1), dim3(64), 0, st, flags, parity, keep_rebin, relist, order);
 }
 void launch_int_offsets(const SortArgs& s, float2* out, hipStream_t st) {
   hipLaunchKernelGGL(k_int_offsets, dim3(grid_for(s.ntot)), dim3(256), 0, st, s, out);

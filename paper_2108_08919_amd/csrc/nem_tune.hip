@@ -24,7 +24,7 @@ extern "C" int nem_autotune(nem_sim* s, int32_t steps, int32_t* tile, int32_t* l
   const int T0 = s->T, L0 = s->LPP, G0 = s->persist;
   int rc = take_snapshot(s);
   if (rc) return rc;
-  use_list_order(s, false);
+  s->cell_order = false;
   hipEvent_t e0, e1;
   HIPCHK(hipEventCreate(&e0));
   HIPCHK(hipEventCreate(&e1));

@@ -142,3 +142,46 @@ def test_shared_tiles_against_oracle(kernel, L, tile, persist, lpp):
         assert e[k] <= 1e-5, (k, e[k])
     sim.check()
     sim.close()
+
+
+@pytest.mark.parametrize("tile,lpp,L,kw", [(4, 1, 37, {}), (8, 2, 33, dict(kernel=1))])
+def test_captured_steps_replay_after_steps_of_the_other_kind(tile, lpp, L, kw):
+    """Ordinary steps captured by the caller, replayed before and after learned
+    ones: a replay runs the captured launches alone, so the device itself has to
+    see that the list is in the other order. Bit for bit the same calls made
+    eagerly, at each replay."""
+    import torch
+    import paper_2108_08919_amd as P
+    from paper_2108_08919_amd import learned
+    p = wl.Params(L=float(L), zeta=0.03, **kw)
+    s0 = random_state(L, 4, amp_u=2e-3)
+    print("captured", tile, lpp, L, kw, flush=True)
+    st = torch.cuda.Stream()
+    sims = []
+    with torch.cuda.stream(st):
+        for _ in range(2):
+            s = P.Sim([p], [L * L], stream=st)
+            s.set_option(P.NEM_OPT_TILE, tile)
+            s.set_option(P.NEM_OPT_LPP, lpp)
+            s.set_state(0, s0)
+            s.step(4)
+            s.check()
+            sims.append(s)
+        z = learned.zero_network()
+    a, b = sims
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st):
+        a.step(2)   # two steps: the buffers' parity after a replay is the one before it
+    for k in range(3):
+        with torch.cuda.stream(st):
+            g.replay()
+        b.step(2)
+        for s in (a, b):
+            s.check()
+        ga, gb = a.get_state(0), b.get_state(0)
+        assert all(np.array_equal(ga[f], gb[f]) for f in ga), k
+        for s in (a, b):
+            s.step_learned(z, 2, 4, 1.0)
+    for s in (a, b, z):
+        s.close()
