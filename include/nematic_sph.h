@@ -158,7 +158,8 @@ int nem_sync(nem_sim* s);
  *     NEM_E_INVAL when anything differs or the buffer is not a checkpoint,
  *     NEM_E_NOMEM when it is shorter than the checkpoint; the simulation is
  *     unchanged in those cases). It sets the saved options and drops captured
- *     graphs. The buffer is the caller's and is only read. */
+ *     graphs. A Verlet list that no build writes (a damaged file) is not walked:
+ *     the next step rebuilds it. The buffer is the caller's and is only read. */
 int nem_raw_bytes(nem_sim* s, uint64_t* bytes);
 int nem_save_raw(nem_sim* s, void* host, uint64_t bytes);
 int nem_load_raw(nem_sim* s, const void* host, uint64_t bytes);

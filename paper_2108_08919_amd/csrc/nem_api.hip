@@ -977,6 +977,21 @@ int nem_load_raw(nem_sim* s, const void* host, uint64_t bytes) {
   }
   // segment sizes depend on the sizes only, so the length is checked before anything changes
   if (bytes < raw_total(s)) { s->err = "nem_load_raw: buffer shorter than the checkpoint"; return NEM_E_NOMEM; }
+  // The passes index by the cell starts: they must be what a binning writes, ascending
+  // from 0 to ntot with every replica's particles in its own cells.
+  {
+    const char* c = w;
+    for (const RawSeg& g : raw_segments(s)) {
+      if (g.dev == s->cell_start) break;
+      c += g.bytes;
+    }
+    auto start = [&](int k) { int v; std::memcpy(&v, c + sizeof(int) * (size_t)k, sizeof(v)); return v; };
+    for (int k = 0; k < s->ncells; ++k)
+      if (start(k) > start(k + 1)) return bad("corrupt cell starts");
+    for (const RepDev& R : s->reps)
+      if (start(R.cell_base) != R.part_base) return bad("corrupt cell starts");
+    if (start(s->ncells) != s->ntot) return bad("corrupt cell starts");
+  }
   // the saved launch options and parity (the Verlet list's LDS slots follow the tile)
   drop_graphs(s);
   const int T = (int)hw[5];
@@ -1004,6 +1019,8 @@ int nem_load_raw(nem_sim* s, const void* host, uint64_t bytes) {
     w += g.bytes;
   }
   build_headers(s);
+  if (hw[0] == RAW_BY_DISTANCE) launch_list_check(s->T, s->hp[0].kernel, step_args(s), s->stream);
+  HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(s->stream));
   for (int r = 0; r < s->R; ++r) s->has_state[r] = 1;
   for (auto& sn : s->snap) sn.valid = false;

@@ -163,6 +163,7 @@ bool launch_pass_learn(int pass, const PassCfg& c, const StepArgs& a, hipStream_
 void launch_set_requests(unsigned* flags, int parity, int keep_rebin, int relist, unsigned order, hipStream_t st);
 void launch_list_export(int T, int kern, const StepArgs& a, int rep, int which, int mode, int* cnt,
                         const int64_t* row_ptr, int32_t* col, int64_t cap, hipStream_t s);
+void launch_list_check(int T, int kern, const StepArgs& a, hipStream_t s);
 void launch_export_offsets(const SortArgs& s, int r, int n, int* cxy, float* oxy, hipStream_t st);
 void launch_ingest(const SortArgs& s, int r, const double* in, int n, unsigned* umax, hipStream_t st);
 void launch_rebin(const SortArgs& s, const HdrArgs& h, hipStream_t st);

@@ -1036,6 +1036,32 @@ __global__ __launch_bounds__(WG) void k_list_export(const StepArgs a, int rep_on
   }
 }
 
+// ------------------------------------------------------- list of a checkpoint
+// The passes take a distance-ordered list as the build wrote it: they test neither
+// its slots nor its class bounds (a clamp is an instruction for every pair and
+// pass). A list that comes from a file is tested here, once: a particle whose
+// counts no build writes, or with a slot past the tile's staged particles, clears
+// the list's order, and the next step renews it.
+template <int T, int KERN>
+__global__ __launch_bounds__(WG) void k_list_check(const StepArgs a) {
+  using F = ListFmt<T, KERN>;
+  const TileRef<T> t(a, blockIdx.x);
+  for (int base = 0; base < t.nin; base += WG) {
+    const int p = base + threadIdx.x;   // a wave is a group of 64 consecutive particles
+    if (p >= t.nin) break;
+    const int g = t.global(p);
+    const uint32_t v = a.vcnt[g];
+    const int cnt = v & 255u, no = v >> 8 & 255u, nm = v >> 16 & 255u, most = v >> 24;
+    bool ok = cnt <= most && most <= KMAX && no <= nm && nm <= cnt && no % F::EPW == 0 && nm % F::EPW == 0 &&
+              v >> 8 == (uint32_t)__builtin_amdgcn_readfirstlane((int)v) >> 8;
+    for (int k = 0; ok && k < cnt; k += F::EPW) {
+      const uint32_t x = a.vl[(size_t)(k / F::EPW) * a.ntot + g];
+      for (int i = 0; i < F::EPW && k + i < cnt; ++i) ok &= (int)(F::at(x, i) >> 3) < t.S;
+    }
+    if (!ok) a.flags[FLAG_ORDER] = LIST_NONE;
+  }
+}
+
 // ---------------------------------------------------------------- kernels
 // One workgroup per tile, or fewer workgroups looping over the tiles
 // (persistent launch: StepArgs::grid > 0). PARTS: blockIdx.y is the part of the tile
@@ -1191,6 +1217,17 @@ void tile_header_shape(int T, int kern, int* maxp, int* ints) {
   *ints = T == 8 ? HdrCfg<8>::INTS : HdrCfg<4>::INTS;
   if (kern == 1) *maxp = T == 8 ? TileCfg<8, 1>::MAXP : TileCfg<4, 1>::MAXP;
   else *maxp = T == 8 ? TileCfg<8, 0>::MAXP : TileCfg<4, 0>::MAXP;
+}
+
+void launch_list_check(int T, int kern, const StepArgs& a, hipStream_t s) {
+  const dim3 grid(a.nwork), block(WG);
+  if (kern == 1) {
+    if (T == 8) hipLaunchKernelGGL((k_list_check<8, 1>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_list_check<4, 1>), grid, block, 0, s, a);
+  } else {
+    if (T == 8) hipLaunchKernelGGL((k_list_check<8, 0>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_list_check<4, 0>), grid, block, 0, s, a);
+  }
 }
 
 void launch_list_export(int T, int kern, const StepArgs& a, int rep, int which, int mode, int* cnt,

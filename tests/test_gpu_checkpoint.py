@@ -127,3 +127,74 @@ def test_fields_record_reads_back(tmp_path):
         for k in FIELDS:
             assert np.array_equal(rec[f"{k}_{r}"], g[k]), (r, k)
     a.close()
+
+
+@pytest.mark.parametrize("kernel,tile,damage", [(0, 4, "slots"), (0, 8, "slots"), (1, 8, "slots"), (1, 4, "counts"),
+                                                (0, 4, "counts"), (0, 8, "bounds")])
+def test_damaged_list_is_rebuilt(kernel, tile, damage):
+    """A checkpoint whose Verlet list was damaged loads, and its list is rebuilt:
+    bit for bit a rebuild forced by a launch option on the undamaged one."""
+    import paper_2108_08919_amd as P
+    L = 30
+    N = L * L
+    p = wl.Params(L=float(L), zeta=0.02, kernel=kernel)
+    a = _sim([p], [random_state(L, 6, amp_u=2e-3)], tile=tile)
+    a.step(3)
+    buf = a.save_raw()
+    bad = buf.copy()
+    cnt = bad[-8 * N - 4 * N:-8 * N].view(np.uint32)
+    words = bad[-8 * N - 4 * N - 4 * 48 * N:-8 * N - 4 * N].view(np.uint32).reshape(48, N)
+    if damage == "slots":
+        words[3, 5] = 0xFFFFFFFF      # the last entries of one particle's fourth word
+    elif damage == "counts":
+        cnt[7] = 0xFFFFFFFF
+    else:
+        cnt[:] += 1 << 8              # outer bounds that are no whole words
+    a.set_option(P.NEM_OPT_TILE, tile)
+    a.step(5)
+    ref = a.get_state(0)
+    print("damaged", kernel, tile, damage, flush=True)
+    b = P.Sim([p], [N])
+    b.load_raw(bad)
+    b.step(5)
+    b.check()
+    g = b.get_state(0)
+    for k in FIELDS:
+        assert np.array_equal(g[k], ref[k]), k
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("what", ["descending", "negative", "past the end", "replica"])
+def test_damaged_cell_starts_are_refused(what):
+    import paper_2108_08919_amd as P
+    params, states = _replicas()
+    a = _sim(params, states)
+    a.step(3)
+    buf = a.save_raw()
+    before = [a.get_state(r) for r in range(2)]
+    N, R = 32 * 32 + 24 * 24, 2
+    nc = [int(np.floor(p.L / (3 * p.h + p.skin))) for p in params]
+    C = sum(n * n for n in nc)
+    # header, then offsets, low parts, u, Q (8 bytes each), Qyy, a, rho, id, cell, image
+    o = 8 + 64 + R * (8 + 8 * 17 + 8 * 7) + N * (4 * 8 + 4 + 8 + 3 * 4 + 8)
+    bad = buf.copy()
+    cells = bad[o:o + 4 * (C + 1)].view(np.int32)
+    assert cells[0] == 0 and cells[-1] == N and cells[nc[0] ** 2] == 32 * 32
+    if what == "descending":
+        cells[3] = cells[5]
+        cells[4] = cells[2]
+    elif what == "negative":
+        cells[0] = -1
+    elif what == "past the end":
+        cells[-1] = N + 64
+    else:
+        cells[nc[0] ** 2] += 1
+    with pytest.raises(P.NemError) as e:
+        a.load_raw(bad)
+    assert e.value.code == P.NEM_E_INVAL
+    for r in range(2):
+        g = a.get_state(r)
+        for k in FIELDS:
+            assert np.array_equal(g[k], before[r][k]), (r, k)
+    a.close()
