@@ -358,20 +358,20 @@ int read_flags(nem_sim* s, unsigned* f) {
   return NEM_OK;
 }
 
-// Read-back of nf arrays of n doubles (contiguous at src) into the caller's
-// memory (dst[f], NULL: skipped). Pageable copies of the runtime wrote the caller's
+// Read-back of the arrays that the caller asks for (dst[f] not NULL) out of nf arrays
+// of n doubles (contiguous at src). Pageable copies of the runtime wrote the caller's
 // pages, most of them touched for the first time, from one thread: 9.5 GB/s, and 30
 // us for each array however small. Here the arrays go through PIN_SLOTS pinned
 // chunks, large enough that the cost of a copy (some 30 us) is small beside it, and
 // are written out in pieces by up to PIN_THREADS threads behind the copies, one a
-// megabyte. Below two megabytes it is one copy and one thread: starting threads
+// megabyte. Below two megabytes it is one chunk and one thread: starting threads
 // would cost more than they save.
 constexpr size_t PIN_CHUNK = 4 << 20, PIN_PIECE = 256 << 10, PIN_SMALL = 2 << 20;
-constexpr int PIN_SLOTS = 4, PIN_THREADS = 8;
+constexpr int PIN_THREADS = 8;
 
 void alloc_pin(nem_sim* s) {
   const size_t all = sizeof(double) * 9 * (size_t)s->stage_n;
-  s->pin_slots = (int)std::min<size_t>(PIN_SLOTS, (all + PIN_CHUNK - 1) / PIN_CHUNK);
+  s->pin_slots = (int)std::min<size_t>(nem_sim::PIN_SLOTS, (all + PIN_CHUNK - 1) / PIN_CHUNK);
   const size_t bytes = (std::min(all, PIN_CHUNK * s->pin_slots) + 63) / 64 * 64;
   if (hipHostMalloc((void**)&s->pin, bytes + 64, hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
@@ -382,49 +382,70 @@ void alloc_pin(nem_sim* s) {
 }
 
 void free_pin(nem_sim* s) {
-  for (hipEvent_t e : s->pin_ev) hipEventDestroy(e);
-  s->pin_ev.clear();
+  for (hipEvent_t& e : s->pin_ev) {
+    if (e) hipEventDestroy(e);
+    e = nullptr;
+  }
   if (s->pin) hipHostFree(s->pin);
   s->pin = nullptr;
   s->pin_flags = nullptr;
 }
 
 int copy_out(nem_sim* s, int nf, double* const* dst, const double* src, size_t n) {
-  const size_t fb = sizeof(double) * n, all = fb * nf;
-  if (s->pin && all <= PIN_SMALL) {   // within the first chunk, which holds nine arrays of the largest box or PIN_CHUNK
-    HIPCHK(hipMemcpyAsync(s->pin, src, all, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipStreamSynchronize(s->stream));
-    for (int f = 0; f < nf; ++f)
-      if (dst[f]) std::memcpy(dst[f], s->pin + fb * f, fb);
-    return NEM_OK;
-  }
-  while (s->pin && (int)s->pin_ev.size() < s->pin_slots) {
-    hipEvent_t e;
-    HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    s->pin_ev.push_back(e);
-  }
-  if (!s->pin) {
-    for (int f = 0; f < nf; ++f)
-      if (dst[f]) HIPCHK(hipMemcpyAsync(dst[f], src + n * f, fb, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipStreamSynchronize(s->stream));
-    return NEM_OK;
-  }
-  const int nc = (int)((all + PIN_CHUNK - 1) / PIN_CHUNK), slots = s->pin_slots;
-  const int np = (int)((all + PIN_PIECE - 1) / PIN_PIECE), per = (int)(PIN_CHUNK / PIN_PIECE);
-  std::vector<std::atomic<int>> left(nc);   // pieces of a chunk not yet written out
-  for (int c = 0; c < nc; ++c) left[c].store(std::min(per, np - c * per), std::memory_order_relaxed);
-  std::atomic<int> ready{0}, next{0};       // chunks that have arrived; pieces taken
-  std::atomic<bool> stop{false};
-  auto write = [&](int p) {
-    const int c = p / per;
-    const char* from = s->pin + PIN_CHUNK * (c % slots) + PIN_PIECE * (p % per);
-    for (size_t o = PIN_PIECE * p, end = std::min(all, o + PIN_PIECE); o < end;) {   // a piece may span two arrays
+  // the arrays asked for, back to back: byte o of the read is byte o % fb of array o / fb
+  struct { char* to; const char* from; } part[9];
+  int m = 0;
+  const size_t fb = sizeof(double) * n;
+  for (int f = 0; f < nf; ++f)
+    if (dst[f]) { part[m].to = (char*)dst[f]; part[m].from = (const char*)(src + n * f); ++m; }
+  const size_t all = fb * m;
+  // bytes [o, end) of the read into pinned memory, one copy for each run of neighbouring arrays
+  auto fetch = [&](char* to, size_t o, size_t end) {
+    hipError_t e = hipSuccess;
+    while (o < end && e == hipSuccess) {
+      size_t f = o / fb;
+      const char* from = part[f].from + (o - f * fb);
+      size_t stop = (f + 1) * fb;
+      for (; stop < end && part[f + 1].from == part[f].from + fb; ++f) stop += fb;
+      const size_t k = std::min(end, stop) - o;
+      e = hipMemcpyAsync(to, from, k, hipMemcpyDeviceToHost, s->stream);
+      to += k;
+      o += k;
+    }
+    return e;
+  };
+  // bytes [o, end) from pinned memory to the caller
+  auto spread = [&](const char* from, size_t o, size_t end) {
+    while (o < end) {
       const size_t f = o / fb, k = std::min(end, (f + 1) * fb) - o;
-      if (dst[f]) std::memcpy((char*)dst[f] + (o - f * fb), from, k);
+      std::memcpy(part[f].to + (o - f * fb), from, k);
       from += k;
       o += k;
     }
-    left[c].fetch_sub(1, std::memory_order_release);
+  };
+  if (!s->pin) {
+    for (int f = 0; f < m; ++f) HIPCHK(hipMemcpyAsync(part[f].to, part[f].from, fb, hipMemcpyDeviceToHost, s->stream));
+    HIPCHK(hipStreamSynchronize(s->stream));
+    return NEM_OK;
+  }
+  if (all <= PIN_SMALL) {   // within the first chunk, which holds nine arrays of the largest box or PIN_CHUNK
+    HIPCHK(fetch(s->pin, 0, all));
+    HIPCHK(hipStreamSynchronize(s->stream));
+    spread(s->pin, 0, all);
+    return NEM_OK;
+  }
+  const int slots = s->pin_slots;
+  for (int k = 0; k < slots; ++k)
+    if (!s->pin_ev[k]) HIPCHK(hipEventCreateWithFlags(&s->pin_ev[k], hipEventDisableTiming));
+  const int nc = (int)((all + PIN_CHUNK - 1) / PIN_CHUNK);
+  const int np = (int)((all + PIN_PIECE - 1) / PIN_PIECE), per = (int)(PIN_CHUNK / PIN_PIECE);
+  std::atomic<int> left[nem_sim::PIN_SLOTS] = {};   // pieces of the chunk in a slot not yet written out
+  std::atomic<int> ready{0}, next{0};               // chunks that have arrived; pieces taken
+  std::atomic<bool> stop{false};
+  auto write = [&](int p) {
+    const int k = p / per % slots;
+    spread(s->pin + PIN_CHUNK * k + PIN_PIECE * (p % per), PIN_PIECE * p, std::min(all, PIN_PIECE * (p + (size_t)1)));
+    left[k].fetch_sub(1, std::memory_order_release);
   };
   auto work = [&]() {
     for (int p = next++; p < np; p = next++) {
@@ -434,10 +455,11 @@ int copy_out(nem_sim* s, int nf, double* const* dst, const double* src, size_t n
       write(p);
     }
   };
-  std::vector<std::thread> pool;
+  std::thread pool[PIN_THREADS];
+  int threads = 0;
   try {
     const int want = (int)std::min<size_t>(PIN_THREADS, all >> 20);
-    for (int t = 0; t < want; ++t) pool.emplace_back(work);
+    for (; threads < want; ++threads) pool[threads] = std::thread(work);
   } catch (...) {
     // as many as there are; with none, this thread writes
   }
@@ -445,20 +467,21 @@ int copy_out(nem_sim* s, int nf, double* const* dst, const double* src, size_t n
   int sent = 0;
   for (int c = 0; c < nc && e == hipSuccess; ++c) {
     for (; sent < nc && sent < c + slots && e == hipSuccess; ++sent) {
-      while (sent >= slots && left[sent - slots].load(std::memory_order_acquire)) std::this_thread::yield();
+      const int k = sent % slots;
+      while (left[k].load(std::memory_order_acquire)) std::this_thread::yield();
+      left[k].store(std::min(per, np - sent * per), std::memory_order_relaxed);   // seen by a thread that has seen ready
       const size_t o = PIN_CHUNK * sent;
-      e = hipMemcpyAsync(s->pin + PIN_CHUNK * (sent % slots), (const char*)src + o, std::min(PIN_CHUNK, all - o),
-                         hipMemcpyDeviceToHost, s->stream);
-      if (e == hipSuccess) e = hipEventRecord(s->pin_ev[sent % slots], s->stream);
+      e = fetch(s->pin + PIN_CHUNK * k, o, std::min(all, o + PIN_CHUNK));
+      if (e == hipSuccess) e = hipEventRecord(s->pin_ev[k], s->stream);
     }
     if (e == hipSuccess) e = hipEventSynchronize(s->pin_ev[c % slots]);
     if (e != hipSuccess) break;
     ready.store(c + 1, std::memory_order_release);
-    if (pool.empty())
+    if (!threads)
       for (int p = c * per; p < std::min(np, (c + 1) * per); ++p) write(p);
   }
   if (e != hipSuccess) stop.store(true);
-  for (auto& t : pool) t.join();
+  for (int t = 0; t < threads; ++t) pool[t].join();
   if (e != hipSuccess) return hip_fail(s, e, "read-back");
   return NEM_OK;
 }

@@ -45,7 +45,8 @@ struct nem_sim {
   // pinned host memory that results are read back through: PIN_SLOTS chunks (fewer
   // for small boxes), then the flag words; NULL: none could be had
   char* pin = nullptr; unsigned* pin_flags = nullptr; int pin_slots = 0;
-  std::vector<hipEvent_t> pin_ev;
+  static constexpr int PIN_SLOTS = 4;
+  hipEvent_t pin_ev[PIN_SLOTS] = {};
   int parity = 0;
   std::vector<char> has_state;
   int T = 4, LPP = 1, COMP = 1;
