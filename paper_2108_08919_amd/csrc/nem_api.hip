@@ -457,12 +457,6 @@ int copy_out(nem_sim* s, int nf, double* const* dst, const double* src, size_t n
   };
   std::thread pool[PIN_THREADS];
   int threads = 0;
-  try {
-    const int want = (int)std::min<size_t>(PIN_THREADS, all >> 20);
-    for (; threads < want; ++threads) pool[threads] = std::thread(work);
-  } catch (...) {
-    // as many as there are; with none, this thread writes
-  }
   hipError_t e = hipSuccess;
   int sent = 0;
   for (int c = 0; c < nc && e == hipSuccess; ++c) {
@@ -476,6 +470,12 @@ int copy_out(nem_sim* s, int nf, double* const* dst, const double* src, size_t n
     }
     if (e == hipSuccess) e = hipEventSynchronize(s->pin_ev[c % slots]);
     if (e != hipSuccess) break;
+    if (c == 0) try {   // not before: the stream may have steps of minutes ahead of the first chunk
+      const int want = (int)std::min<size_t>(PIN_THREADS, all >> 20);
+      for (; threads < want; ++threads) pool[threads] = std::thread(work);
+    } catch (...) {
+      // as many as there are; with none, this thread writes
+    }
     ready.store(c + 1, std::memory_order_release);
     if (!threads)
       for (int p = c * per; p < std::min(np, (c + 1) * per); ++p) write(p);

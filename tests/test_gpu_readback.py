@@ -73,3 +73,29 @@ def test_two_arrays_cost_less_than_nine():
     print("nine", nine, "two", two, flush=True)
     assert two < 0.6 * nine
     sim.close()
+
+
+def test_waiting_for_queued_steps_takes_no_pool_of_threads():
+    """A read waits for the steps enqueued before it on the calling thread alone: the
+    process's processor time stays near that of one waiting thread, where eight
+    writers that wait for their first chunk took eight times the wall time."""
+    import paper_2108_08919_amd as P
+    L = 512
+    n = L * L
+    sim = P.Sim([wl.Params(L=float(L))], [n])
+    sim.set_state(0, random_state(L, 3))
+    out = {k: np.zeros(n) for k in FIELDS}
+    sim.step(100)
+    _read(sim, n, FIELDS, out)
+    # steps replayed from a graph, so that they are all enqueued when the read begins
+    sim.set_option(P.NEM_OPT_GRAPH, 250)
+    sim.step(250)
+    sim.check()
+    sim.step(5000)
+    c0, t0 = time.process_time(), time.perf_counter()
+    _read(sim, n, FIELDS, out)
+    cpu, wall = time.process_time() - c0, time.perf_counter() - t0
+    print("wall", wall, "processor", cpu, flush=True)
+    assert wall > 0.1   # the read did wait
+    assert cpu < 2.0 * wall
+    sim.close()
