@@ -391,7 +391,9 @@ __device__ __forceinline__ void tile_pass_a_step(const StepArgs& a, int w, int p
   __syncthreads();
   if (renew) {
     t.words = build_list<T, KERN>(a, t, R, L, s_x, w, part);
-    l.lists(a, t);
+    Lane<T> n;   // a new one: l's words would hold their registers through the build
+    n.begin(a, t, t.lo, 1);
+    l = n;
   }
   const float hinv = R.hinv_fix;
   for (int base = t.lo; base < t.hi;) {
@@ -1074,7 +1076,8 @@ __global__ __launch_bounds__(WG) void k_pass_a(const StepArgs a) {
 // One kernel whether or not this step renews the list (the requests, where a rebin
 // renews it too, or a list in the other order).
 template <int T, int COMP, int KERN, bool PARTS>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_pass_a_step(const StepArgs a) {
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(T == 8 && KERN == 0 ? 7 : 8)))
+void k_pass_a_step(const StepArgs a) {
   const bool renew = (a.req_cur[0] | a.req_cur[1]) != 0u || a.flags[FLAG_ORDER] != LIST_BY_DISTANCE;
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) {
     tile_pass_a_step<T, COMP, KERN>(a, w, PARTS ? blockIdx.y : 0, PARTS ? a.parts : 1, renew);
@@ -1083,8 +1086,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(8))) void k_
 }
 
 // Occupancy targets (waves per SIMD) of the pair passes: more resident waves
-// hide the LDS and list latency in each pair's dependency chain; the targets
-// are the largest that compile without register spills for the variant.
+// hide the LDS and list latency in each pair's dependency chain; at its target
+// no variant spills vector registers (nor does pass A at 8, or 7 with the 8 x 8
+// tile of the quintic).
 template <int T, int COMP, int FORM, int EL, int KERN>
 struct Waves {
   static constexpr int B = ((T == 4 || KERN == 1) && (COMP == 0 || (COMP == 1 && FORM == 0))) ? 5 : 1;

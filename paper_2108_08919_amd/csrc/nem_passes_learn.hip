@@ -643,12 +643,12 @@ __global__ __launch_bounds__(WG) void k_learn_a_walk(const StepArgs a) {
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) { tile_pass_a_walk<T, COMP, KERN>(a, w); __syncthreads(); }
 }
 
-// Waves per SIMD: the most that compile without register spills for the variant.
+// Waves per SIMD, for which no variant spills vector registers.
 template <int T, int COMP, int FORM, int EL, int KERN>
 struct Waves {
   static constexpr int B = ((T == 4 || KERN == 1) && (COMP == 0 || (COMP == 1 && FORM == 0))) ? 5 : 1;
-  static constexpr int C = 8;
-  static constexpr int D = ((T == 4 || KERN == 1) && EL == 0) ? 8 : 1;
+  static constexpr int C = T == 8 && KERN == 1 ? 7 : 8;
+  static constexpr int D = (T == 4 || KERN == 1) && EL == 0 ? (T == 4 && KERN == 0 && FORM == 1 && COMP > 0 ? 7 : 8) : 1;
 };
 
 template <int T, int COMP, int FORM, int EL, int KERN>
