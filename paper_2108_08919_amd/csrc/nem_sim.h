@@ -46,7 +46,7 @@ struct nem_sim {
   // for small boxes), then the flag words; NULL: none could be had
   char* pin = nullptr; unsigned* pin_flags = nullptr; int pin_slots = 0;
   static constexpr int PIN_SLOTS = 4;
-  hipEvent_t pin_ev[PIN_SLOTS] = {};
+  hipEvent_t pin_ev[PIN_SLOTS] = {}, pin_begin = nullptr;
   int parity = 0;
   std::vector<char> has_state;
   int T = 4, LPP = 1, COMP = 1;
