@@ -99,15 +99,15 @@ struct Lane {
   int nw;               // list words this lane may have
   uint32_t vc;
   u32x16 w;
-  // word i of this lane: word sub + i lpp of the list (row m of it at vl + m ntot)
-  __device__ __forceinline__ uint32_t word(const StepArgs& a, int i) const {
-    if (lpp == 1) return (a.vl + (size_t)i * (size_t)a.ntot)[(uint32_t)g];
-    return (a.vl + (size_t)(sub + i * lpp) * (size_t)a.ntot)[(uint32_t)g];
-  }
+  // word i of this lane: word sub + i lpp of the list (row m of it at vl + m ntot). The
+  // address runs: a product for each row may be a multiply-add that reads the register
+  // beside sub, and waits for the load that is in flight to it.
   __device__ __forceinline__ void load(const StepArgs& a, int i0) {
+    const size_t stride = (size_t)lpp * (size_t)a.ntot;
+    const uint32_t* q = a.vl + (size_t)sub * (size_t)a.ntot + (size_t)i0 * stride + (uint32_t)g;
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (i0 + i < nw) w[i] = word(a, i0 + i);
+    for (int i = 0; i < 16; ++i, q += stride)
+      if (i0 + i < nw) w[i] = *q;
   }
   // list = false: the lists are not built yet (pass A of a step that renews them)
   __device__ __forceinline__ void begin(const StepArgs& a, const TileRef<T>& t, int base, int base_lpp, bool list = true) {
@@ -1078,7 +1078,7 @@ __global__ __launch_bounds__(WG) void k_pass_a(const StepArgs a) {
 template <int T, int COMP, int KERN, bool PARTS>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(T == 8 && KERN == 0 ? 7 : 8)))
 void k_pass_a_step(const StepArgs a) {
-  const bool renew = (a.req_cur[0] | a.req_cur[1]) != 0u || a.flags[FLAG_ORDER] != LIST_BY_DISTANCE;
+  const bool renew = (a.req_cur[0] | a.req_cur[1] | (a.flags[FLAG_ORDER] ^ LIST_BY_DISTANCE)) != 0u;   // loaded together
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) {
     tile_pass_a_step<T, COMP, KERN>(a, w, PARTS ? blockIdx.y : 0, PARTS ? a.parts : 1, renew);
     __syncthreads();

@@ -630,7 +630,7 @@ __device__ __forceinline__ void tile_pass_d(const StepArgs& a, int w) {
 // it, or a list in the other order): exactly one of the two runs its tiles, the
 // other exits at once.
 __device__ __forceinline__ bool renew_list(const StepArgs& a) {
-  return (a.req_cur[0] | a.req_cur[1]) != 0u || a.flags[FLAG_ORDER] != LIST_BY_CELL;
+  return (a.req_cur[0] | a.req_cur[1] | (a.flags[FLAG_ORDER] ^ LIST_BY_CELL)) != 0u;   // loaded together
 }
 template <int T, int COMP, int KERN>
 __global__ __launch_bounds__(WG) void k_learn_a_build(const StepArgs a) {
