@@ -106,7 +106,8 @@ struct StepArgs {
   const unsigned* umax_cur;  // [R][UMAX_SLOTS]: max |u^{n+1/2}| (float bits)
   unsigned* umax_nxt;        // [R][UMAX_SLOTS]: max |u^{n+3/2}| being accumulated
   uint32_t* nl;              // neighbour list of the direct search (diagnostics): word w of particle g
-                             // at nl[w*ntot + g], two 16-bit entries (LDS slot | (dx+1)<<12 | (dy+1)<<14)
+                             // at nl[w*ntot + g], two 16-bit entries (LDS slot | (dx+1)<<12 | (dy+1)<<14);
+                             // scratch of the Verlet build
   int* ncnt;                 // its length per particle
   float* feat;               // NULL, or 12 features per particle at [g] (storage order)
   uint32_t* vl;              // Verlet list (pairs within the Verlet radius at the last build): word w of

@@ -286,10 +286,17 @@ __device__ __forceinline__ void tile_pass_a(const StepArgs& a, int w) {
 // by the rebin criterion. The same margin keeps outer pairs (beyond 2h + delta
 // at the build) at q > 2 and middle pairs (beyond h + delta) at q > 1.
 
-// Build: one sweep over the ~144 candidates of the stencil counts the classes,
-// then one sweep per class writes its entries in cell order. Returns the most
-// list words of a particle of the tile (kept in the header). Runs on the steps
-// that need it only (every few thousand at the benchmark's speeds).
+// Build: one sweep over the ~144 candidates of the stencil records, per cell and
+// distance class, the listed ones as a mask; then all lanes take their k-th entry
+// of a class together, in cell order, so that a list word is stored by the whole
+// wave at once. The masks wait in nl, which only the diagnostics use, and come back
+// nine registers for a class (in LDS they took a workgroup in five from the walk of
+// the quintic's 8 x 8 tiles). A sweep per class that appended what it found, its
+// lanes storing each at its own candidate, took 76 us on the 64^2 box and 1.03 ms on
+// the 2048^2 one; this takes 41 us and 0.59 ms. Returns the most list words of a
+// particle of the tile (kept in the header). Runs on the steps that need it only
+// (every few thousand at the benchmark's speeds, and on every change between
+// ordinary and learned steps).
 template <int T, int KERN>
 __device__ __forceinline__ int build_list(const StepArgs& a, const TileRef<T>& t, ConstRep& R, const CellLDS<T>& L,
                                        const int2* s_x, int w, int part) {
@@ -298,9 +305,12 @@ __device__ __forceinline__ int build_list(const StepArgs& a, const TileRef<T>& t
   __shared__ int most;
   if (threadIdx.x == 0) most = 0;
   __syncthreads();
-  const int ni = t.ni, nint = t.ni * t.nj;
+  const int ni = t.ni, nint = t.ni * t.nj, tid = threadIdx.x;
+  const size_t ntot = (size_t)a.ntot;
+  uint32_t* const nl = a.nl;
+  unsigned* const flags = a.flags;
   for (int base = t.lo; base < t.hi; base += WG) {
-    const int p = base + threadIdx.x;
+    const int p = base + tid;
     const bool act = p < t.hi;
     int li = 0, lj = 0;
     int2 xi = make_int2(0, 0);
@@ -309,62 +319,105 @@ __device__ __forceinline__ int build_list(const StepArgs& a, const TileRef<T>& t
       li = st % ni; lj = st / ni;
       xi = s_x[p];
     }
-    // visit(slot, r2) of every listed candidate, in cell order
-    auto sweep = [&](auto&& visit) {
-#pragma unroll 1
-      for (int q = 0; q < 9; ++q) {
-        const int sc = L.slot[(lj + q / 3) * (ni + 2) + (li + q % 3)];
-        const int j0 = L.start[sc], n = min(L.start[sc + 1] - j0, CELL_MAX);
-#pragma unroll 1
-        for (int j = j0; j < j0 + n; ++j) {
-          const float r2 = fixed_pair(xi, s_x[j]).r2;
-          if (r2 < R.R2v_fix && j != p) visit(j, r2);
-        }
-      }
-    };
-    int all = 0, no = 0, nm = 0;   // listed; outer; outer and middle
+    const int g = act ? t.global(p) : 0;
+    auto cell = [&](int q) { return L.slot[(lj + q / 3) * (ni + 2) + (li + q % 3)]; };
+    // row r of the lane's masks in nl: 9 class + q, candidates 0-31 of cell q; for cells
+    // with more, 27 + q the outer and middle ones and 36 + q the inner ones of candidates 32-47
+    auto kept_mask = [&](int r) -> uint32_t& { return (nl + (size_t)r * ntot)[(uint32_t)g]; };
+    int all = 0, no = 0, nm = 0;   // listed; outer; middle
     bool big = false;
     if (act) {
+      // masks of the candidates j0..j0 + n of a cell, n <= 32; reads up to three records further
+      auto sweep = [&](int j0, int n, uint32_t& mo, uint32_t& mm, uint32_t& mi) {
+        mo = mm = mi = 0u;
+#pragma unroll 1
+        for (int b = 0; b < n; b += 4) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const float r2 = fixed_pair(xi, s_x[j0 + b + u]).r2;
+            const uint32_t bit = 1u << (b + u);
+            mi |= r2 < R.R2v_fix ? bit : 0u;
+            mm |= r2 > R.R2m_fix ? bit : 0u;
+            mo |= r2 > R.R2o_fix ? bit : 0u;
+          }
+        }
+        mi &= 0xFFFFFFFFu >> (32 - n);   // n > 0
+        const uint32_t self = (uint32_t)(p - j0);
+        if (self < 32u) mi &= ~(1u << self);
+        mo &= mi;
+        mm &= mi & ~mo;
+        mi &= ~(mo | mm);
+        no += __popc(mo);
+        nm += __popc(mm);
+        all += __popc(mo) + __popc(mm) + __popc(mi);
+      };
 #pragma unroll 1
       for (int q = 0; q < 9; ++q) {
-        const int sc = L.slot[(lj + q / 3) * (ni + 2) + (li + q % 3)];
-        big |= L.start[sc + 1] - L.start[sc] > CELL_MAX;
+        const int sc = cell(q), j0 = L.start[sc], n = L.start[sc + 1] - j0;
+        big |= n > CELL_MAX;
+        uint32_t mo = 0u, mm = 0u, mi = 0u;
+        if (n > 0) sweep(j0, min(n, 32), mo, mm, mi);
+        kept_mask(q) = mo;
+        kept_mask(9 + q) = mm;
+        kept_mask(18 + q) = mi;
+        if (n > 32) {
+          sweep(j0 + 32, min(n, CELL_MAX) - 32, mo, mm, mi);
+          kept_mask(27 + q) = mo | mm << 16;
+          kept_mask(36 + q) = mi;
+        }
       }
-      sweep([&](int, float r2) {
-        ++all;
-        no += r2 > R.R2o_fix;
-        nm += r2 > R.R2m_fix;
-      });
-      if (all > KMAX || big) flag(a.flags, ERR_OVERFLOW);
+      if (all > KMAX || big) flag(flags, ERR_OVERFLOW);
     }
     const int kept = min(all, KMAX);
     // what every particle of the wave can take in a class, and the most entries
-    int go = act ? min(no, kept) / EPW * EPW : 255, gm = act ? min(nm, kept) / EPW * EPW : 255, gx = kept;
+    int go = act ? min(no, kept) / EPW * EPW : 255, gm = act ? min(no + nm, kept) / EPW * EPW : 255, gx = kept;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
       go = min(go, __shfl_xor(go, o, 64));
       gm = min(gm, __shfl_xor(gm, o, 64));
       gx = max(gx, __shfl_xor(gx, o, 64));
     }
-    if ((threadIdx.x & 63) == 0) atomicMax(&most, gx);
+    if ((tid & 63) == 0) atomicMax(&most, gx);
     if (!act) continue;
-    const int g = t.global(p);
     uint32_t* dst = a.vl + g;
     uint32_t word = 0u;
     int k = 0, i = 0;
 #pragma unroll 1
-    for (int cl = OUTER; cl <= INNER; ++cl)
-      sweep([&](int j, float r2) {
-        if (cl != (r2 > R.R2o_fix ? OUTER : (r2 > R.R2m_fix ? MIDDLE : INNER)) || k >= KMAX) return;
-        word |= F::pack((uint32_t)j, i);
+    for (int cl = OUTER; cl <= INNER; ++cl) {
+      uint32_t cells[9];   // this class's masks of the cells still to come, the next one first
+#pragma unroll
+      for (int q = 0; q < 9; ++q) cells[q] = kept_mask(9 * cl + q);
+      const int end = min(k + (cl == OUTER ? no : (cl == MIDDLE ? nm : all - no - nm)), KMAX);
+      int q = -1, j0 = 0;
+      bool high = false;   // the cell has candidates past the 32nd, still to come
+      uint32_t m = 0u;
+      while (k < end) {
+        while (m == 0u) {   // ends: the masks hold the entries that were counted
+          if (high) {
+            const uint32_t x = kept_mask(cl == INNER ? 36 + q : 27 + q);
+            m = cl == OUTER ? x & 0xFFFFu : (cl == MIDDLE ? x >> 16 : x);
+            j0 += 32;
+            high = false;
+          } else {
+            const int sc = cell(++q);
+            j0 = L.start[sc];
+            high = L.start[sc + 1] - j0 > 32;
+            m = cells[0];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) cells[c] = cells[c + 1];
+          }
+        }
+        word |= F::pack((uint32_t)(j0 + __builtin_ctz(m)), i);
+        m &= m - 1u;
         ++k;
         if (++i == EPW) {
           *dst = F::seal(word);
-          dst += a.ntot;
+          dst += ntot;
           word = 0u;
           i = 0;
         }
-      });
+      }
+    }
     if (i) *dst = F::seal(word);
     a.vcnt[g] = (uint32_t)kept | (uint32_t)go << 8 | (uint32_t)gm << 16 | (uint32_t)gx << 24;
     a.off_build[g] = a.off_cur[g];
@@ -379,7 +432,7 @@ __device__ __forceinline__ int build_list(const StepArgs& a, const TileRef<T>& t
 template <int T, int COMP, int KERN>
 __device__ __forceinline__ void tile_pass_a_step(const StepArgs& a, int w, int part, int parts, bool renew) {
   __shared__ CellLDS<T> L;
-  __shared__ int2 s_x[TileCfg<T, KERN>::MAXP];
+  __shared__ int2 s_x[TileCfg<T, KERN>::MAXP + 3];   // the build reads four records at a time
   TileRef<T> t(a, w, part, parts);
   ConstRep& R = rep_of_tile(a, t.rep);
   Lane<T> l;
@@ -1076,7 +1129,7 @@ __global__ __launch_bounds__(WG) void k_pass_a(const StepArgs a) {
 // One kernel whether or not this step renews the list (the requests, where a rebin
 // renews it too, or a list in the other order).
 template <int T, int COMP, int KERN, bool PARTS>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(T == 8 && KERN == 0 ? 7 : 8)))
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(7)))
 void k_pass_a_step(const StepArgs a) {
   const bool renew = (a.req_cur[0] | a.req_cur[1] | (a.flags[FLAG_ORDER] ^ LIST_BY_DISTANCE)) != 0u;   // loaded together
   for (int w = blockIdx.x; w < a.nwork; w += gridDim.x) {
@@ -1087,8 +1140,9 @@ void k_pass_a_step(const StepArgs a) {
 
 // Occupancy targets (waves per SIMD) of the pair passes: more resident waves
 // hide the LDS and list latency in each pair's dependency chain; at its target
-// no variant spills vector registers (nor does pass A at 8, or 7 with the 8 x 8
-// tile of the quintic).
+// no variant spills vector registers (nor does pass A at 7: most of its variants
+// take 64 registers and so run 8, and a target of 8 leaves them 16 scalar registers
+// fewer, which they spill).
 template <int T, int COMP, int FORM, int EL, int KERN>
 struct Waves {
   static constexpr int B = ((T == 4 || KERN == 1) && (COMP == 0 || (COMP == 1 && FORM == 0))) ? 5 : 1;

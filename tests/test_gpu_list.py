@@ -185,3 +185,79 @@ def test_captured_steps_replay_after_steps_of_the_other_kind(tile, lpp, L, kw):
             s.step_learned(z, 2, 4, 1.0)
     for s in (a, b, z):
         s.close()
+
+
+@pytest.mark.parametrize("kernel,tile,lpp", [(0, 4, 1), (0, 8, 2), (1, 8, 1), (1, 4, 1)])
+def test_list_of_full_cells(kernel, tile, lpp):
+    """Cells of more than the 32 particles that one mask word of the build holds: the
+    neighbour sets against the oracle's predicate, and the list itself: no entry
+    twice, outer entries first, then middle, then inner."""
+    import paper_2108_08919_amd as P
+    L = 40
+    p = wl.Params(L=float(L), kernel=kernel)
+    s0 = random_state(L, 3)
+    kap = oracle.kappa(kernel)
+    nc = int(np.floor(L / (kap * p.h + p.skin)))
+    cs = L / nc
+    rng = np.random.default_rng(5)
+    ex = 24 if kernel == 0 else 28
+    for cx, cy in ((2, 3), (7, 1), (0, nc - 1)):
+        add = dict(x=(cx + 0.02 + 0.96 * rng.random(ex)) * cs, y=(cy + 0.02 + 0.96 * rng.random(ex)) * cs, rho=np.ones(ex))
+        s0 = {f: np.concatenate([s0[f], add.get(f, np.zeros(ex))]) for f in s0}
+    n = s0["x"].size
+    print("full cells", kernel, tile, lpp, flush=True)
+    sim = P.Sim([p], [n])
+    sim.set_option(P.NEM_OPT_TILE, tile)
+    sim.set_option(P.NEM_OPT_LPP, lpp)
+    sim.set_state(0, s0)
+    rp, col, cxy, oxy = sim.neighbor_list(0, 0, offsets=True)
+    sim.check()
+    assert np.bincount(cxy[:, 1] * nc + cxy[:, 0]).max() > 32
+    orp, ocol = oracle.neighbors_offsets(p, nc, cxy, oxy)
+    rows = lambda a, b: [sorted(b[a[i]:a[i + 1]]) for i in range(a.size - 1)]
+    assert rows(rp, col) == rows(orp, ocol)
+    # every entry of the list, by id
+    vrp, vcol = sim.neighbor_list(0, 1)
+    x = np.asarray(cxy, dtype=np.float64) * cs + oxy
+    delta = 0.075 * p.h
+    r = np.concatenate([np.linalg.norm((d := x[vcol[vrp[i]:vrp[i + 1]]] - x[i]) - L * np.round(d / L), axis=1)
+                        for i in range(n)])
+    assert all(np.unique(c).size == c.size for c in (vcol[vrp[i]:vrp[i + 1]] for i in range(n)))
+    assert r.max() < kap * p.h + delta + 1e-5
+    brute = sum(int((np.linalg.norm((d := x - x[i]) - L * np.round(d / L), axis=1) < kap * p.h + delta).sum()) - 1
+                for i in range(n))
+    assert abs(vcol.size - brute) <= 4   # pairs within rounding of the radius
+    # class bounds of the counts (bits 8-15, 16-23) are met by every particle of a tile's group
+    buf = sim.save_raw()
+    cnt = buf[-12 * n:-8 * n].view(np.uint32)
+    assert (cnt & 255).sum() == vcol.size
+    assert np.all((cnt >> 8 & 255) <= (cnt >> 16 & 255)) and np.all((cnt >> 16 & 255) <= (cnt & 255))
+    sim.close()
+
+
+def test_renewing_the_list_costs_few_walks():
+    """Pass A of a step that renews the list against one that walks it, on a box that
+    fills the chip: 5.1 walks; 8.1 with a sweep over the candidates for each class."""
+    import paper_2108_08919_amd as P
+    L = 1024
+    p = wl.Params(L=float(L))
+    sim = P.Sim([p], [L * L])
+    sim.set_state(0, random_state(L, 3))
+    sim.step(3)
+    sim.check()
+    ms = []
+    for renew in (0, 1):
+        best = np.inf
+        for _ in range(12):
+            if renew:
+                sim.set_option(P.NEM_OPT_TILE, 4)
+            sim.set_option(P.NEM_OPT_TIMING, 1)
+            sim.pass_times(reset=True)
+            sim.step(1)
+            sim.check()
+            best = min(best, sim.pass_times(reset=True)[0][1])
+            sim.set_option(P.NEM_OPT_TIMING, 0)
+        ms.append(best)
+    print("walk", ms[0], "renewed", ms[1], flush=True)
+    assert ms[1] < 6.5 * ms[0]
+    sim.close()
