@@ -587,12 +587,13 @@ int enqueue_step(nem_sim* s, hipStream_t st) {
 }
 
 void drop_graphs(nem_sim* s) {
-  for (auto& g : s->graph)
-    if (g) { hipGraphExecDestroy(g); g = nullptr; }
+  for (auto& order : s->graph)
+    for (auto& g : order)
+      if (g) { hipGraphExecDestroy(g); g = nullptr; }
 }
 
-// Capture graph_steps consecutive steps starting at each parity into a graph
-// (once per configuration). No memset nodes: every clear is a kernel.
+// Capture graph_steps consecutive steps of the current list order starting at each
+// parity into a graph (once per configuration and order). No memset nodes: every clear is a kernel.
 int capture_graphs(nem_sim* s) {
   if (!s->cap_stream) HIPCHK(hipStreamCreateWithFlags(&s->cap_stream, hipStreamNonBlocking));
   const int saved = s->parity;
@@ -611,7 +612,7 @@ int capture_graphs(nem_sim* s) {
     hipError_t e = hipStreamEndCapture(s->cap_stream, &g);
     if (rc) { if (g) hipGraphDestroy(g); s->parity = saved; return rc; }
     if (e != hipSuccess) { s->parity = saved; return hip_fail(s, e, "hipStreamEndCapture"); }
-    e = hipGraphInstantiate(&s->graph[par], g, nullptr, nullptr, 0);
+    e = hipGraphInstantiate(&s->graph[s->cell_order][par], g, nullptr, nullptr, 0);
     hipGraphDestroy(g);
     if (e != hipSuccess) { s->parity = saved; return hip_fail(s, e, "hipGraphInstantiate"); }
   }
@@ -660,8 +661,9 @@ int deposit_grid(nem_sim* s, int r, int M) {
 }
 
 int run_steps(nem_sim* s, int64_t nsteps) {
-  const bool graph = s->use_graph && !s->timing && !s->feat && !s->cell_order;
-  if (graph && !s->graph[0]) {
+  // fallback and sample steps are mult of them: where that is less than a chunk they have no use for a capture
+  const bool graph = s->use_graph && !s->timing && !s->feat && (!s->cell_order || nsteps >= s->graph_steps);
+  if (graph && !s->graph[s->cell_order][0]) {
     int rc = capture_graphs(s);
     if (rc) { drop_graphs(s); return rc; }
   }
@@ -670,7 +672,7 @@ int run_steps(nem_sim* s, int64_t nsteps) {
     // whole chunks of graph_steps steps; the parity after a chunk flips only
     // when the chunk length is odd
     for (; it + s->graph_steps <= nsteps; it += s->graph_steps) {
-      HIPCHK(hipGraphLaunch(s->graph[s->parity], s->stream));
+      HIPCHK(hipGraphLaunch(s->graph[s->cell_order][s->parity], s->stream));
       if (s->graph_steps & 1) s->parity ^= 1;
     }
   }

@@ -59,7 +59,7 @@ struct nem_sim {
   std::vector<EvRec> ev_pend;
   int use_graph = 0;
   hipStream_t cap_stream = nullptr;
-  hipGraphExec_t graph[2] = {nullptr, nullptr};
+  hipGraphExec_t graph[2][2] = {};   // of steps by distance and by cell, starting at each parity
   double pass_ms[NEM_NPASS] = {0};
   int64_t pass_n[NEM_NPASS] = {0};
   // grid-diagnostic buffers (allocated on first use, grown with M)

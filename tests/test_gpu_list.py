@@ -261,3 +261,66 @@ def test_renewing_the_list_costs_few_walks():
     print("walk", ms[0], "renewed", ms[1], flush=True)
     assert ms[1] < 6.5 * ms[0]
     sim.close()
+
+
+@pytest.mark.parametrize("graph,mult", [(2, 5), (3, 3), (4, 3)])
+def test_fine_steps_of_learned_calls_replay_graphs(graph, mult):
+    """Fallback and sample steps with NEM_OPT_GRAPH on: whole chunks and what is left
+    over, an odd chunk (the parity flips), a chunk longer than the run; with
+    ordinary steps, which replay graphs of their own, between them. Bit for bit the
+    same calls without graphs, at each turn."""
+    import paper_2108_08919_amd as P
+    L = 37
+    N = L * L
+    p = wl.Params(L=float(L), zeta=0.03)
+    s0 = random_state(L, 4, amp_u=2e-3)
+    print("graphs", graph, mult, flush=True)
+    net = P.Mlp()
+    net.set_weights(np.random.default_rng(2).normal(0.0, 0.1, net.nparams).astype(np.float32))
+    sims = []
+    for g in (graph, 0):
+        s = P.Sim([p], [N])
+        s.set_option(P.NEM_OPT_GRAPH, g)
+        s.set_state(0, s0)
+        s.step(4)
+        sims.append(s)
+    for turn in range(3):
+        seen = []
+        for s in sims:
+            fallbacks, _ = s.step_learned(net, 3, mult, 1e-6)   # every macro step is replayed as fine steps
+            assert fallbacks == 3
+            X, T = s.samples(mult)
+            s.step(7)
+            s.check()
+            seen.append((s.get_state(0), X.cpu().numpy(), T.cpu().numpy()))
+        (ga, xa, ta), (gb, xb, tb) = seen
+        assert all(np.array_equal(ga[k], gb[k]) for k in ga), turn
+        assert np.array_equal(xa, xb) and np.array_equal(ta, tb), turn
+    for s in sims:
+        s.close()
+    net.close()
+
+
+def test_fine_steps_of_learned_calls_gain_from_graphs():
+    """512 fine steps of a sampling call on a box where launches count, with chunks of
+    32 steps replayed and with eager launches: 0.95 of the time (1.00 when these
+    steps took no part in the graphs)."""
+    import time
+    import paper_2108_08919_amd as P
+    L = 32
+    sim = P.Sim([wl.Params(L=float(L))], [L * L])
+    sim.set_state(0, random_state(L, 3))
+    sim.step(3)
+    sim.check()
+    best = {0: np.inf, 32: np.inf}
+    for _ in range(4):
+        for g in best:
+            sim.set_option(P.NEM_OPT_GRAPH, g)
+            sim.samples(512)   # with the capture
+            for _ in range(3):
+                t0 = time.perf_counter()
+                sim.samples(512)
+                best[g] = min(best[g], time.perf_counter() - t0)
+    print("eager", best[0], "graphs", best[32], flush=True)
+    assert best[32] < 0.985 * best[0]
+    sim.close()
