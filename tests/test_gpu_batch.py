@@ -165,3 +165,40 @@ def test_persistent_grid_equals_dispatch():
         for a, b in zip(out[0], other):
             for k in a:
                 assert np.array_equal(a[k], b[k]), k
+
+
+# box whose full tiles hold more than the 256 particles of a workgroup's round: shared by
+# two workgroups (97, tile 4: 261), four (45, tile 8: 1071; the last part takes two
+# rounds) or two (64, tile 8 of Wendland C2: 495) while it is alone; and companions with
+# so many tiles that one workgroup takes a tile
+@pytest.mark.parametrize("kernel,tile,side,company", [(0, 4, 97, (300, 300)), (0, 8, 45, (600,)), (1, 8, 64, (600,))])
+@pytest.mark.parametrize("lpp", [1, 2])
+def test_shared_tiles_give_the_same_bits(kernel, tile, side, company, lpp):
+    """How many workgroups share a tile follows from the whole launch, so a replica
+    takes another variant of the passes alone than in company: bit for bit the same,
+    over steps that build the list, walk it and rebin."""
+    import paper_2108_08919_amd as P
+    p = wl.Params(L=float(side), zeta=0.02, dt=0.01, kernel=kernel)
+    s0 = random_state(side, 8, amp_u=0.05)
+    s0["ux"] = s0["ux"] + 2.5   # 0.025 a step: a new list every two steps, rebins
+    s0["uy"] = s0["uy"] - 1.5
+    print("shared tiles", kernel, tile, side, company, lpp, flush=True)
+
+    def run(reps):
+        sim = P.Sim([q for q, _ in reps], [s["x"].size for _, s in reps])
+        sim.set_option(P.NEM_OPT_TILE, tile)
+        sim.set_option(P.NEM_OPT_LPP, lpp)
+        for r, (_, s) in enumerate(reps):
+            sim.set_state(r, s)
+        out = []
+        for _ in range(4):
+            sim.step(3)
+            sim.check()
+            out.append(sim.get_state(0))
+        sim.close()
+        return out
+    alone = run([(p, s0)])
+    crowd = run([(p, s0)] + [(wl.Params(L=float(c), zeta=0.02, dt=0.01, kernel=kernel), random_state(c, 9, amp_u=0.05))
+                             for c in company])
+    for k, (a, b) in enumerate(zip(alone, crowd)):
+        assert all(np.array_equal(a[f], b[f]) for f in a), k

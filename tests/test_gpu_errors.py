@@ -125,3 +125,43 @@ def test_duplicated_particle_matches_oracle():
     for k in ("x", "y", "ux", "uy", "qxx", "qxy", "rho"):
         assert g[k][i] == g[k][j] and o[k][i] == o[k][j], k
     sim.close()
+
+
+@pytest.mark.parametrize("tile", [4, 8])
+def test_rebin_of_an_overfull_cell_keeps_its_order(tile):
+    """A rebin that gathers more than the 64 particles of a wave in one cell (an error
+    that the build reports) still puts every particle in its cell, ordered by id, once
+    each: the ids, cells and cell starts of a checkpoint."""
+    import ctypes as C
+    import paper_2108_08919_amd as P
+    L, n = 32, 32 * 32
+    p = wl.Params(L=float(L), zeta=0.0, K=0.02, dt=0.01)
+    s0 = random_state(L, 5, amp_u=0.0)
+    s0["ux"] = s0["ux"] + 2.5                # 0.025 a step; cells of side 4, rebinned 0.05 past the edge
+    rng = np.random.default_rng(11)
+    idx = rng.choice(n, 90, replace=False)
+    s0["x"][idx] = rng.uniform(11.9, 11.99, 90)   # cell [8, 12)^2, about to leave it
+    s0["y"][idx] = rng.uniform(8.2, 11.8, 90)
+    sim = P.Sim([p], [n])
+    sim.set_option(P.NEM_OPT_TILE, tile)
+    sim.set_state(0, s0)
+    full = []
+    for _ in range(6):
+        P.lib().nem_step(C.c_void_p(sim.h), 1)
+        nb = C.c_uint64(0)
+        assert P.lib().nem_raw_bytes(C.c_void_p(sim.h), C.byref(nb)) == P.NEM_OK
+        buf = np.empty(nb.value, dtype=np.uint8)
+        assert P.lib().nem_save_raw(C.c_void_p(sim.h), buf.ctypes.data_as(C.c_void_p), nb) == P.NEM_E_OVERFLOW
+        # header, then offsets, low parts, u, Q, Qyy, a and rho before the ids
+        o = 8 + 64 + (8 + 8 * 17 + 8 * 7) + n * (4 * 8 + 4 + 8 + 4)
+        ids = buf[o:o + 4 * n].view(np.int32)
+        cell = buf[o + 4 * n:o + 8 * n].view(np.int32)
+        start = buf[o + 16 * n:o + 16 * n + 4 * 65].view(np.int32)   # after the image counters
+        assert np.array_equal(np.sort(ids), np.arange(n))
+        assert start[0] == 0 and start[-1] == n
+        assert np.array_equal(cell, np.repeat(np.arange(64), np.diff(start)))
+        assert all(np.all(np.diff(ids[a:b]) > 0) for a, b in zip(start[:-1], start[1:]))
+        full.append((np.diff(start).max(), int(np.diff(start).argmax())))
+    print("fullest cell and its index", full, flush=True)
+    assert full[0][0] > 64 and full[-1][0] > 64 and full[0][1] != full[-1][1]   # the crowd changed cells
+    sim.close()

@@ -353,3 +353,47 @@ def test_large_multipliers_zero_net_fallback_and_gain(mult):
         assert nfb == 0
     assert min(gains["q"]) > 1.5 and min(gains["u"]) > 1.2
     m.close(); z.close()
+
+
+@pytest.mark.parametrize("n,batch,epochs", [(1001, 333, 2), (4133, 1000, 3), (96, 32, 2)])
+def test_training_follows_adam_on_the_rows_of_every_batch(n, batch, epochs):
+    """Several batches an epoch and several epochs against a replay on the host: the
+    rows (k stride + offset) mod n of each batch, the library's gradient of those
+    rows at the replayed weights, and Adam's moments and bias correction carried in
+    FP64. Between the two stand the rounding of weights to FP32 and, where that
+    flips the BF16 rounding of a weight, 2^-8 of one weight in the gradient: about
+    1e-3 of a step; held to 2% of the distance trained. (A wrong moment, count of
+    steps or set of rows changes a step by tens of percent.)"""
+    import math
+    import torch
+    import paper_2108_08919_amd as P
+    m, Xt, Tt, *_ = setup(n, 6)
+    w = m.get_weights().astype(np.float64)
+    w0 = w.copy()
+    twin = P.Mlp()
+    twin.set_norm(IDENT)
+    stride = int(0.6180339887 * n) | 1
+    while math.gcd(stride, n) != 1:
+        stride += 2
+    lr, t, loss = 1e-3, 0, 0.0
+    mo, ve = np.zeros_like(w), np.zeros_like(w)
+    for e in range(epochs):
+        off = (e + 1) * 2654435761 % n
+        for first in range(0, n - batch + 1, batch):
+            rows = torch.tensor([((first + k) * (stride % n) + off) % n for k in range(batch)], device="cuda")
+            twin.set_weights(w.astype(np.float32))
+            g, loss = twin.grad(Xt[rows].contiguous(), Tt[rows].contiguous())
+            g = g.astype(np.float64)
+            t += 1
+            mo = 0.9 * mo + 0.1 * g
+            ve = 0.999 * ve + 0.001 * g * g
+            w = w - lr * (mo / (1 - 0.9 ** t)) / (np.sqrt(ve / (1 - 0.999 ** t)) + 1e-8)
+    last = m.train(Xt, Tt, epochs=epochs, batch=batch, lr=lr)
+    w1 = m.get_weights().astype(np.float64)
+    err = np.linalg.norm(w1 - w) / np.linalg.norm(w - w0)
+    print("train", n, batch, epochs, "steps", t, "distance", np.linalg.norm(w - w0), "off by", err, flush=True)
+    assert t == epochs * (n // batch) and t > 2
+    assert err <= 2e-2
+    assert last == pytest.approx(loss, rel=1e-3)
+    m.close()
+    twin.close()
