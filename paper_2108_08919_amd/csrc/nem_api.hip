@@ -369,7 +369,10 @@ int read_flags(nem_sim* s, unsigned* f) {
 constexpr size_t PIN_CHUNK = 4 << 20, PIN_PIECE = 256 << 10, PIN_SMALL = 2 << 20;
 constexpr int PIN_THREADS = 8;
 
+// At the first read (it adds 30 us to it, and as much to nem_destroy): a simulation
+// that is never read holds none.
 void alloc_pin(nem_sim* s) {
+  s->pin_asked = true;
   const size_t all = sizeof(double) * 9 * (size_t)s->stage_n;
   s->pin_slots = (int)std::min<size_t>(nem_sim::PIN_SLOTS, (all + PIN_CHUNK - 1) / PIN_CHUNK);
   const size_t bytes = (std::min(all, PIN_CHUNK * s->pin_slots) + 63) / 64 * 64;
@@ -425,6 +428,7 @@ int copy_out(nem_sim* s, int nf, double* const* dst, const double* src, size_t n
       o += k;
     }
   };
+  if (!s->pin && !s->pin_asked && m > 0) alloc_pin(s);
   if (!s->pin) {
     for (int f = 0; f < m; ++f) HIPCHK(hipMemcpyAsync(part[f].to, part[f].from, fb, hipMemcpyDeviceToHost, s->stream));
     HIPCHK(hipStreamSynchronize(s->stream));
@@ -794,7 +798,6 @@ int nem_create(const nem_params* p, const int64_t* n, int32_t R, void* dev_arena
   if (e != hipSuccess) { hip_fail(s, e, "arena init"); nem_destroy(s); return NEM_E_HIP; }
   rc = build_work(s);
   if (rc) { nem_destroy(s); return rc; }
-  alloc_pin(s);
   *out = s;
   return NEM_OK;
 }

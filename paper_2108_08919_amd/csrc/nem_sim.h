@@ -43,8 +43,9 @@ struct nem_sim {
   double* stage = nullptr; int64_t stage_n = 0;
   double* red = nullptr;
   // pinned host memory that results are read back through: PIN_SLOTS chunks (fewer
-  // for small boxes), then the flag words; NULL: none could be had
-  char* pin = nullptr; unsigned* pin_flags = nullptr; int pin_slots = 0;
+  // for small boxes), then the flag words; allocated by the first read; NULL: none yet,
+  // or none could be had
+  char* pin = nullptr; unsigned* pin_flags = nullptr; int pin_slots = 0; bool pin_asked = false;
   static constexpr int PIN_SLOTS = 4;
   hipEvent_t pin_ev[PIN_SLOTS] = {}, pin_begin = nullptr;
   int parity = 0;
