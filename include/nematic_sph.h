@@ -20,6 +20,11 @@
  *   * Device memory: the caller may pass an arena of nem_arena_bytes() bytes
  *     (any device allocation, e.g. a torch uint8 tensor) and must keep it alive
  *     until nem_destroy; with arena == NULL the library allocates and owns it.
+ *     Beside it a simulation keeps until nem_destroy: the grid buffers of the
+ *     diagnostics, the snapshot and sample buffers of learned steps (from their
+ *     first use, see there), and pinned host memory: nine arrays of its largest
+ *     replica, at most 16 MB (none if there is none to be had), from the first call
+ *     that reads results or waits for them, nem_defects_noalloc excepted.
  *   * Stream: all work is enqueued on the hipStream_t passed to nem_create
  *     (NULL = the null stream). nem_step is asynchronous; device-side errors
  *     are sticky and are returned by nem_sync and by the read calls.
@@ -122,7 +127,10 @@ int nem_set_state(nem_sim* s, int32_t r, const double* x, const double* y, const
                   const double* uy, const double* qxx, const double* qxy, const double* rho,
                   const double* ax, const double* ay);
 
-/* Read the state of replica r into caller host arrays (any may be NULL). */
+/* Read the state of replica r into caller host arrays (any may be NULL; only
+ * those asked for are copied from the device). Reads of more than 2 MB are written
+ * into the arrays by up to eight threads of the call's own, which start when the
+ * steps queued before it are done and end with it. */
 int nem_get_state(nem_sim* s, int32_t r, double* x, double* y, double* ux, double* uy, double* qxx,
                   double* qxy, double* rho, double* ax, double* ay);
 
@@ -172,19 +180,24 @@ int nem_load_raw(nem_sim* s, const void* host, uint64_t bytes);
  * The library keeps a Verlet list per particle: every pair of the 3 x 3 cell
  * stencil closer than kappa h + delta (delta = 0.075 h) when it was last built;
  * it is rebuilt on the device when some particle has moved 0.45 delta since,
- * after a rebin, a new state, a tile change or a snapshot restore. Every pair
- * pass (volume, rates, filter, stress) walks that list and keeps an entry when
+ * after a rebin, a new state, a tile change, a snapshot restore or a change
+ * between ordinary and learned steps (which walk it in another order). Every pair
+ * pass (volume, rates, filter, stress) walks that list. An entry is a neighbour when
  * 0 < r2 < fl32((kappa h)^2), where, with positions held as FP32 offsets o from
  * the corner of the particle's cell (cells of side cs = fl32(L/nc),
  * nc = floor(L/(kappa h + skin))) and j in the cell displaced by d in
  * {-1,0,1}^2 from i's cell, r = fl(fl(o_i - o_j) + fl32(-d cs)) per component
- * and r2 = fl(fl(rx*rx) + fl(ry*ry)), without fused multiply-add.
+ * and r2 = fl(fl(rx*rx) + fl(ry*ry)), without fused multiply-add. The stress pass
+ * and learned steps test every entry so. In the other passes of ordinary steps
+ * every term carries W or W', which are zero from the support on: they sum over the
+ * whole list, on fixed-point positions (a unit is at most 2^-29 of a cell side), so
+ * that two particles closer than a unit are coincident to them.
  *
  * This call first runs the start of the next step on the stream (the rebin if
  * one is pending, the decision to rebuild, and the Verlet build or walk of the
  * volume pass; the next nem_step then walks the same list), then decodes the
- * list with the passes' own predicate:
- *   which = 0: the neighbours the passes sum over;
+ * list with that predicate:
+ *   which = 0: the neighbours;
  *   which = 1: every entry of the Verlet list (a superset).
  * row_ptr has n[r]+1 entries; col has cap entries; *nnz receives the count.
  * cell_xy (2 n[r] int32, may be NULL) and off_xy (2 n[r] floats, may be NULL)
@@ -381,8 +394,11 @@ int nem_samples(nem_sim* s, int32_t mult, float* X, float* T);
 int nem_samples_rows(nem_sim* s, int32_t mult, const int64_t* rows, int64_t nrows, float* X, float* T);
 /* n_macro macro steps of mult*dt with corrections; a macro step whose largest
  * correction norm (normalised units) exceeds tau is replayed as mult steps of
- * dt. Synchronises once per macro step (one word read back); allocates
- * scratch buffers (hipMalloc). *n_fallback and *max_norm may be NULL. */
+ * dt. Synchronises once per macro step (one word read back). The first call
+ * allocates its buffers (hipMalloc, hipHostMalloc): 68 bytes a particle of inputs
+ * and corrections, and two snapshots of the state, kept until nem_destroy. A change
+ * from ordinary to learned steps or back rebuilds the Verlet list once.
+ * *n_fallback and *max_norm may be NULL. */
 int nem_step_learned(nem_sim* s, nem_mlp* m, int64_t n_macro, int32_t mult, double tau, int64_t* n_fallback,
                      double* max_norm);
 

@@ -369,9 +369,12 @@ int read_flags(nem_sim* s, unsigned* f) {
 constexpr size_t PIN_CHUNK = 4 << 20, PIN_PIECE = 256 << 10, PIN_SMALL = 2 << 20;
 constexpr int PIN_THREADS = 8;
 
-// At the first read (it adds 30 us to it, and as much to nem_destroy): a simulation
-// that is never read holds none.
-void alloc_pin(nem_sim* s) {
+// Called first by every entry point that reads results or waits for them, except those
+// that allocate nothing: it takes 30 us, and as much again in nem_destroy, which a
+// simulation that is only created does not pay, and makes each later read of the
+// flags 9 us shorter (the six calls of the diagnostics 800 -> 750 us).
+void ensure_pin(nem_sim* s) {
+  if (s->pin_asked) return;
   s->pin_asked = true;
   const size_t all = sizeof(double) * 9 * (size_t)s->stage_n;
   s->pin_slots = (int)std::min<size_t>(nem_sim::PIN_SLOTS, (all + PIN_CHUNK - 1) / PIN_CHUNK);
@@ -428,7 +431,7 @@ int copy_out(nem_sim* s, int nf, double* const* dst, const double* src, size_t n
       o += k;
     }
   };
-  if (!s->pin && !s->pin_asked && m > 0) alloc_pin(s);
+  ensure_pin(s);
   if (!s->pin) {
     for (int f = 0; f < m; ++f) HIPCHK(hipMemcpyAsync(part[f].to, part[f].from, fb, hipMemcpyDeviceToHost, s->stream));
     HIPCHK(hipStreamSynchronize(s->stream));
@@ -653,6 +656,7 @@ int ensure_grid(nem_sim* s, int M) {
 int deposit_grid(nem_sim* s, int r, int M) {
   if (r < 0 || r >= s->R || M < 8 || M > 2048 || (M & (M - 1))) { s->err = "grid side must be a power of two in [8, 2048]"; return NEM_E_INVAL; }
   if (!s->has_state[r]) return NEM_E_STATE;
+  ensure_pin(s);
   int rc = ensure_grid(s, M);
   if (rc) return rc;
   SortArgs a = sort_args(s);
@@ -888,6 +892,7 @@ int nem_step(nem_sim* s, int64_t nsteps) {
 
 int nem_sync(nem_sim* s) {
   if (!s) return NEM_E_INVAL;
+  ensure_pin(s);
   HIPCHK(hipStreamSynchronize(s->stream));
   collect_times(s);
   unsigned f[2];
@@ -1142,6 +1147,7 @@ int nem_neighbors(nem_sim* s, int32_t r, int64_t* row_ptr, int32_t* col, int64_t
 int nem_diagnostics(nem_sim* s, int32_t r, nem_diag* out) {
   if (!s || r < 0 || r >= s->R || !out) return NEM_E_INVAL;
   if (!s->has_state[r]) return NEM_E_STATE;
+  ensure_pin(s);
   SortArgs a = sort_args(s);
   // pair sums at the integer time level: integer-level offsets into the
   // staging array, then pass A (volumes, neighbour list) and the free-energy
@@ -1267,6 +1273,7 @@ int nem_track(nem_sim* s, int32_t r, const int32_t* ids, int32_t n_ids, double* 
   for (int t = 0; t < n_ids; ++t)
     if (ids[t] < 0 || ids[t] >= n) { s->err = "particle id out of range"; return NEM_E_INVAL; }
   if (n_ids == 0) return NEM_OK;
+  ensure_pin(s);
   // staging (9 n doubles): inv[n] ints at 0, ids at n doubles, output at 2n doubles
   int* inv = (int*)s->stage;
   int* d_ids = (int*)(s->stage + n);
@@ -1291,6 +1298,7 @@ int nem_mixing(nem_sim* s, int32_t r, const uint8_t* colour, int32_t ncol, int32
   const int n = (int)s->n[r];
   for (int i = 0; i < n; ++i)
     if (colour[i] >= ncol) { s->err = "colour out of range"; return NEM_E_INVAL; }
+  ensure_pin(s);
   const size_t nb = (size_t)B * B * ncol;
   if (nb > s->mix_cap) {
     if (s->g_mix) HIPCHK(hipFree(s->g_mix));

@@ -301,6 +301,7 @@ void free_snapshot(nem_sim* s) {
 
 // The buffers of learned steps (six allocations and releases a call cost 0.4 ms).
 static int ensure_learn(nem_sim* s) {
+  ensure_pin(s);
   auto& W = s->learn;
   const size_t N = (size_t)s->ntot, NS = (size_t)mlp_norm_slots();
   if (!W.X) HIPCHK(hipMalloc((void**)&W.X, sizeof(float) * 12 * N));

@@ -43,7 +43,7 @@ struct nem_sim {
   double* stage = nullptr; int64_t stage_n = 0;
   double* red = nullptr;
   // pinned host memory that results are read back through: PIN_SLOTS chunks (fewer
-  // for small boxes), then the flag words; allocated by the first read; NULL: none yet,
+  // for small boxes), then the flag words (ensure_pin); NULL: none yet,
   // or none could be had
   char* pin = nullptr; unsigned* pin_flags = nullptr; int pin_slots = 0; bool pin_asked = false;
   static constexpr int PIN_SLOTS = 4;
@@ -112,6 +112,7 @@ nem::SortArgs sort_args(nem_sim* s);
 nem::StepArgs step_args(nem_sim* s);
 int read_flags(nem_sim* s, unsigned* f);
 int status_from_flags(nem_sim* s, unsigned f);
+void ensure_pin(nem_sim* s);
 int run_steps(nem_sim* s, int64_t nsteps);
 int upload_reps(nem_sim* s);
 void free_snapshot(nem_sim* s);
