@@ -545,6 +545,8 @@ __global__ __launch_bounds__(256) void k_mlp_stats(const float* X, const float* 
 // ---------------------------------------------------------------- launchers
 int mlp_nparam() { return NPARAM; }
 int mlp_norm_slots() { return NORM_SLOTS; }
+// Partial sums of a batch: their grouping fixes the bits of a gradient and of a
+// trained network, so it stays as it is though nothing asks for an even number.
 int mlp_backward_parts(int64_t B) {
   const int64_t nblk = (B + ROWS - 1) / ROWS;
   return (int)std::min<int64_t>(std::max<int64_t>(nblk, 2), 1024) / 2 * 2;

@@ -416,8 +416,11 @@ __device__ __forceinline__ void tile_cells(const TileRef<T>& t, CellLDS<T>& L) {
 // for which the 2^32 units are at least 3.5 cell sides. Differences of
 // neighbours are exact modulo 2^32, so a pair needs no image shift and is
 // rounded once, in the conversion to float; a unit is 2^-28 dx for cells of
-// 4 dx, 16 to 64 times finer than the FP32 offsets it is taken from. Distances
-// are in units; the powers of two come out of the sums at the end.
+// 4 dx: 16 to 64 times finer than the FP32 offsets it is taken from where these
+// are above half a dx, coarser below dx / 16. Two particles closer than a unit are
+// coincident here (no pair); pass D, on the offsets, takes them as neighbours, and its
+// APD sums grow as r^-2 there as they would in any case. Distances are in units; the
+// powers of two come out of the sums at the end.
 template <typename Rep>
 __device__ __forceinline__ int2 fixed_position(Rep& R, float2 off, int entry) {
   const int rx = (entry >> 16) & 15, ry = (entry >> 20) & 15;

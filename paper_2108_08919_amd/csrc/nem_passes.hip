@@ -25,9 +25,9 @@
 // scalar; and positions are fixed-point where no predicate is decided, which
 // takes the direction code, its decoding and its table read out of every pair.
 // Vector instructions per particle of passes A, B, C, D on the 2048^2 box: 1748,
-// 3522, 2103, 2382 -> 923, 2945, 1379, 1888; time 170, 321, 208, 237 -> 105, 265,
-// 156, 193 us; on the 64^2 box, where a pass is one workgroup's latency, 17.1,
-// 18.7, 16.8, 18.4 -> 8.9, 14.2, 10.8, 14.5 us.
+// 3522, 2103, 2382 -> 984, 2947, 1321, 1832; time 170, 321, 208, 237 -> 102, 247,
+// 146, 183 us; on the 64^2 box, where a pass is one workgroup's latency, 17.1,
+// 18.7, 16.8, 18.4 -> 8.7, 14.4, 10.8, 14.1 us.
 //
 //   pass A  Verlet list (rebuilt from the ~144 candidates of the stencil when
 //           particles have moved too far); volume V_i = 1 / sum_j W_ij
